@@ -196,7 +196,7 @@ struct CnnInputArgs {
 };
 
 // Kernel entry points (taken by address in the launcher).
-const void* wr_small_kernel_ptr();
+const void* wr_small_kernel_ptr(int H);
 const void* wr_uniforms_kernel_ptr();
 const void* wr_persist_kernel_ptr(int KH);   // null if no instantiation for KH
 const void* wr_score_kernel_ptr(int KT2);    // teacher-forced recurrence for H = 32 KT2; null if none

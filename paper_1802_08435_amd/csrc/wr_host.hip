@@ -67,7 +67,6 @@ struct wavernn_model {
   // small path
   float* d_image = nullptr;
   float* d_Wc = nullptr;
-  SmallLayout sl;
   // persistent path
   PersistPlan plan;
   const void* pk = nullptr;          // kernel instantiation for the plan
@@ -250,7 +249,6 @@ wavernn_status build_small(wavernn_model* m, const wavernn_weights* w) {
   const wavernn_config& c = m->cfg;
   const int H = c.hidden, Hh = H / 2;
   const SmallLayout L = small_layout(H);
-  m->sl = L;
   Rounder rd{c.weight_dtype == WAVERNN_BF16};
   REff R{&m->cfg, w};
   std::vector<float> img(L.image_floats, 0.0f);
@@ -287,7 +285,6 @@ wavernn_status build_small(wavernn_model* m, const wavernn_weights* w) {
     s = m->upload(&m->d_Wc, wc.data(), wc.size() * 4);
     if (s != WAVERNN_OK) return s;
   }
-  HIPOK(hipFuncSetAttribute(wr_small_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, L.total_floats * 4));
   return WAVERNN_OK;
 }
 
@@ -1227,7 +1224,7 @@ wavernn_status run_small(wavernn_model* m, const RunIO& io) {
   if (io.init) { a.h_in = io.init->h; a.c_in = io.init->c_prev; a.f_in = io.init->f_prev; }
   if (io.fin) { a.h_out = io.fin->h; a.c_out = io.fin->c_prev; a.f_out = io.fin->f_prev; }
   void* args[] = {&a};
-  HIPOK(hipLaunchKernel(wr_small_kernel_ptr(), dim3(io.S), dim3(256), args, m->sl.total_floats * 4, io.st));
+  HIPOK(hipLaunchKernel(wr_small_kernel_ptr(m->cfg.hidden), dim3(io.S), dim3(WR_SMALL_THREADS), args, 0, io.st));
   return WAVERNN_OK;
 }
 
@@ -1783,8 +1780,7 @@ wavernn_status wavernn_create(const wavernn_config* cfg, const wavernn_weights* 
     return fail(WAVERNN_E_HIP, "no HIP device");
   }
   const int H = cfg->hidden;
-  const SmallLayout L = small_layout(H);
-  const bool small_fits = (size_t)L.total_floats * 4 + 256 <= 160 * 1024;
+  const bool small_fits = H <= WR_SMALL_MAXH;
   const int B = cfg->subscale;
   if (cfg->fused) {
     // Fused Subscale WaveRNN 2x (Sec. 4.4): the batch-1 persistent structure
@@ -1955,7 +1951,7 @@ int32_t wavernn_model_path(const wavernn_model* m, int32_t n_streams, int32_t* g
   int g = 0, b = 0, path = (int)m->path;
   BatchPlan B;
   if (m->path == PATH_SMALL) {
-    g = n_streams > 0 ? n_streams : 1, b = 256;
+    g = n_streams > 0 ? n_streams : 1, b = WR_SMALL_THREADS;
   } else if (m->path == PATH_BATCHED &&
              batch_plan(m->cfg.hidden, (n_streams > 0 ? n_streams : 1) * m->cfg.subscale, &B, m->cfg.ctx_dim,
                         m->cfg.subscale, horizon_of(m->cfg), lead_of(m->cfg), m->has_cnn)) {

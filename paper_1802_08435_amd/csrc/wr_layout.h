@@ -9,13 +9,15 @@
 #endif
 
 // ---------------------------------------------------------------------------
-// Single-workgroup kernel: one fp32 image copied to LDS, then scratch arrays.
-// Offsets in floats, each region 16-byte aligned.
+// Single-workgroup kernel: one fp32 image of the weights, which the waves load
+// into their registers.  Offsets in floats, each region 16-byte aligned.
 // ---------------------------------------------------------------------------
+#define WR_SMALL_MAXH 72       // the registers of 5 waves hold H <= 72 in fp32
+#define WR_SMALL_THREADS 320
+
 struct SmallLayout {
   int H;
-  int Rt, I, bias, O1t, O2t, O3t, O4t, b1, b2, b3, b4, image_floats;  // image (weights)
-  int add, G, h, hn, hid, z, w, C, total_floats;                       // scratch
+  int Rt, I, bias, O1t, O2t, O3t, O4t, b1, b2, b3, b4, image_floats;
 };
 
 WR_HD inline int wr_take(int& o, int n) {
@@ -41,15 +43,6 @@ WR_HD inline SmallLayout small_layout(int H) {
   L.b3 = wr_take(o, Hh);
   L.b4 = wr_take(o, 256);
   L.image_floats = o;
-  L.add = wr_take(o, 3 * H);
-  L.G = wr_take(o, 3 * H);
-  L.h = wr_take(o, H);
-  L.hn = wr_take(o, H);
-  L.hid = wr_take(o, Hh);
-  L.z = wr_take(o, 256);
-  L.w = wr_take(o, 256);
-  L.C = wr_take(o, 256);
-  L.total_floats = o;
   return L;
 }
 
