@@ -8,12 +8,21 @@
 // rows 2b (bf16 high part) and 2b+1 (remainder), and lane l of the result
 // holds vectors 2(l/16) and 2(l/16)+1 of row l%16.  Per step and half the
 // heads run their O1 rows / O2 columns for all vectors and publish L x 256
-// partial logits.  With L <= 4 every head evaluates every gate of every
-// vector and sums and draws every vector; with L = 8 head j evaluates the
-// gates of its own 64 units for all vectors and the heads exchange those
-// slices of y, and vector v is owned by head v mod NH, which alone sums its
-// partials, draws it and publishes its classes.
+// partial logits, and every head sums and draws every vector.  With L <= 4
+// every head evaluates every gate of every vector; with L = 8 head j evaluates
+// the gates of its own 64 units for all vectors and the heads exchange those
+// slices of y.
+//
+// What bounds a step is the chain of exchanges between workgroups (gate words,
+// y slices at L = 8, partial logits twice, and for subscale the drawn samples),
+// so a group sits whole on one XCD, and when it finds itself there
+// (leads_share_xcd) every word but the drawn samples, which other groups read,
+// is published into that XCD's L2.  H = 896, us a step, with the units spread
+// over the XCDs and one owner drawing each vector, and now: 64 utterances
+// 10.3 -> 7.2, 14 utterances 7.0 -> 5.8, subscale 16 with F = 4 10.0 -> 7.7.
 #include "wr_kern.h"
+
+#include <type_traits>
 
 namespace {
 
@@ -47,26 +56,6 @@ __device__ __forceinline__ int64_t cb_offset(const BatchArgs& a, int v, int64_t 
   return ((int64_t)(v / a.B) * a.n_cb + fr) * 3 * a.P.H;
 }
 
-// Wait until the N words base[k*stride] (k < N) carry `tag`; values to v[].
-template <int N>
-__device__ __forceinline__ bool poll_strided(const xw* base, int stride, uint32_t tag, float* v, const BatchArgs& a) {
-  uint64_t pending = N >= 64 ? ~0ull : (1ull << N) - 1ull;
-  WaitBudget wb{wr_clock(), 0};
-  for (;;) {
-    xw w[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) w[k] = (pending >> k & 1ull) ? xpeek(base + (size_t)k * stride) : 0;
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-      if ((pending >> k & 1ull) && xok(w[k], tag)) {
-        v[k] = xval(w[k]);
-        pending &= ~(1ull << k);
-      }
-    if (!pending) return true;
-    if (!wait_ok(wb, a.err, a.limit, a.err)) return false;
-  }
-}
-
 // A pointer the compiler must treat as recomputed here: keeps address
 // arithmetic inside the step loop instead of hoisting dozens of 64-bit
 // addresses into registers for the whole launch.
@@ -76,65 +65,76 @@ __device__ __forceinline__ T* opaque(T* p) {
   return p;
 }
 
-// Delay (x 64 clocks) before the first probe of words that other workgroups
-// publish at about the time this one starts waiting.  A probe issued at once
-// would almost surely come back without them, a coherent load takes about a
-// microsecond, and many such early probes at once slow the exchange for all
-// (measured: with 8-vector groups a head's y and partial-logit gathers each
-// take about 0.3 to 0.5 us less with this delay than with none).
-#define WR_POLL_DELAY 12
-// The owned partials stay in the group's L2 (leads_share_xcd): their first
-// probe waits less (measured at 64 utterances: 6 x 64 clocks 1.6% faster
-// than 12, and 0.5% faster than 2).
-#define WR_OWN_DELAY 6
-
-// Wait until the N words base + off(k) carry `tag`, storing each value with
-// put(k, value) as it arrives (LDS, not registers).  The addresses are
-// rebuilt in every round from an opaque base, so only the N words in flight
-// occupy registers.
-template <int N, class O, class F>
-__device__ __forceinline__ bool poll_put(const xw* base, O off, F put, uint32_t tag, const BatchArgs& a,
-                                         uint32_t need = ~0u) {
-  static_assert(N <= 32, "one pending bit per word");
-  uint32_t pending = (N >= 32 ? ~0u : (1u << N) - 1u) & need;
-  WaitBudget wb{wr_clock(), 0};
-  for (;;) {
-    const xw* b = opaque(base);
-    xw w[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) w[k] = (pending >> k & 1u) ? xpeek(b + off(k)) : 0;
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-      if ((pending >> k & 1u) && xok(w[k], tag)) {
-        put(k, xval(w[k]));
-        pending &= ~(1u << k);
-      }
-    if (!pending) return true;
-    if (!wait_ok(wb, a.err, a.limit, a.err)) return false;
-  }
+// Operand images of this kernel: the 16 rows of 8 inputs (256 bytes, lane
+// order) padded to 272, so the words of consecutive columns that a wave
+// writes while it gathers fall into different LDS banks.
+__device__ __forceinline__ bf16x8 afrag_p(const unsigned char* img, int kt) {
+  const int l = threadIdx.x & 63;
+  return *(const bf16x8*)(img + kt * WR_FRAGP + (l >> 4) * WR_KGP + (l & 15) * 16);
+}
+// Input column c of vector b of an image.
+__device__ __forceinline__ void aput_p(unsigned char* img, int c, float x, int b) {
+  const float hi = __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+  const __bf16 bh = (__bf16)hi, bl = (__bf16)(x - hi);
+  __bf16* row0 = (__bf16*)(img + (c >> 3) * WR_KGP + 2 * b * 16) + (c & 7);
+  row0[0] = bh;
+  row0[8] = bl;
 }
 
-// poll_put over N pairs of adjacent words read as 64-bit accesses:
-// put(k, first, second) for pair k at base + off(k) (off even).
-template <int N, class O, class F>
-__device__ __forceinline__ bool poll_put2(const xw* base, O off, F put, uint32_t tag, const BatchArgs& a) {
-  static_assert(N <= 32, "one pending bit per pair");
-  uint32_t pending = N >= 32 ? ~0u : (1u << N) - 1u;   // (a 32-bit shift by 32 is undefined)
-  WaitBudget wb{wr_clock(), 0};
+// Delay (x 64 clocks) before the first probe of words that other workgroups
+// publish at about the time this one starts waiting.  A probe issued at once
+// would almost surely come back without them, and the early probes of all
+// workgroups slow the exchange for everyone.  With a group's words in its
+// XCD's L2 the best delay is short (64 utterances / 14 utterances / subscale
+// 16 with F = 4, us a step: 4 x 64 clocks 7.18 / 5.80 / 7.74; 2: 7.23 / 5.81 /
+// 7.80; 10: 7.49 / 5.81 / 8.53).
+#define WR_POLL_DELAY 4
+
+// Gather y [L][HH] of one half of h into operand image `img` (columns 0 ..
+// HH - 1 of each vector): 16-byte loads of four adjacent columns, each word
+// checked for its tag, converted and written as two 8-byte LDS stores (4-byte
+// loads and 2-byte stores made the gather bound by its instructions and by
+// LDS bank conflicts: 9.05 -> 7.3 us a step at 64 utterances).  Quads
+// of columns [skip, skip + 64) (a head's own slice) are left out; skip < 0:
+// none.  With PUT false the words are only waited for.
+template <int L, int HH, bool PUT>
+__device__ __forceinline__ bool gather_y(const xw* Y, uint32_t tag, unsigned char* img, int skip, const BatchArgs& a) {
+  constexpr int Q = HH / 4, N = (L * Q + WR_THREADS - 1) / WR_THREADS;
+  uint32_t pending = 0;
+  xw4 w[N];
+#pragma unroll
+  for (int m = 0; m < N; ++m) {
+    const int q = threadIdx.x + WR_THREADS * m;
+    if (q < L * Q && !(skip >= 0 && (q % Q) / 16 == skip / 64)) pending |= 1u << m;
+  }
+  const uint32_t todo = pending;
+  WaitBudget wb{0, 0};
   for (;;) {
-    const xw* b = opaque(base);
-    uint64_t w[N];
+    const __amdgpu_buffer_rsrc_t r = xrsrc(xopaque(Y), (uint32_t)(L * HH) * 4u);
 #pragma unroll
-    for (int k = 0; k < N; ++k) w[k] = (pending >> k & 1u) ? xpeek2(b + off(k)) : 0;
+    for (int m = 0; m < N; ++m)
+      if (pending >> m & 1u) w[m] = xpeek4(r, 16u * (threadIdx.x + WR_THREADS * m));
 #pragma unroll
-    for (int k = 0; k < N; ++k)
-      if ((pending >> k & 1u) && xok2(w[k], tag)) {
-        put(k, xval((xw)w[k]), xval((xw)(w[k] >> 32)));
-        pending &= ~(1u << k);
-      }
-    if (!pending) return true;
+    for (int m = 0; m < N; ++m)
+      if ((pending >> m & 1u) && xok4(w[m], tag)) pending &= ~(1u << m);
+    if (!pending) break;
+    if (!wb.spins) wb.start = wr_clock();
     if (!wait_ok(wb, a.err, a.limit, a.err)) return false;
   }
+  if (PUT) {
+#pragma unroll
+    for (int m = 0; m < N; ++m)
+      if (todo >> m & 1u) {
+        const int q = threadIdx.x + WR_THREADS * m, b = q / Q, c = 4 * (q % Q);
+        const float x0 = xval(w[m].x), x1 = xval(w[m].y), x2 = xval(w[m].z), x3 = xval(w[m].w);
+        unsigned char* p = img + (c >> 3) * WR_KGP + 2 * b * 16 + (c & 7) * 2;
+        *(uint2*)p = uint2{__builtin_amdgcn_perm(w[m].y, w[m].x, 0x07060302), __builtin_amdgcn_perm(w[m].w, w[m].z, 0x07060302)};
+        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+        auto low = [](float x) { return (__bf16)(x - __uint_as_float(__float_as_uint(x) & 0xffff0000u)); };
+        *(bf16x4*)(p + 16) = bf16x4{low(x0), low(x1), low(x2), low(x3)};
+      }
+  }
+  return true;
 }
 
 // Drawn samples for the subscale context cross groups, whose heads and units
@@ -179,24 +179,22 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
   const int H = P.H, Hh = P.Hh;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   unsigned char* imc = lds;                        // y_c operand image [KT]
-  unsigned char* imf = imc + KT * WR_FRAG;         // y_f operand image [KT]
-  unsigned char* imo = imf + KT * WR_FRAG;         // relu(first layer) image [2]
-  float* op = (float*)(imo + 2 * WR_FRAG);         // [2][L][64] first-layer partials
-  float* zs = op + 2 * L * 64;                     // [L][256] logit sums over the heads
-  float* zk = zs + L * 256;                        // [L][256] logits of the last draws
-  float* hcs = zk + L * 256;                       // [L][448] coarse half of h (= y_c)
+  unsigned char* imf = imc + KT * WR_FRAGP;        // y_f operand image [KT]
+  unsigned char* imo = imf + KT * WR_FRAGP;        // relu(first layer) image [2]
+  float* op = (float*)(imo + 2 * WR_FRAGP);        // [2][L][64] first-layer partials
+  float* zk = op + 2 * L * 64;                     // [L][256] logits of the last draws
+  float* bias = zk + L * 256;                      // [2][256] class biases
+  float* hcs = bias + 512;                         // [L][448] coarse half of h (= y_c)
   float* hfs = hcs + L * 448;                      // [L][448] fine half of h (= y_f)
-  float* gv = hfs + L * 448;                       // [4L][448] staged pre-activations and e-gate bias of the gate threads
-  int64_t* cbo = (int64_t*)(gv + 4 * L * 448);    // [L] bias + conditioning row offsets of this step
+  int64_t* cbo = (int64_t*)(hfs + L * 448);        // [L] bias + conditioning row offsets of this step
   int* misc = (int*)(cbo + L);                     // [0] abort, [8+b] c_t, [16+b] c_prev, [24+b] f_prev,
                                                    // [48+b] step - position of vector b
   float* fmisc = (float*)(misc + 32);              // [b] lse_c, [8+b] z_c[c] of vector b
   float2* uni = (float2*)(misc + 64);              // [2][L][64] (u_c, u_f) of a batch of 64 steps
   int* tgt = (int*)(uni + 2 * L * 64);             // [2][L][64] teacher-forcing targets
-  float* gvf = (float*)(tgt + 2 * L * 64);         // ALL: [4L][448] the fine half's words (as gv), read with the coarse
 
   const int v0 = g * L;                            // first vector of this group
-  for (int i = tid; i < (2 * KT + 2) * WR_FRAG / 16; i += WR_THREADS) ((uint4*)lds)[i] = uint4{0, 0, 0, 0};
+  for (int i = tid; i < (2 * KT + 2) * WR_FRAGP / 16; i += WR_THREADS) ((uint4*)lds)[i] = uint4{0, 0, 0, 0};
   bf16x8 W1[KH], W3[KH], W2[4], W4[4];
   {
     const uint4* src = a.hw + ((size_t)(j * 8 + wave) * P.hw_frags) * 64 + lane;
@@ -241,9 +239,10 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
   // relu thread: vector rb, row rr of this head's 64 first-layer rows
   const int rb = tid >> 6, rr = tid & 63;
   const float b1r = a.b1[j * 64 + rr], b3r = a.b3[j * 64 + rr];
-  // draw wave w draws vector w: class biases of its 4 classes per lane
-  const float4 b2l = *(const float4*)(a.b2 + 4 * lane);
-  const float4 b4l = *(const float4*)(a.b4 + 4 * lane);
+  if (tid < WR_CLASSES) {                          // class biases
+    bias[tid] = a.b2[tid];
+    bias[WR_CLASSES + tid] = a.b4[tid];
+  }
   if (tid < L) {
     const int vb = min(v0 + tid, a.S - 1);
     cbo[tid] = cb_offset<LAG>(a, vb, 0);
@@ -268,8 +267,8 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
       f32x4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
 #pragma unroll
       for (int i = 0; i < KH; i += 2) {
-        acc0 = mfma(afrag(img, kc * KH + i), W[i], acc0);
-        if (i + 1 < KH) acc1 = mfma(afrag(img, kc * KH + i + 1), W[i + 1], acc1);
+        acc0 = mfma(afrag_p(img, kc * KH + i), W[i], acc0);
+        if (i + 1 < KH) acc1 = mfma(afrag_p(img, kc * KH + i + 1), W[i + 1], acc1);
       }
       const int r = 16 * rt + (lane & 15);
       if (bl0 < L) {                                // lanes of vectors past L hold rows of zero inputs
@@ -279,7 +278,7 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
     }
     __syncthreads();
     if (!FL && rb < L)
-      aput(imo + (rr >> 5) * WR_FRAG, rr & 31, wr_relu((op[rb * 64 + rr] + op[(L + rb) * 64 + rr]) + bias), rb);
+      aput_p(imo, rr, wr_relu((op[rb * 64 + rr] + op[(L + rb) * 64 + rr]) + bias), rb);
     __syncthreads();
   };
   // class tiles 2*wave, 2*wave+1 over this head's 64 columns, for all vectors
@@ -287,7 +286,7 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
   auto second_layer = [&](const bf16x8* W, xw* dst, uint32_t tag) {
     f32x4 A = {0, 0, 0, 0}, B = {0, 0, 0, 0};
     if (!FL) {
-      const bf16x8 x0 = afrag(imo, 0), x1 = afrag(imo, 1);
+      const bf16x8 x0 = afrag_p(imo, 0), x1 = afrag_p(imo, 1);
       A = mfma(x0, W[0], A);
       B = mfma(x0, W[2], B);
       A = mfma(x1, W[1], A);
@@ -301,152 +300,209 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
       xpub_l(dst + (bl0 + 1) * 256 + c0 + 16, tag, mfma_row_hi(B), lx);
     }
   };
-  // Vector ownership.  With 8 vectors per group head j draws the vectors j,
-  // j + NH, ... (slot q: vector j + NH q) and every other head learns their
-  // classes from one word each: only the owner sums a vector's partial
-  // logits, so a head reads 1/NH of the partials.  With up to 4 vectors
-  // (ALL) every head sums and draws every vector (slot q: vector q): the
-  // partials of all of them are no more words per thread than an owner's
-  // share of 8, and no class words have to travel.
-  constexpr bool ALL = L <= 4;
-  constexpr int OV = ALL ? L : (L + NH - 1) / NH;   // most vectors a head draws
-  constexpr int SP = (OV + 1) / 2;                  // drawn slots per gathering thread
-  const int nown = ALL ? L : (L - j + NH - 1) / NH; // vectors this head draws
-  auto vec = [&](int q) { return ALL ? q : j + NH * q; };   // vector of slot q
-  // Sums over the heads, in head order, of the owned vectors' partials:
-  // thread (class v, parity s) reads slots s, s + 2, ... of every head (all
-  // words in flight at once, the first probe after WR_POLL_DELAY), re-reading
-  // only words without the step's tag.
-  auto gather_own = [&](const xw* src, uint32_t tag) {
-    __builtin_amdgcn_s_sleep(WR_OWN_DELAY);
-    const int v = tid & 255, sp = tid >> 8;
-    // word k (< SP NH): head k % NH, slot sp + 2 (k / NH); staged in gv (free here)
-    float* stage = gv + tid;                        // [SP NH][512]
-    uint32_t need = 0;
+  // Wave w < L gathers the partial logits of vector w from every head alone
+  // (lane l: classes 4 l .. 4 l + 3, one 16-byte load a head), sums them in
+  // head order and draws, in registers: no barrier between gather and draw,
+  // and with every head drawing every vector no class has to travel.
+  const bool draws = wave < L;
+  auto gather_wave = [&](const xw* src, uint32_t tag, float4* z) -> bool {
+    __builtin_amdgcn_s_sleep(WR_POLL_DELAY);
+    const uint32_t lo = (uint32_t)(wave * 256 + 4 * lane) * 4u, ps = (uint32_t)(L * 256) * 4u;
+    xw4 w[NH];
+    uint32_t pending = 0;
+    {
+      const __amdgpu_buffer_rsrc_t r = xrsrc(xopaque(src), NH * ps);
 #pragma unroll
-    for (int k = 0; k < SP * NH; ++k)
-      if (sp + 2 * (k / NH) < nown) need |= 1u << k;
-    if (!poll_put<SP * NH>(src + v,
-                           [&](int k) { return (size_t)((k % NH) * L + vec(sp + 2 * (k / NH))) * 256; },
-                           [&](int k, float x) { stage[k * WR_THREADS] = x; }, tag, a, need)) {
-      misc[0] = 1;
-      return;
+      for (int k = 0; k < NH; ++k) w[k] = xpeek4(r, k * ps + lo);
     }
 #pragma unroll
-    for (int m = 0; m < SP; ++m) {
-      if (sp + 2 * m >= nown) break;
-      float s = 0.0f;
-#pragma unroll
-      for (int jj = 0; jj < NH; ++jj) s += stage[(m * NH + jj) * WR_THREADS];
-      zs[(sp + 2 * m) * 256 + v] = s;
-    }
-  };
-  // The 3L pre-activation words of gate thread u of each half and the L
-  // additive terms of each half's e gate (bias + conditioning, and with
-  // subscale the context term, which stays outside the reset product), staged
-  // in LDS: coarse word k at gv[k * 448 + u] and the term of vector b at
-  // gv[(3L + b) * 448 + u], fine ones likewise in gvf.  The units publish
-  // both halves at once, so all 4L word pairs are polled together at the
-  // start of the step: the fine gates wait for nothing but c_t.
-  const bool trg = g == 0 && j == 0 && tid == 0;            // a gate thread (tracing)
-  auto read_gates = [&](uint32_t tag, int64_t t) {
-#pragma unroll
-    for (int b = 0; b < L; ++b) {
-      gv[(3 * L + b) * 448 + u] = a.cb[cbo[b] + 2 * H + u];
-      gvf[(3 * L + b) * 448 + u] = a.cb[cbo[b] + 2 * H + Hh + u];
-    }
-    if (trg) trace_at(a, t, 13);
-    // pair k: half k / HP; in a half, the context pairs (vectors 2r, 2r + 1) and
-    // then the gate pairs (gate q, vectors b, b + 1) of unit u
-    constexpr int XP = CTX ? L / 2 : 0, HP = XP + 3 * L / 2;
-    if (!poll_put2<2 * HP>((const xw*)X,
-                           [&](int k) -> size_t {
-                             const int h = k / HP, r = k % HP;
-                             if (r < XP) return (size_t)(h ? P.x_xf : P.x_xc) + (size_t)u * L + 2 * r;
-                             const int q = (r - XP) / (L / 2), b = 2 * ((r - XP) % (L / 2));
-                             return (size_t)(h ? P.x_gf : P.x_ga) + (size_t)q * Hh * L + (size_t)u * L + b;
-                           },
-                           [&](int k, float x0, float x1) {
-                             const int h = k / HP, r = k % HP;
-                             float* gw = h ? gvf : gv;
-                             if (r < XP) {
-                               gw[(3 * L + 2 * r) * 448 + u] += x0;
-                               gw[(3 * L + 2 * r + 1) * 448 + u] += x1;
-                             } else {
-                               const int q = (r - XP) / (L / 2), b = 2 * ((r - XP) % (L / 2));
-                               gw[(3 * b + q) * 448 + u] = x0;
-                               gw[(3 * b + 3 + q) * 448 + u] = x1;
-                             }
-                           },
-                           tag, a))
-      misc[0] = 1;
-  };
-  xw* CC = X + P.x_cc;                              // drawn coarse classes [L]
-  xw* CF = X + P.x_cf;                              // drawn fine classes [L]
-  // SLICE: one (unit, vector) pair per thread.  Its three pre-activation
-  // words, the e gate's context term (subscale) and, for the coarse half,
-  // the first word unit k = tid publishes: a unit publishes its words of
-  // step t + 1 only after reading all of h of step t, so once every unit's
-  // word has arrived this head may replace its slice of y of step t.  Then
-  // the gates, this head's slice of y, and the other slices from their heads.
-  // The classes of the thread's vector travel with the same poll: c_{t-1} and
-  // f_{t-1} with the coarse words (from step 1 on), c_t with the fine words.
-  int cprev = 0, fprev = 0, ccur = 0;               // SLICE: classes of vector sb
-  size_t uflag = 0;
-  if (SLICE && tid < P.NU) {
-    const int tile = tid * WR_BUCT, gt = tile / (HH / 16);
-    uflag = P.x_ga + (size_t)(gt * HH + 16 * (tile % (HH / 16))) * L;
-  }
-  auto slice_gates = [&](bool fine, uint32_t tag, int64_t t, uint32_t actm) {
-    const float cb = a.cb[cbo[sb] + 2 * H + (fine ? HH : 0) + su];
-    const size_t go = (fine ? P.x_gf : P.x_ga) + (size_t)su * L + sb;
-    const size_t xo = (fine ? P.x_xf : P.x_xc) + (size_t)su * L + sb;
-    // words 0-2 gates, 3 context term, 4 unit flag, 5 c (fine: c_t; coarse: c_{t-1}), 6 f_{t-1}
-    uint32_t pending = 7u | (CTX ? 8u : 0u) | (!fine && tid < P.NU ? 16u : 0u) | (fine ? 32u : t > 0 ? 96u : 0u);
-    float gw[7] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    const size_t co = P.x_cc + sb, fo = P.x_cf + sb;
-    WaitBudget wb{wr_clock(), 0};
-    for (;;) {
-      const xw* xb = opaque((const xw*)X);
-      xw w[7];
-#pragma unroll
-      for (int k = 0; k < 7; ++k)
-        w[k] = (pending >> k & 1u) ? xpeek(xb + (k < 3 ? go + (size_t)k * HH * L : k == 3 ? xo : k == 4 ? uflag : k == 5 ? co : fo)) : 0;
-#pragma unroll
-      for (int k = 0; k < 7; ++k)
-        if ((pending >> k & 1u) && xok(w[k], k >= 5 && !fine ? tag - 1u : tag)) {
-          gw[k] = xval(w[k]);
-          pending &= ~(1u << k);
+    for (int k = 0; k < NH; ++k)
+      if (!xok4(w[k], tag)) pending |= 1u << k;
+    if (pending) {
+      WaitBudget wb{wr_clock(), 0};
+      while (pending) {
+        if (!wait_ok(wb, a.err, a.limit, a.err)) {
+          *z = float4{0.0f, 0.0f, 0.0f, 0.0f};     // a valid draw follows; the step is abandoned after it
+          return false;
         }
+        const __amdgpu_buffer_rsrc_t r = xrsrc(xopaque(src), NH * ps);
+#pragma unroll
+        for (int k = 0; k < NH; ++k)
+          if (pending >> k & 1u) w[k] = xpeek4(r, k * ps + lo);
+#pragma unroll
+        for (int k = 0; k < NH; ++k)
+          if ((pending >> k & 1u) && xok4(w[k], tag)) pending &= ~(1u << k);
+      }
+    }
+    float4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < NH; ++k) {
+      s.x += xval(w[k].x);
+      s.y += xval(w[k].y);
+      s.z += xval(w[k].z);
+      s.w += xval(w[k].w);
+    }
+    *z = s;
+    return true;
+  };
+  // ALL: the 3L pre-activation words of gate thread u of each half and the
+  // e gates' context terms (subscale; outside the reset product), as pairs of
+  // vectors.  The units publish both halves at once, so one poll at the start
+  // of the step reads all of them and the fine gates wait only for c_t.  Words
+  // that do not wait for the step's drawn samples are there before the step
+  // starts: their first probe goes out before the fine draw (`probe`).  Those
+  // that do (window context) come late: one pair is polled until it is there,
+  // then the rest is read, so failed probes stay small.
+  // Pair k: half k / HP; in a half, the context pairs (vectors 2r, 2r + 1) and
+  // then the gate pairs (gate q, vectors b, b + 1) of unit u.
+  const bool trg = g == 0 && j == 0 && tid == 0;            // a gate thread (tracing)
+  constexpr bool ALL = !SLICE;
+  constexpr int XP = CTX && ALL ? L / 2 : 0, HP = ALL ? XP + 3 * L / 2 : 1, AL = ALL ? L : 1;
+  constexpr bool late = CTX;
+  uint64_t gp[2 * HP] = {};
+  float cbe_c[AL] = {}, cbe_f[AL] = {};            // e gates' bias + conditioning of this step
+  auto all_load = [&](uint32_t pending) {
+    const xw* xb = opaque((const xw*)X);
+#pragma unroll
+    for (int k = 0; k < 2 * HP; ++k)
+      if (pending >> k & 1u) {
+        const int h = k / HP, r = k % HP, q = (r - XP) / (AL / 2 ? AL / 2 : 1), b = 2 * ((r - XP) % (AL / 2 ? AL / 2 : 1));
+        gp[k] = xpeek2(xb + (r < XP ? (h ? P.x_xf : P.x_xc) + 2 * r : (h ? P.x_gf : P.x_ga) + q * Hh * L + b) + u * L);
+      }
+  };
+  auto all_probe = [&]() {
+#pragma unroll
+    for (int b = 0; b < AL; ++b) {
+      cbe_c[b] = a.cb[cbo[b] + 2 * H + u];
+      cbe_f[b] = a.cb[cbo[b] + 2 * H + Hh + u];
+    }
+    if (!late) all_load(~0u);
+  };
+  auto all_words = [&](uint32_t tag) {
+    uint32_t pending = 2 * HP >= 32 ? ~0u : (1u << 2 * HP) - 1u;
+    WaitBudget wb{wr_clock(), 0};
+    if (late) {
+      do {
+        all_load(1u);
+        if (xok2(gp[0], tag)) break;
+      } while (wait_ok(wb, a.err, a.limit, a.err));
+      all_load(pending & ~1u);
+    }
+    for (;;) {
+#pragma unroll
+      for (int k = 0; k < 2 * HP; ++k)
+        if (xok2(gp[k], tag)) pending &= ~(1u << k);
       if (!pending) break;
       if (!wait_ok(wb, a.err, a.limit, a.err)) {
         misc[0] = 1;
         return;
       }
+      all_load(pending);
     }
-    if (trg) trace_at(a, t, fine ? 12 : 11);
-    if (FL) {                                       // the exchange alone: own slice out, the others in
-      xpub((fine ? YF : YC) + sb * HH + su, tag, 0.0f);
-      uint32_t own = 0;
+  };
+  // the gates of unit u of one half, every vector
+  auto all_gates = [&](auto fine_, uint32_t tag, uint32_t actm) {
+    constexpr bool fine = decltype(fine_)::value;
+    xw* Y = fine ? YF : YC;
 #pragma unroll
-      for (int m = 0; m < KH; ++m)
-        if ((tid + WR_THREADS * m) % HH / 64 == j) own |= 1u << m;
-      __builtin_amdgcn_s_sleep(WR_POLL_DELAY);
-      if (!poll_put<KH>(fine ? YF : YC, [&](int m) { return (size_t)(tid + WR_THREADS * m); },
-                        [&](int, float) {}, tag, a, ~own))
+    for (int b = 0; b < AL; ++b) {
+      if (FL) {
+        if (mine) xpub_l(Y + b * Hh + u, tag, 0.0f, lx);
+        continue;
+      }
+      auto word = [&](int r) {                     // pair r of this half, vector b of it
+        const uint64_t w = gp[(fine ? HP : 0) + r];
+        return xval((xw)(b & 1 ? w >> 32 : w));
+      };
+      constexpr int LP = AL / 2 ? AL / 2 : 1;
+      const float wu = word(XP + b / 2), wr = word(XP + LP + b / 2), we = word(XP + 2 * LP + b / 2);
+      const float cbe = CTX ? (fine ? cbe_f : cbe_c)[b] + word(b / 2) : (fine ? cbe_f : cbe_c)[b];
+      const float x0 = fscale(misc[16 + b]), x1 = fscale(misc[24 + b]);
+      float pu, pr, pe;
+      if (fine) {
+        const float x2 = fscale(misc[8 + b]);
+        pu = __builtin_fmaf(ifn[0][2], x2, __builtin_fmaf(ifn[0][1], x1, ifn[0][0] * x0));
+        pr = __builtin_fmaf(ifn[1][2], x2, __builtin_fmaf(ifn[1][1], x1, ifn[1][0] * x0));
+        pe = __builtin_fmaf(ifn[2][2], x2, __builtin_fmaf(ifn[2][1], x1, ifn[2][0] * x0));
+      } else {
+        pu = __builtin_fmaf(ic[0][1], x1, ic[0][0] * x0);
+        pr = __builtin_fmaf(ic[1][1], x1, ic[1][0] * x0);
+        pe = __builtin_fmaf(ic[2][1], x1, ic[2][0] * x0);
+      }
+      const float uu = fsig(wu + pu);
+      const float rg = fsig(wr + pr);
+      const float e = ftanh(__builtin_fmaf(rg, we, pe + cbe));
+      float* hs = (fine ? hfs : hcs) + b * 448 + u;
+      const float hn = actm >> b & 1u ? __builtin_fmaf(uu, *hs, (1.0f - uu) * e) : *hs;   // idle: state kept
+      *hs = hn;
+      aput_p(fine ? imf : imc, u, hn, b);
+      if (mine) xpub_l(Y + b * Hh + u, tag, hn, lx);   // this head's slice, for the units
+    }
+  };
+  // SLICE: one (unit, vector) pair per thread.  Its three pre-activation
+  // words of each half (the units publish both halves at once), the e gates'
+  // context terms (subscale), and the first word unit k = tid publishes: a
+  // unit publishes its words of step t + 1 only after reading all of h of
+  // step t, so once every unit's word has arrived this head may replace its
+  // slices of y of step t.  One poll at the start of a step, its first probe
+  // issued before the fine draw (`pw`): the fine gates then wait only for c_t.
+  // Words 0-2 coarse gates, 3-5 fine gates, 6 and 7 context terms, 8 unit flag.
+  constexpr int NW = 9;
+  const uint32_t wneed = 63u | (CTX ? 192u : 0u) | (SLICE && tid < P.NU ? 256u : 0u);
+  const uint32_t so = (uint32_t)(su * L + sb);
+  uint32_t uflag = 0;
+  if (SLICE && tid < P.NU) {
+    const int tile = tid * WR_BUCT, gt = tile / (HH / 16);
+    uflag = (uint32_t)(P.x_ga + (gt * HH + 16 * (tile % (HH / 16))) * L);
+  }
+  xw pw[NW] = {};
+  float cbc = 0.0f, cbf = 0.0f;                    // e gates' bias + conditioning of this step
+  auto slice_load = [&](uint32_t pending) {
+    const xw* xb = opaque((const xw*)X);
+#pragma unroll
+    for (int k = 0; k < NW; ++k)
+      if (pending >> k & 1u)
+        pw[k] = xpeek(xb + (k == 8 ? uflag
+                                   : (uint32_t)(k < 3 ? P.x_ga + k * HH * L
+                                                      : k < 6 ? P.x_gf + (k - 3) * HH * L : k == 6 ? P.x_xc : P.x_xf) + so));
+  };
+  auto slice_probe = [&]() {                       // words of the coming step and its conditioning
+    const float* cbr = a.cb + cbo[sb] + 2 * H + su;
+    cbc = cbr[0];
+    cbf = cbr[HH];
+    slice_load(wneed);
+  };
+  auto slice_words = [&](uint32_t tag) {
+    uint32_t pending = wneed;
+    WaitBudget wb{wr_clock(), 0};
+    for (;;) {
+#pragma unroll
+      for (int k = 0; k < NW; ++k)
+        if (xok(pw[k], tag)) pending &= ~(1u << k);
+      if (!pending) break;
+      if (!wait_ok(wb, a.err, a.limit, a.err)) {
         misc[0] = 1;
+        return;
+      }
+      slice_load(pending);
+    }
+  };
+  auto slice_gates = [&](bool fine, uint32_t tag, int64_t t, uint32_t actm) {
+    float* hs = (fine ? hfs : hcs) + sb * 448 + su;
+    unsigned char* img = fine ? imf : imc;
+    xw* Y = fine ? YF : YC;
+    if (FL) {                                       // the exchange alone: own slice out, the others in
+      xpub_l(Y + sb * HH + su, tag, 0.0f, lx);
+      __builtin_amdgcn_s_sleep(WR_POLL_DELAY);
+      if (!gather_y<L, HH, false>(Y, tag, img, 64 * j, a)) misc[0] = 1;
       return;
     }
-    if (fine) ccur = (int)gw[5];
-    else if (t > 0) {
-      cprev = (int)gw[5];
-      fprev = (int)gw[6];
-    }
-    const float cbe = cb + gw[3];
-    const float x0 = fscale(cprev), x1 = fscale(fprev);
+    const float cbe = (fine ? cbf : cbc) + (CTX ? xval(pw[fine ? 7 : 6]) : 0.0f);
+    const float x0 = fscale(misc[16 + sb]), x1 = fscale(misc[24 + sb]);
+    const int g0 = fine ? 3 : 0;
     float pu, pr, pe;
     if (fine) {
-      const float x2 = fscale(ccur);
+      const float x2 = fscale(misc[8 + sb]);
       pu = __builtin_fmaf(ifn[0][2], x2, __builtin_fmaf(ifn[0][1], x1, ifn[0][0] * x0));
       pr = __builtin_fmaf(ifn[1][2], x2, __builtin_fmaf(ifn[1][1], x1, ifn[1][0] * x0));
       pe = __builtin_fmaf(ifn[2][2], x2, __builtin_fmaf(ifn[2][1], x1, ifn[2][0] * x0));
@@ -455,31 +511,35 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
       pr = __builtin_fmaf(ic[1][1], x1, ic[1][0] * x0);
       pe = __builtin_fmaf(ic[2][1], x1, ic[2][0] * x0);
     }
-    const float uu = fsig(gw[0] + pu);
-    const float rg = fsig(gw[1] + pr);
-    const float e = ftanh(__builtin_fmaf(rg, gw[2], pe + cbe));
-    float* hs = (fine ? hfs : hcs) + sb * 448 + su;
+    const float uu = fsig(xval(pw[g0]) + pu);
+    const float rg = fsig(xval(pw[g0 + 1]) + pr);
+    const float e = ftanh(__builtin_fmaf(rg, xval(pw[g0 + 2]), pe + cbe));
     const float hn = actm >> sb & 1u ? __builtin_fmaf(uu, *hs, (1.0f - uu) * e) : *hs;   // idle: state kept
+    xpub_l(Y + sb * HH + su, tag, hn, lx);
     *hs = hn;
-    unsigned char* img = fine ? imf : imc;
-    aput(img + (su >> 5) * WR_FRAG, su & 31, xround(hn), sb);
-    xw* Y = fine ? YF : YC;
-    xpub(Y + sb * HH + su, tag, hn);
-    // the other heads' slices: word w = tid + 512 m of y [8][Hh] (Hh / 64 per thread)
-    uint32_t own = 0;
-#pragma unroll
-    for (int m = 0; m < KH; ++m)
-      if ((tid + WR_THREADS * m) % HH / 64 == j) own |= 1u << m;
+    aput_p(img, su, xround(hn), sb);
     __builtin_amdgcn_s_sleep(WR_POLL_DELAY);
-    if (!poll_put<KH>(Y, [&](int m) { return (size_t)(tid + WR_THREADS * m); },
-                      [&](int m, float y) {
-                        const int w = tid + WR_THREADS * m, b = w / HH, c = w % HH;
-                        aput(img + (c >> 5) * WR_FRAG, c & 31, y, b);
-                      },
-                      tag, a, ~own))
-      misc[0] = 1;
+    if (!gather_y<L, HH, true>(Y, tag, img, 64 * j, a)) misc[0] = 1;   // the other heads' slices
   };
-  const int bw = vec(wave);                         // vector (in the group) drawn by this wave, if wave < nown
+  // the table row of vector tid's next position: frame and sample within it,
+  // stepped without a division (the steps' tail is on the chain)
+  const int cstep = a.B / a.frame_len, crem = a.B % a.frame_len;
+  int64_t cfr = 0;                                 // frame of the position
+  int cin = 0;                                     // sample within the frame
+  auto cb_next = [&](int64_t t) {                  // thread b < L: offset of its vector at step t + 1
+    if (LAG) {
+      const int64_t p = t + 1 - misc[48 + tid];
+      if (p <= 0 || p >= a.rows) return;           // clamped to the first or last position
+    }
+    cfr += cstep;
+    cin += crem;
+    if (cin >= a.frame_len) {
+      cin -= a.frame_len;
+      ++cfr;
+    }
+    cbo[tid] = ((int64_t)(min(v0 + tid, a.S - 1) / a.B) * a.n_cb + (cfr < a.n_cb ? cfr : a.n_cb - 1)) * 3 * H;
+  };
+  const int bw = wave;                              // vector (in the group) drawn by this wave, if below L
   const int vw = min(v0 + bw, a.S - 1);
   const size_t ob = obase(a, vw);
   auto fill_batch = [&](int64_t t, int buf) {       // wave w: uniforms / targets of its owned vector
@@ -491,18 +551,23 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
       tgt[(buf * L + wave) * 64 + lane] = a.target ? a.target[ob + (size_t)a.B * p] : 0;
     }
   };
-  if (wave < nown) fill_batch(0, 0);
+  if (draws) fill_batch(0, 0);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (SLICE) {
-    cprev = misc[16 + sb];
-    fprev = misc[24 + sb];
-  }
   const bool trw = g == 0 && j == 0 && tid == WR_THREADS - 64;
-  const bool own = wave < nown;                     // this wave draws an owned vector
-  const bool writer = own && (!ALL || bw % NH == j); // ... and writes its outputs (one head per vector)
+  const bool writer = draws && bw % NH == j;        // this head writes the vector's outputs
   const bool live = writer && v0 + bw < a.S;       // ... of a vector in use
-  if (WR_LOCAL_XCHG) lx = leads_share_xcd(X + P.x_xcc, P.NH, j, misc + 1, a);
+  if (tid < L) {
+    const int vb = min(v0 + tid, a.S - 1);
+    int64_t p = vpos<LAG>(a, vb, 0);
+    if (LAG) p = p < 0 ? 0 : p >= a.rows ? a.rows - 1 : p;
+    const int64_t n = (int64_t)a.B * ((LAG ? 0 : a.t0) + p) + vb % a.B;
+    cfr = n / a.frame_len;
+    cin = (int)(n - cfr * a.frame_len);
+  }
+  if (WR_LOCAL_XCHG) lx = leads_share_xcd(X + P.x_xcc, P.NH + P.NU, j, misc + 1, a);
+  if (SLICE) slice_probe();
+  else if (gate) all_probe();
 
   for (int64_t t = 0; t < a.T; ++t) {
     const uint32_t tag = (uint32_t)(t + 1);
@@ -518,33 +583,16 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
       }
     }
     const int bs = (int)((t >> 6) & 1) * L * 64 + wave * 64 + (int)(t & 63);   // draw wave's batch slot
-    if (own && (t & 63) == 0) fill_batch(t + 64, (int)(((t >> 6) + 1) & 1));
-    // (1) coarse gates of every unit and vector: the pre-activation words of
-    // thread u (both halves with up to 4 vectors) are polled together and
-    // staged in LDS, then one vector at a time
+    if (draws && (t & 63) == 0) fill_batch(t + 64, (int)(((t >> 6) + 1) & 1));
+    // (1) coarse gates of every unit and vector
     if (SLICE) {
+      slice_words(tag);
+      if (trg) trace_at(a, t, 11);
       slice_gates(false, tag, t, actm);
     } else if (gate) {
-      read_gates(tag, t);
+      all_words(tag);
       if (trg) trace_at(a, t, 11);
-#pragma unroll 2
-      for (int b = 0; b < L; ++b) {
-        if (FL) {
-          if (mine) xpub(YC + b * Hh + u, tag, 0.0f);
-          continue;
-        }
-        const float cbe = gv[(3 * L + b) * 448 + u];
-        const float x0 = fscale(misc[16 + b]), x1 = fscale(misc[24 + b]);
-        const float uu = fsig(gv[(3 * b) * 448 + u] + __builtin_fmaf(ic[0][1], x1, ic[0][0] * x0));
-        const float rg = fsig(gv[(3 * b + 1) * 448 + u] + __builtin_fmaf(ic[1][1], x1, ic[1][0] * x0));
-        const float e = ftanh(
-            __builtin_fmaf(rg, gv[(3 * b + 2) * 448 + u], __builtin_fmaf(ic[2][1], x1, ic[2][0] * x0) + cbe));
-        const float hn = actm >> b & 1u ? __builtin_fmaf(uu, hcs[b * 448 + u], (1.0f - uu) * e)
-                                        : hcs[b * 448 + u];   // an idle lane keeps its state
-        hcs[b * 448 + u] = hn;
-        aput(imc + (u >> 5) * WR_FRAG, u & 31, hn, b);
-        if (mine) xpub(YC + b * Hh + u, tag, hn);   // this head's slice, for the units
-      }
+      all_gates(std::false_type{}, tag, actm);
     }
     __syncthreads();
     if (misc[0]) return;
@@ -553,27 +601,22 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
     first_layer(W1, imc, b1r);
     second_layer(W2, PCo, tag);
     if (trw) trace_at(a, t, 3);
-    // (3) the owned vectors' sums over the heads, their coarse draws (wave w:
-    // slot w), then every vector's class from its owner
-    gather_own(PC, tag);
-    __syncthreads();
-    if (misc[0]) return;
-    if (trw) trace_at(a, t, 4);
-    if (own) {
+    if (tid < L && t + 1 < a.T) cb_next(t);           // (this step's offsets have been used)
+    // (3) every vector's sums over the heads and coarse draw (wave w: vector w)
+    if (draws) {
+      float4 z;
+      if (!gather_wave(PC, tag, &z)) misc[0] = 1;
+      if (trw) trace_at(a, t, 4);
       float lse;
       const int forced = a.target ? (tgt[bs] >> 8) : -1;
-      const int c = FL ? 0 : draw_wave<false>(zs + wave * 256, nullptr, b2l, uni[bs].x, forced, zk + wave * 256,
-                                              a.nll_out ? &lse : nullptr);
+      const int c = FL ? 0 : draw_z(z, *(const float4*)(bias + 4 * lane), uni[bs].x, forced, zk + wave * 256, a.nll_out ? &lse : nullptr);
       const int64_t pw = LAG ? t - misc[48 + bw] : t;   // this vector's position; an idle lane keeps its classes
       const bool act = actm >> bw & 1u;
       if (live && act && a.zc_out)
         *(float4*)(a.zc_out + (ob + (size_t)a.B * pw) * WR_CLASSES + 4 * lane) =
             *(const float4*)(zk + wave * 256 + 4 * lane);
       if (lane == 0) {
-        int cw = c;                                 // the class word: an idle lane's last class
-        if (act) misc[8 + bw] = c;
-        else cw = misc[8 + bw];
-        if (!ALL) xpub_l(CC + bw, tag, (float)cw, lx);
+        if (act) misc[8 + bw] = c;                  // (an idle lane keeps its last class)
         if (a.nll_out) {
           fmisc[wave] = lse;
           fmisc[8 + wave] = zk[wave * 256 + c];
@@ -581,33 +624,13 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
       }
     }
     __syncthreads();
+    if (misc[0]) return;
     if (trw) trace_at(a, t, 5);
     // (4) fine gates with c_t
     if (SLICE) {
       slice_gates(true, tag, t, actm);
     } else if (gate) {
-      if (trg) trace_at(a, t, 12);                 // (the fine words came with the coarse ones)
-#pragma unroll 2
-      for (int b = 0; b < L; ++b) {
-        if (FL) {
-          if (mine) xpub(YF + b * Hh + u, tag, 0.0f);
-          continue;
-        }
-        const float cbe = gvf[(3 * L + b) * 448 + u];
-        const float x0 = fscale(misc[16 + b]), x1 = fscale(misc[24 + b]), x2 = fscale(misc[8 + b]);
-        const float uu = fsig(gvf[(3 * b) * 448 + u] +
-                              __builtin_fmaf(ifn[0][2], x2, __builtin_fmaf(ifn[0][1], x1, ifn[0][0] * x0)));
-        const float rg = fsig(gvf[(3 * b + 1) * 448 + u] +
-                              __builtin_fmaf(ifn[1][2], x2, __builtin_fmaf(ifn[1][1], x1, ifn[1][0] * x0)));
-        const float e = ftanh(__builtin_fmaf(
-            rg, gvf[(3 * b + 2) * 448 + u],
-            __builtin_fmaf(ifn[2][2], x2, __builtin_fmaf(ifn[2][1], x1, ifn[2][0] * x0)) + cbe));
-        const float hn = actm >> b & 1u ? __builtin_fmaf(uu, hfs[b * 448 + u], (1.0f - uu) * e)
-                                        : hfs[b * 448 + u];
-        hfs[b * 448 + u] = hn;
-        aput(imf + (u >> 5) * WR_FRAG, u & 31, hn, b);
-        if (mine) xpub(YF + b * Hh + u, tag, hn);
-      }
+      all_gates(std::true_type{}, tag, actm);
     }
     __syncthreads();
     if (misc[0]) return;
@@ -616,16 +639,20 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
     first_layer(W3, imf, b3r);
     second_layer(W4, PFo, tag);
     if (trw) trace_at(a, t, 8);
-    // (6) the owned vectors' fine sums and draws, then every vector's class
-    gather_own(PF, tag);
-    __syncthreads();
-    if (misc[0]) return;
-    if (trw) trace_at(a, t, 9);
-    if (own) {
+    // (6) every vector's fine sums and draw
+    auto probe = [&]() {                              // the next step's words, ahead of the gather's loads
+      if (t + 1 >= a.T) return;
+      if (SLICE) slice_probe();
+      else if (gate) all_probe();
+    };
+    probe();
+    if (draws) {
+      float4 z;
+      if (!gather_wave(PF, tag, &z)) misc[0] = 1;
+      if (trw) trace_at(a, t, 9);
       float lse;
       const int forced = a.target ? (tgt[bs] & 255) : -1;
-      const int f = FL ? 0 : draw_wave<false>(zs + wave * 256, nullptr, b4l, uni[bs].y, forced, zk + wave * 256,
-                                              a.nll_out ? &lse : nullptr);
+      const int f = FL ? 0 : draw_z(z, *(const float4*)(bias + WR_CLASSES + 4 * lane), uni[bs].y, forced, zk + wave * 256, a.nll_out ? &lse : nullptr);
       const int c = misc[8 + bw];
       const int64_t pw = LAG ? t - misc[48 + bw] : t;
       const bool act = actm >> bw & 1u;
@@ -633,12 +660,6 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
         *(float4*)(a.zf_out + (ob + (size_t)a.B * pw) * WR_CLASSES + 4 * lane) =
             *(const float4*)(zk + wave * 256 + 4 * lane);
       if (lane == 0) {
-        int fw = f;
-        if (SLICE) {                                // the owner's record (final state)
-          if (act) misc[24 + bw] = f;
-          else fw = misc[24 + bw];
-        }
-        if (!ALL) xpub_l(CF + bw, tag, (float)fw, lx);
         // for later contexts; an idle lane publishes a word too (value unused)
         if (a.ux && writer) spub(X + P.x_sp, L, P.SS, bw, tag, act ? 256 * c + f : 0);
         if (live && act) {
@@ -646,17 +667,14 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
           if (a.nll_out)
             a.nll_out[ob + (size_t)a.B * pw] = (fmisc[wave] - fmisc[8 + wave]) + (lse - zk[wave * 256 + f]);
         }
-        if (ALL) {                                  // this head's own record of the vector's classes
-          if (act) {
-            misc[16 + bw] = c;
-            misc[24 + bw] = f;
-          }
-          if (t + 1 < a.T) cbo[bw] = cb_offset<LAG>(a, min(v0 + bw, a.S - 1), t + 1);
+        if (act) {                                  // this head's own record of the vector's classes
+          misc[16 + bw] = c;
+          misc[24 + bw] = f;
         }
       }
     }
-    if (SLICE && tid < L && t + 1 < a.T) cbo[tid] = cb_offset<LAG>(a, min(v0 + tid, a.S - 1), t + 1);
     __syncthreads();
+    if (misc[0]) return;
     if (trw) trace_at(a, t, 10);
   }
   if (SLICE && a.h_out && v0 + sb < a.S) {          // each head its own slice
@@ -670,14 +688,10 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
           a.h_out[(size_t)(v0 + b) * H + u] = hcs[b * 448 + u];
           a.h_out[(size_t)(v0 + b) * H + Hh + u] = hfs[b * 448 + u];
         }
-    if (tid < L && v0 + tid < a.S && !SLICE) {
+    if (tid < L && v0 + tid < a.S) {
       if (a.c_out) a.c_out[v0 + tid] = (uint8_t)misc[16 + tid];
       if (a.f_out) a.f_out[v0 + tid] = (uint8_t)misc[24 + tid];
     }
-  }
-  if (SLICE && lane == 0 && live) {                 // the owner: last classes of its vectors
-    if (a.c_out) a.c_out[v0 + bw] = (uint8_t)misc[8 + bw];
-    if (a.f_out) a.f_out[v0 + bw] = (uint8_t)misc[24 + bw];
   }
 }
 
@@ -695,8 +709,8 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
   const int q = wave & 3;
   const unsigned char* WL = lds + (fw ? WR_BUCT * KT + q * KT : q * KT) * WR_FRAG;   // this wave's LDS half
   unsigned char* img = lds + P.u_lds_w;                                             // [2KT] operand image
-  unsigned char* cimg = img + 2 * KT * WR_FRAG;                                     // [KX] context image
-  int* hist = (int*)(cimg + P.KX * WR_FRAG);          // [utterance slot][HC]: sample q at q % HC
+  unsigned char* cimg = img + 2 * KT * WR_FRAGP;                                    // [KX] context image
+  int* hist = (int*)(cimg + P.KX * WR_FRAGP);         // [utterance slot][HC]: sample q at q % HC
   int* misc = hist + P.RING;
   const int HC = LAG ? P.HC : 256, HCm = HC - 1;   // (256 always holds a lockstep context)
   const int tile = k * WR_BUCT + q;
@@ -709,7 +723,7 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
   {
     const uint4* src = a.uw + (size_t)k * (P.u_lds_w / 16);
     for (int x = tid; x < P.u_lds_w / 16; x += WR_THREADS) ((uint4*)lds)[x] = src[x];
-    for (int x = tid; x < (2 * KT + P.KX) * WR_FRAG / 16; x += WR_THREADS) ((uint4*)img)[x] = uint4{0, 0, 0, 0};
+    for (int x = tid; x < (2 * KT + P.KX) * WR_FRAGP / 16; x += WR_THREADS) ((uint4*)img)[x] = uint4{0, 0, 0, 0};
     if (tid == 0) misc[0] = 0;
   }
   bf16x8 WX[CTX ? 8 : 1];                              // context-projection fragments of this wave's tile
@@ -729,7 +743,7 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
   for (int x = tid; x < L * H; x += WR_THREADS) {
     const int b = x / H, col = x % H;
     const float y = a.h_in ? xround(a.h_in[(size_t)min(v0 + b, a.S - 1) * H + col]) : 0.0f;
-    aput(img + (col >> 5) * WR_FRAG, col & 31, y, b);
+    aput_p(img, col, y, b);
   }
   // A launch that starts at step t0 > 0 of a call (the call resumed) starts
   // each ring slot with what a launch from step 0 would hold there now: slot
@@ -763,10 +777,10 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
 #pragma unroll
     for (int x = 0; x < KT; x += 2) {
       const bf16x8 w0 = fw ? WR[x] : *(const bf16x8*)(WL + x * WR_FRAG + lane * 16);
-      acc0 = mfma(afrag(img, x), w0, acc0);
+      acc0 = mfma(afrag_p(img, x), w0, acc0);
       if (x + 1 < KT) {
         const bf16x8 w1 = fw ? WR[x + 1] : *(const bf16x8*)(WL + (x + 1) * WR_FRAG + lane * 16);
-        acc1 = mfma(afrag(img, x + 1), w1, acc1);
+        acc1 = mfma(afrag_p(img, x + 1), w1, acc1);
       }
     }
   };
@@ -776,10 +790,10 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
 #pragma unroll
     for (int x = 0; x < KT; x += 2) {
       const bf16x8 w0 = fw ? *(const bf16x8*)(WL + x * WR_FRAG + lane * 16) : WR[x];
-      acc0 = mfma(afrag(img, KT + x), w0, acc0);
+      acc0 = mfma(afrag_p(img, KT + x), w0, acc0);
       if (x + 1 < KT) {
         const bf16x8 w1 = fw ? *(const bf16x8*)(WL + (x + 1) * WR_FRAG + lane * 16) : WR[x + 1];
-        acc1 = mfma(afrag(img, KT + x + 1), w1, acc1);
+        acc1 = mfma(afrag_p(img, KT + x + 1), w1, acc1);
       }
     }
   };
@@ -789,14 +803,15 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
   // at the start of a step, before h arrives, into its own sums for every row.
   const bool table = CTX && LAG && a.ctab;
   const bool ahead = CTX && LAG && (a.A > 0 || table);
+  bool lx = false;   // the whole group on one XCD: words into its L2
   auto publish = [&](uint32_t tag, float cb0, float cb1) {
     if (bl0 >= L) return;                               // rows of vectors past L: zero inputs, not published
     if (ahead && gt < 2) {
       cb0 += mfma_row(xa0) + mfma_row(xa1);
       cb1 += mfma_row_hi(xa0) + mfma_row_hi(xa1);
     }
-    xpub2(dst, tag, (mfma_row(acc0) + mfma_row(acc1)) + cb0, (mfma_row_hi(acc0) + mfma_row_hi(acc1)) + cb1);
-    if (CTX && gt == 2) xpub2(dstx, tag, mfma_row(xa0) + mfma_row(xa1), mfma_row_hi(xa0) + mfma_row_hi(xa1));
+    xpub2_l(dst, tag, (mfma_row(acc0) + mfma_row(acc1)) + cb0, (mfma_row_hi(acc0) + mfma_row_hi(acc1)) + cb1, lx);
+    if (CTX && gt == 2) xpub2_l(dstx, tag, mfma_row(xa0) + mfma_row(xa1), mfma_row_hi(xa0) + mfma_row_hi(xa1), lx);
   };
   // Subscale context (Sec. 4): the samples drawn at step t - A by the lanes
   // of every utterance of this group join the ring; vector b's context for
@@ -821,29 +836,24 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
       const int vb = min(v0 + b, a.S - 1);
       int64_t r = vpos<LAG>(a, vb, t + 1) - (a.ctab_row0 + (int64_t)(vb % a.B) * a.ctab_step);
       r = r < 0 ? 0 : r >= a.ctab_rows ? a.ctab_rows - 1 : r;
-      aput(cimg + (col >> 5) * WR_FRAG, col & 31, a.ctab[((size_t)vb * a.ctab_rows + r) * Dx + col], b);
+      aput_p(cimg, col, a.ctab[((size_t)vb * a.ctab_rows + r) * Dx + col], b);
     }
     __syncthreads();
   };
-  auto context = [&](int64_t t) {
-    if (table) {
-      table_image(t);
-    } else {
-    const int64_t td = t - (LAG ? a.A : 0);            // the step whose samples join the ring now
-    const uint32_t tag = (uint32_t)(td + 1);
-    if (tid < nut * a.B && td >= 0) {                  // one thread per (utterance, lane)
-      const int vv = ub0 * a.B + tid;                  // vector of that lane
-      int y = 0;
-      const int64_t p = vpos<LAG>(a, vv, td);          // lanes idle at step td drew nothing
-      if (vv < a.S) {                                  // (but their words are waited for too)
-        if (!wait_sample(a.xc + (size_t)(vv / L) * P.x_words + P.x_sp, L, P.SS, vv % L, tag, &y, a)) misc[0] = 1;
-        const int64_t qn = (int64_t)a.B * (p + (LAG ? 0 : a.t0)) + tid % a.B;   // the sample's index
-        if (p >= 0 && p < a.rows) hist[(tid / a.B) * HC + (int)(qn & HCm)] = y;
-      }
-    }
-    __syncthreads();
-    if (misc[0] || FL) return;                         // (the floor: the sample waits, not the context)
-    const int half = a.P.KX * 16;                      // context samples per vector
+  // Window context, in two parts.  The image of step t + 1 is built at the
+  // start of step t from the ring, all but the entries of the samples of step
+  // td = t - A, which are drawn last: once those arrive only they are written
+  // before the products, so one LDS write and one barrier lie between a drawn
+  // sample and the products (subscale 16, F = 4: 8.75 -> 8.34 us a step).
+  const int half = a.P.KX * 16;                        // context samples per vector
+  const int D = LAG ? a.F + 1 + a.A : 0;
+  auto sample_at = [&](int b, int jj, int y) {         // context sample jj of vector b
+    aput_p(cimg, 2 * jj, fscale(y >> 8), b);
+    aput_p(cimg, 2 * jj + 1, fscale(y & 255), b);
+  };
+  auto window_image = [&](int64_t t) {
+    const int64_t td = t - (LAG ? a.A : 0);
+    const bool late = td >= 0;                         // (earlier samples: in the ring from the start)
     for (int x = tid; x < L * half; x += WR_THREADS) {
       const int b = x / half, jj = x % half;
       const int vb = min(v0 + b, a.S - 1), s = vb % a.B;
@@ -853,7 +863,7 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
       bool seen;
       if (!LAG) {                                      // lockstep: the samples before n1 of earlier rows
         qn = n1 - 1 - jj;
-        seen = qn >= 0 && qn < (int64_t)a.B * (a.t0 + t + 1);
+        seen = qn >= 0 && qn < (int64_t)a.B * (a.t0 + t + (late ? 0 : 1));
       } else {                                         // horizon F: half before n1, half after
         const int d = jj < half / 2 ? -1 - jj : 1 + (jj - half / 2);
         qn = n1 + d;
@@ -861,24 +871,58 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
         const int sd = s + d + 2 * half * a.B;         // > 0
         const int dk = sd / a.B - 2 * half, z = sd % a.B;
         seen = p1 >= 0 && p1 < a.rows && qn >= 0 && qn < (int64_t)a.B * a.rows && z < s && dk <= a.F;
+        if (late && z == s - 1 && dk == a.F) seen = false;
       }
-      float c = 0.0f, f = 0.0f;
-      if (seen) {
-        const int sv = hist[(vb / a.B - ub0) * HC + (int)(qn & HCm)];
-        c = fscale(sv >> 8);
-        f = fscale(sv & 255);
-      }
-      aput(cimg + ((2 * jj) >> 5) * WR_FRAG, (2 * jj) & 31, c, b);
-      aput(cimg + ((2 * jj + 1) >> 5) * WR_FRAG, (2 * jj + 1) & 31, f, b);
+      const int sv = seen ? hist[(vb / a.B - ub0) * HC + (int)(qn & HCm)] : 0;
+      aput_p(cimg, 2 * jj, seen ? fscale(sv >> 8) : 0.0f, b);
+      aput_p(cimg, 2 * jj + 1, seen ? fscale(sv & 255) : 0.0f, b);
     }
     __syncthreads();
+  };
+  // the samples of step td: into the ring, and into the contexts that see them.
+  // Horizon: sub-tensor z = s - 1 ran position p1 + F (of vector s's next, p1)
+  // at step td, and no other sub-tensor's sample of that step is seen.
+  auto late_samples = [&](int64_t t) {
+    const int64_t td = t - (LAG ? a.A : 0);
+    if (tid < nut * a.B && td >= 0) {                  // one thread per (utterance, lane)
+      const int vv = ub0 * a.B + tid, z = tid % a.B;   // vector of that lane
+      int y = 0;
+      const int64_t p = vpos<LAG>(a, vv, td);          // lanes idle at step td drew nothing
+      if (vv < a.S) {                                  // (but their words are waited for too)
+        if (!wait_sample(a.xc + (size_t)(vv / L) * P.x_words + P.x_sp, L, P.SS, vv % L, (uint32_t)(td + 1), &y, a))
+          misc[0] = 1;
+        if (!FL && p >= 0 && p < a.rows) {
+          if (LAG) {
+            const int b = vv + 1 - v0;
+            const int64_t p1 = t + 1 + a.t0 - (int64_t)(z + 1) * D;
+            const int d = a.B * a.F - 1, jj = d < 0 ? 0 : half / 2 + d - 1;
+            if (z + 1 < a.B && b >= 0 && b < L && jj < half && p1 >= 0 && p1 < a.rows) sample_at(b, jj, y);
+          } else {
+            for (int b = 0; b < L; ++b) {
+              const int vb = v0 + b, jj = a.B + vb % a.B - 1 - z;
+              if (vb < a.S && vb / a.B == vv / a.B && jj < half) sample_at(b, jj, y);
+            }
+          }
+          const int64_t qn = (int64_t)a.B * (p + (LAG ? 0 : a.t0)) + z;   // the sample's index
+          hist[(tid / a.B) * HC + (int)(qn & HCm)] = y;
+        }
+      }
+    }
+    __syncthreads();
+  };
+  auto context = [&](int64_t t) {
+    if (table) {
+      table_image(t);
+    } else {
+      late_samples(t);
+      if (misc[0] || FL) return;                       // (the floor: the sample waits, not the context)
     }
     const bool apart = gt == 2 || ahead;               // kept apart from the products of h
     f32x4 c0 = apart ? f32x4{0, 0, 0, 0} : acc0, c1 = apart ? f32x4{0, 0, 0, 0} : acc1;
 #pragma unroll
     for (int x = 0; x < (CTX ? 8 : 0); x += 2) {
-      if (x < P.KX) c0 = mfma(afrag(cimg, x), WX[x], c0);
-      if (x + 1 < P.KX) c1 = mfma(afrag(cimg, x + 1), WX[x + 1], c1);
+      if (x < P.KX) c0 = mfma(afrag_p(cimg, x), WX[x], c0);
+      if (x + 1 < P.KX) c1 = mfma(afrag_p(cimg, x + 1), WX[x + 1], c1);
     }
     if (apart) {
       xa0 = c0;
@@ -892,58 +936,19 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
     return gt < 2 && b < L ? a.cb[cb_offset<LAG>(a, min(v0 + b, a.S - 1), t) + row] : 0.0f;
   };
   // Wait for one half of h of the group's vectors and write the operand
-  // tiles kt0 ...: with 8 vectors (7 words per thread) lane jj of wave 0
-  // first watches the last word head jj publishes, so that only 7 words per
-  // wave are polled while h is not there; with fewer vectors every thread
-  // polls its own words directly, the first probe after WR_POLL_DELAY.
+  // tiles kt0 ....
   auto gather_half = [&](const xw* Y, uint32_t tag, int kt0) {
-    if (L < 8) __builtin_amdgcn_s_sleep(WR_POLL_DELAY);
-    if (L >= 8) {
-      if (wave == 0) {
-        const int hj = lane < P.NH ? lane : 0;
-        float y;
-        if (!poll_strided<1>(Y + (L - 1) * Hh + 64 * hj + 63, 0, tag, &y, a)) misc[0] = 1;
-      }
-      __syncthreads();
-      if (misc[0]) return;
-    }
-    constexpr int PER = (L * 448 + WR_THREADS - 1) / WR_THREADS;   // words per thread at most
-    float y[PER];
-    uint32_t pending = 0;
-#pragma unroll
-    for (int m = 0; m < PER; ++m)
-      if (tid + m * WR_THREADS < L * Hh) pending |= 1u << m;
-    WaitBudget wb{wr_clock(), 0};
-    while (pending) {
-      xw w[PER];
-#pragma unroll
-      for (int m = 0; m < PER; ++m) w[m] = (pending >> m & 1u) ? xpeek(Y + tid + m * WR_THREADS) : 0;
-#pragma unroll
-      for (int m = 0; m < PER; ++m)
-        if ((pending >> m & 1u) && xok(w[m], tag)) {
-          y[m] = xval(w[m]);
-          pending &= ~(1u << m);
-        }
-      if (pending && !wait_ok(wb, a.err, a.limit, a.err)) {
-        misc[0] = 1;
-        break;
-      }
-    }
-#pragma unroll
-    for (int m = 0; m < PER; ++m) {
-      const int x = tid + m * WR_THREADS;
-      if (!FL && x < L * Hh && !(pending >> m & 1u)) {
-        const int b = x / Hh, col = x % Hh;
-        aput(img + (kt0 + (col >> 5)) * WR_FRAG, col & 31, y[m], b);
-      }
-    }
+    __builtin_amdgcn_s_sleep(WR_POLL_DELAY);
+    if (!gather_y<L, 64 * KH, !FL>(Y, tag, img + kt0 * WR_FRAGP, -1, a)) misc[0] = 1;
     __syncthreads();
   };
+  if (WR_LOCAL_XCHG) lx = leads_share_xcd(X + P.x_xcc, P.NH + P.NU, P.NH + k, misc + 1, a);
   phase_c();
   phase_f();
   // the first step's context: row 0 of the table; for a resumed window
   // context, from the refilled rings (nothing to wait for: those samples were
   // made before the launch); a call's step 0 has none
+  if (CTX && !table && a.prev && !FL) window_image(-1);
   if (table || (CTX && a.prev)) context(-1);
   publish(1u, cbv(bl0, 0), cbv(bl0 + 1, 0));
   const xw* YC = X + P.x_yc;
@@ -953,6 +958,7 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
     const float cb0 = cbv(bl0, t + 1), cb1 = cbv(bl0 + 1, t + 1);
     const bool tr = g == 0 && k == 0 && tid == 0;
     if (tr) trace_at(a, t, 16);
+    if (CTX && !table && !FL) window_image(t);
     if (ahead) {
       context(t);
       if (misc[0]) return;

@@ -138,10 +138,11 @@ __device__ __forceinline__ void xpub_l(xw* p, uint32_t tag, float v, bool local)
   else __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Two adjacent words (p 8-byte aligned) written and read as one 64-bit access.
-__device__ __forceinline__ void xpub2(xw* p, uint32_t tag, float v0, float v1) {
+__device__ __forceinline__ void xpub2_l(xw* p, uint32_t tag, float v0, float v1, bool local) {
   const uint64_t w = (uint64_t)((__float_as_uint(v0) & ~1u) | (tag & 1u)) |
                      (uint64_t)((__float_as_uint(v1) & ~1u) | (tag & 1u)) << 32;
-  __hip_atomic_store((uint64_t*)p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (local) __hip_atomic_store((uint64_t*)p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else __hip_atomic_store((uint64_t*)p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint64_t xpeek2(const xw* p) {
   return __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

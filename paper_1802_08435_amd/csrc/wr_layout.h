@@ -326,13 +326,15 @@ WR_HD inline bool sparse_plan(int H, int SR, int BH, int BW, int NRC, int NRF, P
 // so each head reads and evaluates as few gate words as possible.  The MFMA operand A
 // carries vector b in rows 2b (bf16 high part) and 2b+1 (remainder), so a
 // group does the same number of matrix-core instructions as batch 1.
-// Head j of group g sits at block 8j + g (one XCD per group); the units of all
-// groups take the remaining blocks.  A unit owns UCT = 4 coarse and 4 fine
+// Workgroup i of group g (its heads, then its units) sits at block 8i + g: one
+// XCD per group.  A unit owns UCT = 4 coarse and 4 fine
 // row tiles: waves 0-3 the coarse tiles (coarse columns in LDS, fine columns
 // in VGPRs), waves 4-7 the fine tiles (coarse columns in VGPRs, fine columns
 // in LDS).
 // ---------------------------------------------------------------------------
 #define WR_BL 8           // most vectors per group
+#define WR_KGP 272        // bytes of 8 inputs of an operand image: 16 rows of 16 bytes, padded
+#define WR_FRAGP (4 * WR_KGP)
 #define WR_BUCT 4         // coarse (and fine) row tiles per batched unit
 
 struct BatchPlan {
@@ -340,10 +342,9 @@ struct BatchPlan {
   int L;                  // vectors per group (2, 4 or 8)
   int hw_frags;           // head fragments per wave (as the batch-1 plan)
   int u_lds_w;            // unit LDS weights: [UCT][KT] coarse tiles, then [UCT][KT] fine tiles
-  int x_xcc;              // per group: the XCD of each head, published at the start
-  int x_yc, x_yf, x_ga, x_gf, x_pc, x_pf, x_sp, x_xc, x_xf, x_cc, x_cf, x_words;   // per group: y [L][Hh],
-      // g [3][Hh][L], p [NH][L][256], drawn samples [2][L], e-gate context terms [Hh][L] x 2,
-      // drawn coarse and fine classes [L] each
+  int x_xcc;              // per group: the XCD of each head and unit, published at the start
+  int x_yc, x_yf, x_ga, x_gf, x_pc, x_pf, x_sp, x_xc, x_xf, x_words;   // per group: y [L][Hh],
+      // g [3][Hh][L], p [NH][L][256], drawn samples [2][L], e-gate context terms [Hh][L] x 2
   int KX;                 // subscale context column tiles (Dx / 32), 0 without context
   int HC;                 // drawn samples a unit keeps per utterance (ring, a power of two)
   int HS;                 // utterances whose samples a unit keeps (slots of HC)
@@ -353,16 +354,11 @@ struct BatchPlan {
 };
 
 // Role of block b: head index j (group *g), NH + unit index, or -1 (idle).
+// Blocks are dealt round-robin over the 8 XCDs, so group g (its heads, then
+// its units) sits on XCD g: at most 7 + 21 workgroups on its 32 CUs.
 WR_HD inline int wr_batch_role(const BatchPlan& P, int b, int* g) {
-  if (b < 8 * P.NH && b % 8 < P.G) {
-    *g = b % 8;
-    return b / 8;
-  }
-  const int before = b < 8 * P.NH ? (b / 8) * P.G + (b % 8 < P.G ? b % 8 : P.G) : P.NH * P.G;
-  const int ku = b - before;
-  if (ku >= P.NU * P.G) return -1;
-  *g = ku / P.NU;
-  return P.NH + ku % P.NU;
+  *g = b % 8;
+  return *g < P.G && b / 8 < P.NH + P.NU ? b / 8 : -1;
 }
 
 // B, F, A: subscale factor, future horizon (F < 0: lockstep rows) and the
@@ -383,9 +379,7 @@ WR_HD inline bool batch_plan(int H, int n_vectors, BatchPlan* P, int ctx_dim = 0
   P->NU = P->NCT / WR_BUCT;
   P->L = n_vectors <= 2 * WR_BL ? WR_BL / 4 : n_vectors <= 4 * WR_BL ? WR_BL / 2 : WR_BL;
   P->G = (n_vectors + P->L - 1) / P->L;
-  int gr = 8 * (P->NH - 1) + P->G;           // the last head block + 1
-  while (gr - P->NH * P->G < P->NU * P->G) ++gr;
-  P->grid = gr;
+  P->grid = 8 * (P->NH + P->NU - 1) + P->G;  // the last group's last unit block + 1
   P->hw_frags = 2 * P->KH + 8;
   P->u_lds_w = 2 * WR_BUCT * P->KT * WR_FRAG;
   int o = 0;
@@ -401,17 +395,13 @@ WR_HD inline bool batch_plan(int H, int n_vectors, BatchPlan* P, int ctx_dim = 0
   P->x_sp = take(P->SS * P->L);
   P->x_xc = take(P->L * P->Hh);
   P->x_xf = take(P->L * P->Hh);
-  P->x_cc = take(P->L);
-  P->x_cf = take(P->L);
-  P->x_xcc = take(P->NH);
+  P->x_xcc = take(P->NH + P->NU);
   P->x_words = o;
   // head: operand images (2 KT + 2 fragments), first-layer partials [2][L][64],
-  // logit sums [L][256], logits [L][256], both halves of h and the staged
-  // gate inputs [2 + 4][L][448], bias row offsets [L], misc [64],
-  // uniforms [2][L][64][2], targets [2][L][64], and with up to 4 vectors the
-  // fine half's staged gate inputs [4][L][448]
-  P->lds_h = (2 * P->KT + 2) * WR_FRAG + 4 * (2 * P->L * 64 + 2 * P->L * 256 + 6 * P->L * 448 + 2 * P->L + 64 +
-                                               2 * P->L * 64 * 2 + 2 * P->L * 64 + (P->L <= 4 ? 4 * P->L * 448 : 0));
+  // logits [L][256], class biases [2][256], both halves of h [2][L][448], bias row offsets [L], misc
+  // [64], uniforms [2][L][64][2], targets [2][L][64]
+  P->lds_h = (2 * P->KT + 2) * WR_FRAGP + 4 * (2 * P->L * 64 + P->L * 256 + 512 + 2 * P->L * 448 + 2 * P->L + 64 +
+                                                2 * P->L * 64 * 2 + 2 * P->L * 64);
   // Ring of drawn samples per utterance: lockstep, the Dx/2 samples before
   // a row plus the row; with horizon F the lanes of an utterance are up to
   // (B - 1)(F + 1 + A) positions apart, so the newest sample and the oldest
@@ -426,7 +416,7 @@ WR_HD inline bool batch_plan(int H, int n_vectors, BatchPlan* P, int ctx_dim = 0
   }
   // unit: weights, operand image (2 KT fragments), context image (KX fragments),
   // sample rings [HS][HC], misc [16]
-  P->lds_u = P->u_lds_w + (2 * P->KT + P->KX) * WR_FRAG + 4 * (P->RING + 16);
+  P->lds_u = P->u_lds_w + (2 * P->KT + P->KX) * WR_FRAGP + 4 * (P->RING + 16);
   P->lds = P->lds_h > P->lds_u ? P->lds_h : P->lds_u;
   return P->lds <= 160 * 1024 && P->grid <= 256;
 }
