@@ -66,18 +66,23 @@ struct PersistArgs {
 };
 
 // Teacher-forced recurrence of the dense batch-1 model (wr_score.hip).
-// With several utterances (wr_score_multi, nv of them) every per-utterance
-// array holds them one after another: cb [nv][n_cb][3H], target [nv][T],
-// h [nv][H], c / f [nv], traj [nv][T][Hh]; xc is [2][8][H].
+// S utterances in G groups of LV (the last one partly used); every
+// per-utterance array holds them one after another: cb [S][n_cb][3H], target
+// [S][T], h [S][H], c / f [S], traj [S][T][Hh].  Exchange words of a group:
+// h [2][LV][H], then the XCDs of its workgroups.
+inline __host__ __device__ int score_words(int H, int LV) { return 2 * LV * H + 64; }
 struct ScoreArgs {
-  const uint4* w;           // [H/16][3][H/32][64 lanes] R fragments: workgroup k, gate g: rows g H + 16 k ..
+  const uint4* w;           // [H/32][4 waves][3H/64][64 lanes] R fragments: workgroup k (rows g H + 32 k ..): fine
+                            // (32 k >= Hh) wave w [3 gates] unit tile w / 2, column tiles w % 2, + 2, ..; coarse wave w
+                            // [2 unit tiles][3 gates], column tiles w, w + 2, .. of the coarse columns (w < 2) or
+                            // half w - 2 of the fine columns
   const float* Iw;          // [3H][3], I* mask applied
-  const float* cb;          // [n_cb][3H] gate bias + conditioning per frame
+  const float* cb;          // [S][n_cb][3H] gate bias + conditioning per frame
   int64_t n_cb;
   int frame_len;
-  int H, Hh;
+  int S, G;
   int64_t T, t0;
-  const uint16_t* target;   // [T]
+  const uint16_t* target;   // [S][T]
   const float* h_in;        // [H] or null
   const uint8_t* c_in;
   const uint8_t* f_in;
@@ -86,10 +91,9 @@ struct ScoreArgs {
   uint8_t* f_out;
   float* traj_c;            // [T][Hh] coarse half of h after each step
   float* traj_f;            // [T][Hh] fine half
-  xw* xc;                   // [2][H] exchange words, zeroed before the launch
+  xw* xc;                   // [G][score_words] exchange words, zeroed before the launch
   unsigned* err;
   u64 limit;
-  int nv;                   // wr_score_multi: utterances of the launch (1..8)
 };
 
 struct BatchArgs {
@@ -199,8 +203,7 @@ struct CnnInputArgs {
 const void* wr_small_kernel_ptr(int H);
 const void* wr_uniforms_kernel_ptr();
 const void* wr_persist_kernel_ptr(int KH);   // null if no instantiation for KH
-const void* wr_score_kernel_ptr(int KT2);    // teacher-forced recurrence for H = 32 KT2; null if none
-const void* wr_score_multi_ptr(int KT2);     // the same for up to 8 utterances at once
+const void* wr_score_kernel_ptr(int KT2, int LV);   // teacher-forced recurrence for H = 32 KT2, LV utterances a group; null if none
 const void* wr_score_nll_ptr();
 const void* wr_sparse_kernel_ptr(int KH, int GU);   // null if no instantiation
 const void* wr_cond_kernel_ptr();

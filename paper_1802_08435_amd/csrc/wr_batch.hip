@@ -65,22 +65,6 @@ __device__ __forceinline__ T* opaque(T* p) {
   return p;
 }
 
-// Operand images of this kernel: the 16 rows of 8 inputs (256 bytes, lane
-// order) padded to 272, so the words of consecutive columns that a wave
-// writes while it gathers fall into different LDS banks.
-__device__ __forceinline__ bf16x8 afrag_p(const unsigned char* img, int kt) {
-  const int l = threadIdx.x & 63;
-  return *(const bf16x8*)(img + kt * WR_FRAGP + (l >> 4) * WR_KGP + (l & 15) * 16);
-}
-// Input column c of vector b of an image.
-__device__ __forceinline__ void aput_p(unsigned char* img, int c, float x, int b) {
-  const float hi = __uint_as_float(__float_as_uint(x) & 0xffff0000u);
-  const __bf16 bh = (__bf16)hi, bl = (__bf16)(x - hi);
-  __bf16* row0 = (__bf16*)(img + (c >> 3) * WR_KGP + 2 * b * 16) + (c & 7);
-  row0[0] = bh;
-  row0[8] = bl;
-}
-
 // Delay (x 64 clocks) before the first probe of words that other workgroups
 // publish at about the time this one starts waiting.  A probe issued at once
 // would almost surely come back without them, and the early probes of all
@@ -89,53 +73,6 @@ __device__ __forceinline__ void aput_p(unsigned char* img, int c, float x, int b
 // 16 with F = 4, us a step: 4 x 64 clocks 7.18 / 5.80 / 7.74; 2: 7.23 / 5.81 /
 // 7.80; 10: 7.49 / 5.81 / 8.53).
 #define WR_POLL_DELAY 4
-
-// Gather y [L][HH] of one half of h into operand image `img` (columns 0 ..
-// HH - 1 of each vector): 16-byte loads of four adjacent columns, each word
-// checked for its tag, converted and written as two 8-byte LDS stores (4-byte
-// loads and 2-byte stores made the gather bound by its instructions and by
-// LDS bank conflicts: 9.05 -> 7.3 us a step at 64 utterances).  Quads
-// of columns [skip, skip + 64) (a head's own slice) are left out; skip < 0:
-// none.  With PUT false the words are only waited for.
-template <int L, int HH, bool PUT>
-__device__ __forceinline__ bool gather_y(const xw* Y, uint32_t tag, unsigned char* img, int skip, const BatchArgs& a) {
-  constexpr int Q = HH / 4, N = (L * Q + WR_THREADS - 1) / WR_THREADS;
-  uint32_t pending = 0;
-  xw4 w[N];
-#pragma unroll
-  for (int m = 0; m < N; ++m) {
-    const int q = threadIdx.x + WR_THREADS * m;
-    if (q < L * Q && !(skip >= 0 && (q % Q) / 16 == skip / 64)) pending |= 1u << m;
-  }
-  const uint32_t todo = pending;
-  WaitBudget wb{0, 0};
-  for (;;) {
-    const __amdgpu_buffer_rsrc_t r = xrsrc(xopaque(Y), (uint32_t)(L * HH) * 4u);
-#pragma unroll
-    for (int m = 0; m < N; ++m)
-      if (pending >> m & 1u) w[m] = xpeek4(r, 16u * (threadIdx.x + WR_THREADS * m));
-#pragma unroll
-    for (int m = 0; m < N; ++m)
-      if ((pending >> m & 1u) && xok4(w[m], tag)) pending &= ~(1u << m);
-    if (!pending) break;
-    if (!wb.spins) wb.start = wr_clock();
-    if (!wait_ok(wb, a.err, a.limit, a.err)) return false;
-  }
-  if (PUT) {
-#pragma unroll
-    for (int m = 0; m < N; ++m)
-      if (todo >> m & 1u) {
-        const int q = threadIdx.x + WR_THREADS * m, b = q / Q, c = 4 * (q % Q);
-        const float x0 = xval(w[m].x), x1 = xval(w[m].y), x2 = xval(w[m].z), x3 = xval(w[m].w);
-        unsigned char* p = img + (c >> 3) * WR_KGP + 2 * b * 16 + (c & 7) * 2;
-        *(uint2*)p = uint2{__builtin_amdgcn_perm(w[m].y, w[m].x, 0x07060302), __builtin_amdgcn_perm(w[m].w, w[m].z, 0x07060302)};
-        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-        auto low = [](float x) { return (__bf16)(x - __uint_as_float(__float_as_uint(x) & 0xffff0000u)); };
-        *(bf16x4*)(p + 16) = bf16x4{low(x0), low(x1), low(x2), low(x3)};
-      }
-  }
-  return true;
-}
 
 // Drawn samples for the subscale context cross groups, whose heads and units
 // are not chained step by step to each other: a sample word carries the
@@ -494,7 +431,7 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
     if (FL) {                                       // the exchange alone: own slice out, the others in
       xpub_l(Y + sb * HH + su, tag, 0.0f, lx);
       __builtin_amdgcn_s_sleep(WR_POLL_DELAY);
-      if (!gather_y<L, HH, false>(Y, tag, img, 64 * j, a)) misc[0] = 1;
+      if (!gather_y<L, HH, WR_THREADS, false>(Y, tag, img, tid, 64 * j, a)) misc[0] = 1;
       return;
     }
     const float cbe = (fine ? cbf : cbc) + (CTX ? xval(pw[fine ? 7 : 6]) : 0.0f);
@@ -519,7 +456,7 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
     *hs = hn;
     aput_p(img, su, xround(hn), sb);
     __builtin_amdgcn_s_sleep(WR_POLL_DELAY);
-    if (!gather_y<L, HH, true>(Y, tag, img, 64 * j, a)) misc[0] = 1;   // the other heads' slices
+    if (!gather_y<L, HH, WR_THREADS, true>(Y, tag, img, tid, 64 * j, a)) misc[0] = 1;   // the other heads' slices
   };
   // the table row of vector tid's next position: frame and sample within it,
   // stepped without a division (the steps' tail is on the chain)
@@ -939,7 +876,7 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
   // tiles kt0 ....
   auto gather_half = [&](const xw* Y, uint32_t tag, int kt0) {
     __builtin_amdgcn_s_sleep(WR_POLL_DELAY);
-    if (!gather_y<L, 64 * KH, !FL>(Y, tag, img + kt0 * WR_FRAGP, -1, a)) misc[0] = 1;
+    if (!gather_y<L, 64 * KH, WR_THREADS, !FL>(Y, tag, img + kt0 * WR_FRAGP, tid, -1, a)) misc[0] = 1;
     __syncthreads();
   };
   if (WR_LOCAL_XCHG) lx = leads_share_xcd(X + P.x_xcc, P.NH + P.NU, P.NH + k, misc + 1, a);

@@ -82,12 +82,11 @@ struct wavernn_model {
   // teacher-forced scoring on the dense batch-1 plan: the recurrence kernel, the
   // output layers as GEMM fragments (O1 [NP][Hh], O2 [256][NP], O3, O4; NP = Hh
   // rounded up to 128) and biases, and the buffers of a call
-  const void* sk = nullptr;
-  const void* smk = nullptr;         // the scoring recurrence for up to 8 utterances at once (null: none)
-  xw* d_sxc[WR_FAN] = {};            // its exchange words [2][8][H] per slot
-  float* d_scb[WR_FAN] = {};         // its tables [8][frames][3H] per slot
-  int64_t scb_cap = 0;               // floats of each
-  uint4* d_srw = nullptr;             // [H/16][3][H/32][64] R fragments of the scoring recurrence
+  bool score = false;                // served (its kernels exist and their grids fit)
+  xw* d_sxc = nullptr;               // its exchange words, for 8 groups of 8
+  float* d_scb = nullptr;            // its tables [utterances][frames][3H]
+  int64_t scb_cap = 0;               // floats
+  uint4* d_srw = nullptr;             // R fragments of the scoring recurrence (ScoreArgs::w)
   uint4* d_sw = nullptr;
   float* d_sb = nullptr;
   size_t sw_off[4] = {}, sb_off[4] = {};
@@ -101,7 +100,6 @@ struct wavernn_model {
   // concurrent batch-1 launches: a few utterances, each on its own persistent
   // grid and its own internal stream, all grids co-resident at once
   int nfan = 0;                      // most utterances served this way (0: none)
-  bool score_fan = false;            // scoring runs up to nfan utterances' recurrence grids side by side
   hipStream_t fan_st[WR_FAN - 1] = {};  // launches 1 .. (launch 0 runs on the caller's stream)
   hipEvent_t fan_fork = nullptr, fan_join[WR_FAN - 1] = {};
   xw* d_fxc[WR_FAN] = {};            // exchange words of launch i
@@ -392,8 +390,6 @@ wavernn_status check_coresident(wavernn_model* m, const void* k, int grid, int l
   return WAVERNN_OK;
 }
 
-int score_lds(int H);
-int score_multi_lds(int H);
 
 // Launch s of n persistent grids side by side: heads and mirrors on XCD
 // 8 s / n, units spread over the XCDs.
@@ -438,14 +434,6 @@ wavernn_status build_fanout(wavernn_model* m) {
     if (s != WAVERNN_OK) return s;
   }
   m->nfan = n;
-  if (m->sk) {   // the scoring recurrences' grids (H / 16 workgroups each) of n launches together
-    const int H = P.H;
-    int c1 = 0, c8 = 0;
-    HIPOK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&c1, m->sk, WR_THREADS, score_lds(H)));
-    if (m->smk) HIPOK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&c8, m->smk, WR_THREADS, score_multi_lds(H)));
-    const int per_cu = m->smk ? std::min(c1, c8) : c1;
-    m->score_fan = per_cu * prop.multiProcessorCount >= n * (H / 16);
-  }
   return WAVERNN_OK;
 }
 
@@ -800,10 +788,6 @@ wavernn_status build_cnn(wavernn_model* m, const wavernn_ctx_cnn* n) {
   return WAVERNN_OK;
 }
 
-// LDS of the scoring recurrence: the operand image of h, [3][16] pre-activations, misc.
-int score_lds(int H) { return H / 32 * WR_FRAG + 48 * 4 + 64; }
-int score_multi_lds(int H) { return H / 32 * WR_FRAG + 3 * 8 * 16 * 4 + 64; }
-
 // Teacher-forced scoring on the dense batch-1 plan: the recurrence kernel
 // (the plan's units, heads that evaluate their own slices from the given
 // bytes) and the output layers as GEMM fragments for the matrix cores: O1 and
@@ -813,17 +797,21 @@ int score_multi_lds(int H) { return H / 32 * WR_FRAG + 3 * 8 * 16 * 4 + 64; }
 wavernn_status build_score(wavernn_model* m, const wavernn_weights* w) {
   const PersistPlan& P = m->plan;
   const int H = P.H, Hh = P.Hh, NP = (Hh + 127) / 128 * 128, KT2 = H / 32;
-  m->sk = wr_score_kernel_ptr(KT2);
-  if (!m->sk) return fail(WAVERNN_E_UNSUPPORTED, "hidden %d: no scoring kernel instantiation", H);
-  {   // recurrence: workgroup k, gate g holds rows g H + 16 k .. + 15 over every column tile
+  if (!wr_score_kernel_ptr(KT2, 1)) return fail(WAVERNN_E_UNSUPPORTED, "hidden %d: no scoring kernel instantiation", H);
+  {   // the recurrence's fragments, in the order its waves use them (ScoreArgs::w)
     REff R{&m->cfg, w};
     auto Rm = [&](int r, int c) { return R(r, c); };
-    std::vector<uint16_t> rw((size_t)H / 16 * 3 * KT2 * 512);
-    for (int k = 0; k < H / 16; ++k)
-      for (int g = 0; g < 3; ++g)
-        for (int kt = 0; kt < KT2; ++kt)
-          frag(rw.data() + ((size_t)(k * 3 + g) * KT2 + kt) * 512, Rm, [&](int r) { return g * H + 16 * k + r; },
-               32 * kt);
+    const int KT = KT2 / 2, FH = KT2 / 2, CH = KT / 2, NF = 3 * FH;
+    std::vector<uint16_t> rw((size_t)H / 32 * 4 * NF * 512);
+    for (int k = 0; k < H / 32; ++k)
+      for (int wv = 0; wv < 4; ++wv)
+        for (int f = 0; f < NF; ++f) {
+          const bool fine = 32 * k >= Hh;
+          const int q = fine ? (wv >> 1) * 3 + f / FH : f / CH, i = fine ? f % FH : f % CH;   // unit tile * 3 + gate
+          const int kt = fine ? 2 * i + (wv & 1) : wv < 2 ? 2 * i + wv : KT + (wv - 2) * CH + i;
+          frag(rw.data() + ((size_t)(k * 4 + wv) * NF + f) * 512, Rm,
+               [&](int r) { return q % 3 * H + 32 * k + 16 * (q / 3) + r; }, 32 * kt);
+        }
     wavernn_status s = m->upload(&m->d_srw, rw.data(), rw.size() * 2);
     if (s != WAVERNN_OK) return s;
   }
@@ -849,10 +837,10 @@ wavernn_status build_score(wavernn_model* m, const wavernn_weights* w) {
   if ((s = m->upload(&m->d_sw, wv.data(), wv.size() * 2)) != WAVERNN_OK) return s;
   if ((s = m->upload(&m->d_sb, bv.data(), bv.size() * 4)) != WAVERNN_OK) return s;
   HIPOK(hipFuncSetAttribute(wr_cnn_gemm_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * CNN_LDS_BUF));
-  if ((s = check_coresident(m, m->sk, H / 16, score_lds(H), "scoring")) != WAVERNN_OK) return s;
-  // several utterances per launch where its grid fits too (else one at a time)
-  m->smk = wr_score_multi_ptr(H / 32);
-  if (m->smk && check_coresident(m, m->smk, H / 16, score_multi_lds(H), "scoring") != WAVERNN_OK) m->smk = nullptr;
+  for (int LV = 1; LV <= 8 && LV < 2 * m->cfg.max_streams; LV *= 2)
+    if ((s = check_coresident(m, wr_score_kernel_ptr(KT2, LV), 8 * (H / 32), 0, "scoring")) != WAVERNN_OK) return s;
+  if ((s = m->alloc(&m->d_sxc, (size_t)8 * score_words(H, 8) * 4)) != WAVERNN_OK) return s;
+  m->score = true;
   return WAVERNN_OK;
 }
 
@@ -1347,30 +1335,15 @@ wavernn_status run_score(wavernn_model* m, const RunIO& io) {
   const int64_t n_cb = m->cfg.cond_dim > 0 ? io.n_frames : 1;
   const bool post = io.zc || io.zf || io.nll;
   const int64_t ch = std::min(CH, rows);   // rows of one chunk of the output layers
-  // Up to nfan utterances: one single-utterance grid each, side by side on
-  // the caller's stream and the internal ones (measured faster than one grid
-  // carrying them); more: launches of up to 8 on the several-utterance
-  // kernel, nfan of them side by side.  Each slot has its own exchange words
-  // and table; all are joined before the output layers.
-  const int nf = m->score_fan ? m->nfan : 1;
-  const int LV = io.S > nf && m->smk ? 8 : 1;
-  const int G = (io.S + LV - 1) / LV;
-  const int conc = std::min(G, nf);
-  const bool slots = conc > 1 || LV > 1;   // per-slot buffers (else the model's own)
-  const int H = m->plan.H, Dc = m->cfg.cond_dim;
-  const int64_t cbf = (int64_t)8 * n_cb * 3 * H;    // table floats per slot (up to 8 utterances)
-  if (rows > m->traj_cap || (post && ch > m->so_cap) || n_cb > m->cb_cap || (slots && cbf > m->scb_cap))
-    HIPOK(hipStreamSynchronize(io.st));
-  wavernn_status st = grow_cb(m, &m->d_cb, &m->cb_cap, n_cb);
-  if (st != WAVERNN_OK) return st;
-  if (slots) {
-    for (int i = 0; i < WR_FAN; ++i)
-      if (!m->d_sxc[i] && (st = m->alloc(&m->d_sxc[i], (size_t)(2 * 8 * H + 1) / 2 * 8)) != WAVERNN_OK) return st;
-    if (cbf > m->scb_cap) {
-      for (int i = 0; i < WR_FAN; ++i)
-        if ((st = m->alloc(&m->d_scb[i], (size_t)cbf * 4)) != WAVERNN_OK) return st;
-      m->scb_cap = cbf;
-    }
+  // One launch for all utterances: as few per group as 8 groups allow.
+  const int H = m->plan.H, Dc = m->cfg.cond_dim, NW = H / 32;
+  const int LV = io.S <= 8 ? 1 : io.S <= 16 ? 2 : io.S <= 32 ? 4 : 8, G = (io.S + LV - 1) / LV;
+  const int64_t cbf = (int64_t)io.S * n_cb * 3 * H;
+  if (rows > m->traj_cap || (post && ch > m->so_cap) || cbf > m->scb_cap) HIPOK(hipStreamSynchronize(io.st));
+  wavernn_status st;
+  if (cbf > m->scb_cap) {
+    if ((st = m->alloc(&m->d_scb, (size_t)cbf * 4)) != WAVERNN_OK) return st;
+    m->scb_cap = cbf;
   }
   if (rows > m->traj_cap) {
     if ((st = m->alloc(&m->d_traj, (size_t)2 * rows * Hh * 4)) != WAVERNN_OK) return st;
@@ -1381,54 +1354,39 @@ wavernn_status run_score(wavernn_model* m, const RunIO& io) {
     if ((st = m->alloc(&m->d_sz, (size_t)2 * ch * 256 * 4)) != WAVERNN_OK) return st;
     m->so_cap = ch;
   }
-  if (conc > 1) HIPOK(hipEventRecord(m->fan_fork, io.st));
-  for (int g = 0; g < G; ++g) {
-    const int slot = g % conc, s0 = g * LV, nv = std::min(LV, io.S - s0);
-    hipStream_t sst = slot > 0 ? m->fan_st[slot - 1] : io.st;
-    xw* xc = slots ? m->d_sxc[slot] : m->d_xc;
-    float* cbt = slots ? m->d_scb[slot] : m->d_cb;
-    if (slot > 0 && g < conc) HIPOK(hipStreamWaitEvent(sst, m->fan_fork, 0));
-    const float* feat = io.cond ? io.cond + (size_t)s0 * io.n_frames * Dc : nullptr;
-    if ((st = launch_cond(m, feat, n_cb, nv, cbt, sst)) != WAVERNN_OK) return st;
-    if ((st = launch_fill(xc, 2 * LV * H, sst)) != WAVERNN_OK) return st;
+  if ((st = launch_cond(m, io.cond, n_cb, io.S, m->d_scb, io.st)) != WAVERNN_OK) return st;
+  if ((st = launch_fill(m->d_sxc, (int64_t)G * score_words(H, LV), io.st)) != WAVERNN_OK) return st;
+  {
     ScoreArgs a;
     memset(&a, 0, sizeof a);
     a.w = m->d_srw;
     a.Iw = m->d_I;
-    a.cb = cbt;
+    a.cb = m->d_scb;
     a.n_cb = n_cb;
     a.frame_len = Dc > 0 ? (m->cfg.frame_len > 0 ? m->cfg.frame_len : 1) : (1 << 30);
-    a.H = H;
-    a.Hh = Hh;
+    a.S = io.S;
+    a.G = G;
     a.T = io.T;
     a.t0 = io.init ? io.init->t0 : 0;
-    a.target = io.target + (size_t)s0 * io.T;
+    a.target = io.target;
     if (io.init) {
-      a.h_in = io.init->h + (size_t)s0 * H;
-      a.c_in = io.init->c_prev + s0;
-      a.f_in = io.init->f_prev + s0;
+      a.h_in = io.init->h;
+      a.c_in = io.init->c_prev;
+      a.f_in = io.init->f_prev;
     }
     if (io.fin) {
-      a.h_out = io.fin->h + (size_t)s0 * H;
-      a.c_out = io.fin->c_prev + s0;
-      a.f_out = io.fin->f_prev + s0;
+      a.h_out = io.fin->h;
+      a.c_out = io.fin->c_prev;
+      a.f_out = io.fin->f_prev;
     }
-    a.traj_c = m->d_traj + (size_t)s0 * io.T * Hh;
-    a.traj_f = m->d_traj + (size_t)(io.S + s0) * io.T * Hh;
-    a.xc = xc;
+    a.traj_c = m->d_traj;
+    a.traj_f = m->d_traj + (size_t)rows * Hh;
+    a.xc = m->d_sxc;
     a.err = m->d_err;
     a.limit = kWaitTicks;
-    a.nv = nv;
     void* args[] = {&a};
-    // an ordinary launch of H / 16 workgroups (co-residency checked at create; waits bounded)
-    if (LV > 1)
-      HIPOK(hipLaunchKernel(m->smk, dim3(H / 16), dim3(WR_THREADS), args, score_multi_lds(H), sst));
-    else
-      HIPOK(hipLaunchKernel(m->sk, dim3(H / 16), dim3(WR_THREADS), args, score_lds(H), sst));
-  }
-  for (int i = 1; i < conc; ++i) {
-    HIPOK(hipEventRecord(m->fan_join[i - 1], m->fan_st[i - 1]));
-    HIPOK(hipStreamWaitEvent(io.st, m->fan_join[i - 1], 0));
+    // an ordinary launch (co-residency checked at create; waits bounded): workgroup k of group g is block 8 k + g
+    HIPOK(hipLaunchKernel(wr_score_kernel_ptr(H / 32, LV), dim3(8 * (NW - 1) + G), dim3(WR_THREADS), args, 0, io.st));
   }
   if (!post) return WAVERNN_OK;
   for (int64_t r0 = 0; r0 < rows; r0 += CH) {
@@ -1653,8 +1611,7 @@ wavernn_status run(wavernn_model* m, RunIO& io, bool noalloc = false) {
   if (m->fused) return run_persist(m, io);   // one fused launch per utterance
   if (m->path == PATH_PERSIST) {
     // one utterance (or a model that runs its utterances one after another) scores on the recurrence kernel
-    if (io.target && m->sk && (io.S == 1 || m->smk || (io.S <= m->nfan && m->score_fan) || (!m->nfan && !m->has_batch)))
-      return run_score(m, io);
+    if (io.target && m->score) return run_score(m, io);
     if (io.S > 1 && io.S <= m->nfan) return run_fanout(m, io);
     return io.S > 1 && m->has_batch ? run_batch(m, io) : run_persist(m, io);
   }

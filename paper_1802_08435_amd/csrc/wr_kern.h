@@ -217,6 +217,70 @@ __device__ __forceinline__ bool sum_parts(const xw* src, int stride, int j0, int
   return true;
 }
 
+// Padded operand images (batched and scoring kernels): the 16 rows of 8 inputs
+// (256 bytes, lane order) padded to 272, so the words of consecutive columns that a wave
+// writes while it gathers fall into different LDS banks.
+__device__ __forceinline__ bf16x8 afrag_p(const unsigned char* img, int kt) {
+  const int l = threadIdx.x & 63;
+  return *(const bf16x8*)(img + kt * WR_FRAGP + (l >> 4) * WR_KGP + (l & 15) * 16);
+}
+// Input column c of vector b of an image.
+__device__ __forceinline__ void aput_p(unsigned char* img, int c, float x, int b) {
+  const float hi = __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+  const __bf16 bh = (__bf16)hi, bl = (__bf16)(x - hi);
+  __bf16* row0 = (__bf16*)(img + (c >> 3) * WR_KGP + 2 * b * 16) + (c & 7);
+  row0[0] = bh;
+  row0[8] = bl;
+}
+
+// Gather y [L][HH] (one half of h, or all of it) into padded operand image
+// `img` (columns 0 .. HH - 1 of each vector) with NT threads, this one number
+// r: 16-byte loads of four adjacent columns, each word checked for its tag,
+// converted and written as two 8-byte LDS stores (4-byte loads and 2-byte
+// stores made the gather bound by its instructions and by LDS bank conflicts:
+// 9.05 -> 7.3 us a step of the batched kernel at 64 utterances).  Quads of
+// columns [skip, skip + 64) (a head's own slice) are left out; skip < 0: none.
+// With PUT false the words are only waited for.
+template <int L, int HH, int NT, bool PUT, class A>
+__device__ __forceinline__ bool gather_y(const xw* Y, uint32_t tag, unsigned char* img, int r, int skip, const A& a) {
+  constexpr int Q = HH / 4, N = (L * Q + NT - 1) / NT;
+  uint32_t pending = 0;
+  xw4 w[N];
+#pragma unroll
+  for (int m = 0; m < N; ++m) {
+    const int q = r + NT * m;
+    if (q < L * Q && !(skip >= 0 && (q % Q) / 16 == skip / 64)) pending |= 1u << m;
+  }
+  const uint32_t todo = pending;
+  WaitBudget wb{0, 0};
+  for (;;) {
+    const __amdgpu_buffer_rsrc_t rs = xrsrc(xopaque(Y), (uint32_t)(L * HH) * 4u);
+#pragma unroll
+    for (int m = 0; m < N; ++m)
+      if (pending >> m & 1u) w[m] = xpeek4(rs, 16u * (r + NT * m));
+#pragma unroll
+    for (int m = 0; m < N; ++m)
+      if ((pending >> m & 1u) && xok4(w[m], tag)) pending &= ~(1u << m);
+    if (!pending) break;
+    if (!wb.spins) wb.start = wr_clock();
+    if (!wait_ok(wb, a.err, a.limit, a.err)) return false;
+  }
+  if (PUT) {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    auto low = [](float x) { return (__bf16)(x - __uint_as_float(__float_as_uint(x) & 0xffff0000u)); };
+#pragma unroll
+    for (int m = 0; m < N; ++m)
+      if (todo >> m & 1u) {
+        const int q = r + NT * m, b = q / Q, c = 4 * (q % Q);
+        unsigned char* p = img + (c >> 3) * WR_KGP + 2 * b * 16 + (c & 7) * 2;
+        *(uint2*)p = uint2{__builtin_amdgcn_perm(w[m].y, w[m].x, 0x07060302),   // the high halves of two words
+                           __builtin_amdgcn_perm(w[m].w, w[m].z, 0x07060302)};
+        *(bf16x4*)(p + 16) = bf16x4{low(xval(w[m].x)), low(xval(w[m].y)), low(xval(w[m].z)), low(xval(w[m].w))};
+      }
+  }
+  return true;
+}
+
 // Phase timestamp of a traced step.
 template <class A>
 __device__ __forceinline__ void trace_at(const A& a, int64_t t, int slot) {

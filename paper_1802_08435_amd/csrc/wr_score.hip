@@ -3,318 +3,213 @@
 // (the gates of Eq. 2): no draw and no output layer sits in the serial loop,
 // so one kind of workgroup does it all, with one exchange per step.
 //
-// Workgroup k owns hidden units 16 k .. 16 k + 15 (all in one half).  Waves
-// 0-2 hold the tiles of its three gate rows of R (u, r, e) in VGPRs and form
-// R h for them on the matrix cores; 16 lanes finish the gates with the given
-// bytes and publish the new slice of h; waves 3-7 gather the next h from every
-// workgroup into the operand image (an all-gather: one hop per step).  The
-// products and the gate arithmetic are the sampling kernel's operation for
+// The utterances of a call are dealt to up to 8 groups of LV of them (LV = 1,
+// 2, 4 or 8: as few a group as 8 groups allow), group g on XCD g, all in one
+// launch.  Workgroup k of a group owns hidden units 32 k .. 32 k + 31 (all in
+// one half) of its vectors.  Waves 0-3 hold the six tiles of their gate rows of
+// R (u, r, e) in VGPRs and form R h on the matrix cores; of waves 4-7, 32 LV
+// threads finish the gates with the given bytes and publish the new slice of
+// h, and all gather the next h from the group's workgroups into the operand image (an
+// all-gather: one hop per step).
+//
+// What bounds it is that hop and the products between two of them, so a group
+// fits one XCD (28 of its 32 CUs at H = 896) and publishes into its L2 when it
+// finds itself there.  H = 896, us a step, with 56 workgroups of 16 units over
+// all XCDs (grids of several utterances on streams of their own) and now: one
+// utterance 2.27 -> 1.42, 21 utterances 4.2 -> 2.4 with their output layers.
+//
+// The products and the gate arithmetic are the sampling kernel's operation for
 // operation, so a scored trajectory reproduces the sampler's state bit for
 // bit: a fine row's R h is one pass over all columns (even and odd column
 // tiles in two accumulation chains), a coarse row's is the sampling units'
 // coarse-column part (two chains, + bias and conditioning) plus the sampling
 // mirrors' fine-column part (one chain per half of the fine columns, the
 // halves added), each rounded as the exchange delivers it (lowest bit
-// cleared).  The output layers run
+// cleared).  Every chain is one wave's, over several row tiles, so that an
+// operand read from LDS serves 3 (fine) or 6 (coarse) products: fine wave w
+// runs chain w % 2 of unit tile w / 2, coarse wave w chain w of both.  Vector b
+// sits in rows 2b and 2b + 1 of the operand image, so the products cost what
+// one vector's do and do not depend on the others.  The output layers run
 // afterwards over all steps at once (wr_cnn_gemm), and the NLL per step in
 // wr_score_nll.
 //
-// Exchange: h_s goes to buffer s mod 2 of [2][H] words, tagged with the
+// Exchange: h_s goes to buffer s mod 2 of [2][LV][H] words, tagged with the
 // parity of its generation s / 2 + 1.  A workgroup writes h_{s+2} into a
 // buffer only after it has read every workgroup's h_{s+1}, which each
 // publishes only after reading all of h_s: no reader is overtaken, and the
 // generation bit tells h_s from h_{s-2} in the same buffer.
 #include "wr_kern.h"
 
-namespace {
+// Delay (x 64 clocks) before a gather's first probe (one utterance of 24,000
+// steps, ms: 0 34.5, 2 34.1, 4 35.2, 8 37.4; eight a group: 0 and 2 alike).
+#define WR_SCORE_DELAY 2
 
-__device__ __forceinline__ const float* score_cb(const ScoreArgs& a, int64_t n) {
-  int64_t fr = n / a.frame_len;
-  if (fr >= a.n_cb) fr = a.n_cb - 1;
-  return a.cb + (size_t)fr * 3 * a.H;
-}
-
-// The products of a gate wave's 16 rows with h (operand image img, fragments
-// W over all KT2 column tiles).  Fine rows: even and odd column tiles in
-// acc0 and acc1 (the sampling units' fine rows).  Coarse rows: the coarse
-// column tiles in acc0 and acc1 (the units' coarse-column part), and the two
-// halves of the fine column tiles in one chain each, accA and accB (the
-// mirrors' waves, in column order).
-template <int KT2>
-__device__ __forceinline__ void score_products(const unsigned char* img, const bf16x8* W, bool fine, f32x4& acc0,
-                                               f32x4& acc1, f32x4& accA, f32x4& accB) {
-  constexpr int KT = KT2 / 2, MK = KT / 2;
-  if (fine) {
+template <int KT2, int LV>
+__global__ __launch_bounds__(WR_THREADS, 1) void wr_score_kernel(ScoreArgs a) {
+  constexpr int H = 32 * KT2, Hh = H / 2, KT = KT2 / 2, NW = H / 32;
+  constexpr int FH = KT2 / 2, CH = KT / 2, NF = 3 * FH;   // column tiles of a fine and a coarse chain, fragments
+  const int g = blockIdx.x % 8, k = blockIdx.x / 8;
+  if (g >= a.G || k >= NW) return;
+  __shared__ __align__(16) unsigned char img[KT2 * WR_FRAGP];   // operand image of h
+  __shared__ float part[24 * LV * 16];               // [chain][unit tile][gate][LV][16] products
+  __shared__ int tgt[2][64 * LV];                    // [j][LV] targets of a batch of 64 steps
+  __shared__ int misc[2];                            // [0] abort
+  const int v0 = g * LV, nv = min(LV, a.S - v0);     // this group's vectors
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const bool fine = 32 * k >= Hh;
+  xw* X = a.xc + (size_t)g * score_words(H, LV);
+  for (int i = tid; i < KT2 * WR_FRAGP / 16; i += WR_THREADS) ((uint4*)img)[i] = uint4{0, 0, 0, 0};
+  if (tid == 0) misc[0] = 0;
+  __syncthreads();
+  for (int i = tid; i < nv * H; i += WR_THREADS)
+    aput_p(img, i % H, a.h_in ? xround(a.h_in[(size_t)v0 * H + i]) : 0.0f, i / H);
+  if (wave < 4) {   // products; each role has its own step loop, so its registers are its own
+    bf16x8 W[NF];
+    const uint4* src = a.w + ((size_t)(k * 4 + wave) * NF) * 64 + lane;
 #pragma unroll
-    for (int i = 0; i < KT2; i += 2) {
-      acc0 = mfma(afrag(img, i), W[i], acc0);
-      if (i + 1 < KT2) acc1 = mfma(afrag(img, i + 1), W[i + 1], acc1);
+    for (int i = 0; i < NF; ++i) W[i] = __builtin_bit_cast(bf16x8, src[(size_t)i * 64]);
+    leads_share_xcd(X + 2 * LV * H, NW, k, misc + 1, a);
+    __syncthreads();
+    const int row = lane & 15, b0 = 2 * (lane >> 4);
+    auto put = [&](int i, f32x4 d) {                 // tile i = chain * 6 + unit tile * 3 + gate
+      if (b0 < LV) part[(i * LV + b0) * 16 + row] = mfma_row(d);
+      if (b0 + 1 < LV) part[(i * LV + b0 + 1) * 16 + row] = mfma_row_hi(d);
+    };
+    for (int64_t s = 0; s < a.T; ++s) {
+      if (s > 0) {
+        __syncthreads();                             // h_{s-1} is in the image
+        if (misc[0]) return;
+      }
+      if (fine) {
+        f32x4 acc[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) acc[q] = f32x4{0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < FH; ++i) {
+          const bf16x8 x = afrag_p(img, 2 * i + (wave & 1));
+#pragma unroll
+          for (int q = 0; q < 3; ++q) acc[q] = mfma(x, W[q * FH + i], acc[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q) put((wave & 1) * 6 + (wave >> 1) * 3 + q, acc[q]);
+      } else {
+        f32x4 acc[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) acc[q] = f32x4{0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+          const bf16x8 x = afrag_p(img, wave < 2 ? 2 * i + wave : KT + (wave - 2) * CH + i);
+#pragma unroll
+          for (int q = 0; q < 6; ++q) acc[q] = mfma(x, W[q * CH + i], acc[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 6; ++q) put(wave * 6 + q, acc[q]);
+      }
+      __syncthreads();                               // the products are in
     }
     return;
   }
-#pragma unroll
-  for (int i = 0; i < KT; i += 2) {
-    acc0 = mfma(afrag(img, i), W[i], acc0);
-    if (i + 1 < KT) acc1 = mfma(afrag(img, i + 1), W[i + 1], acc1);
-  }
-#pragma unroll
-  for (int i = 0; i < MK; ++i) {
-    accA = mfma(afrag(img, KT + i), W[KT + i], accA);
-    accB = mfma(afrag(img, KT + MK + i), W[KT + MK + i], accB);
-  }
-}
-
-}  // namespace
-
-template <int KT2>
-__global__ __launch_bounds__(WR_THREADS, 1) void wr_score_kernel(ScoreArgs a) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  unsigned char* img = lds;                          // [KT2] operand image of h
-  float* pre = (float*)(lds + KT2 * WR_FRAG);        // [3][16] this step's R h (+ bias, conditioning) of u, r, e
-  int* misc = (int*)(pre + 48);                      // [0] abort
-  constexpr int NG = WR_THREADS - 192;               // gathering lanes (waves 3-7)
-  constexpr int MW4 = (8 * KT2 + NG - 1) / NG;       // 16-byte groups of h per gathering lane
-  const int k = blockIdx.x, H = a.H, Hh = a.Hh;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  for (int i = tid; i < KT2 * WR_FRAG / 16; i += WR_THREADS) ((uint4*)img)[i] = uint4{0, 0, 0, 0};
-  if (tid == 0) misc[0] = 0;
-  bf16x8 W[KT2];
-  if (wave < 3) {
-    const uint4* src = a.w + ((size_t)(k * 3 + wave) * KT2) * 64 + lane;
-#pragma unroll
-    for (int i = 0; i < KT2; ++i) W[i] = __builtin_bit_cast(bf16x8, src[(size_t)i * 64]);
-  }
-  __syncthreads();
-  for (int i = tid; i < H; i += WR_THREADS) aput(img + (i >> 5) * WR_FRAG, i & 31, a.h_in ? xround(a.h_in[i]) : 0.0f);
-  // gate thread tid < 16: unit u, its I* row, its full-precision state and the last bytes
-  const bool gt = tid < 16;
-  const int u = 16 * k + (tid & 15);
-  const bool fine = u >= Hh;
+  // waves 4-7.  Gate thread r < 32 nv: unit u of vector ub, its I* row, its
+  // full-precision state and last bytes
+  const int r = tid - 256, ub = r >> 5, vb = v0 + (ub < nv ? ub : 0);
+  const bool gt = ub < nv;
+  const int u = 32 * k + (r & 31);
   float cf[3][3];
 #pragma unroll
-  for (int g = 0; g < 3; ++g)
+  for (int q = 0; q < 3; ++q)
 #pragma unroll
-    for (int q = 0; q < 3; ++q) cf[g][q] = gt ? a.Iw[3 * (g * H + u) + q] : 0.0f;
-  float h = gt && a.h_in ? a.h_in[u] : 0.0f;
-  int cp = a.c_in ? a.c_in[0] : 128, fp = a.f_in ? a.f_in[0] : 0;
+    for (int c = 0; c < 3; ++c) cf[q][c] = gt ? a.Iw[3 * (q * H + u) + c] : 0.0f;
+  float h = gt && a.h_in ? a.h_in[(size_t)vb * H + u] : 0.0f;
+  int cp = a.c_in ? a.c_in[vb] : 128, fp = a.f_in ? a.f_in[vb] : 0;
+  // this vector's bias + conditioning of unit u, read once a frame; the frame
+  // changes at step `edge` (the last one stays)
+  const float* cbv = a.cb + (size_t)vb * a.n_cb * 3 * H + u;
+  float cb[3] = {0.0f, 0.0f, 0.0f};
+  int64_t fr = a.t0 / a.frame_len, edge = 0;
+  if (fr >= a.n_cb) fr = a.n_cb - 1;
+  auto frame = [&]() {
+    if (gt)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) cb[q] = cbv[fr * 3 * H + q * H];
+    edge = fr + 1 < a.n_cb ? (fr + 1) * a.frame_len - a.t0 : INT64_MAX;
+    ++fr;
+  };
+  frame();
+  // targets of 64 steps, read here and put into LDS a step later
+  constexpr int TN = (64 * LV + 255) / 256;
+  int tv[TN] = {};
+  auto targets = [&](int64_t s) {
+#pragma unroll
+    for (int m = 0; m < TN; ++m) {
+      const int i = r + 256 * m, b = i % LV;
+      const int64_t n = s + i / LV;
+      if (i < 64 * LV && b < nv && n < a.T) tv[m] = a.target[(size_t)(v0 + b) * a.T + n];
+    }
+  };
+  auto put_targets = [&](int buf) {
+#pragma unroll
+    for (int m = 0; m < TN; ++m)
+      if (r + 256 * m < 64 * LV) tgt[buf][r + 256 * m] = tv[m];
+  };
+  targets(0);
+  put_targets(0);
+  const bool lx = leads_share_xcd(X + 2 * LV * H, NW, k, misc + 1, a) && WR_LOCAL_XCHG;
   __builtin_amdgcn_s_waitcnt(0);   // prologue loads in before the loop (see the persistent heads)
   __syncthreads();
   for (int64_t s = 0; s < a.T; ++s) {
-    if (s > 0) {   // h_{s-1} of every workgroup into the image
-      if (wave >= 3) {   // 4 words (units 4 q .. 4 q + 3) per 16-byte load, each word checked
-        const xw* Y = a.xc + (size_t)((s - 1) & 1) * H;
-        const uint32_t tag = (uint32_t)((s - 1) >> 1) + 1u;
-        const int r = tid - 192;
-        uint32_t pending = 0;
-#pragma unroll
-        for (int m = 0; m < MW4; ++m)
-          if (r + NG * m < H / 4) pending |= 1u << m;
-        WaitBudget wb{wr_clock(), 0};
-        while (pending) {
-          const __amdgpu_buffer_rsrc_t rs = xrsrc(xopaque(Y), (uint32_t)H * 4u);
-          xw4 w[MW4];
-#pragma unroll
-          for (int m = 0; m < MW4; ++m) w[m] = (pending >> m & 1u) ? xpeek4(rs, 16u * (r + NG * m)) : xw4{0, 0, 0, 0};
-#pragma unroll
-          for (int m = 0; m < MW4; ++m)
-            if ((pending >> m & 1u) && xok4(w[m], tag)) {
-              const int i = 4 * (r + NG * m);
-              aput(img + (i >> 5) * WR_FRAG, i & 31, xval(w[m].x));
-              aput(img + (i >> 5) * WR_FRAG, (i & 31) + 1, xval(w[m].y));
-              aput(img + (i >> 5) * WR_FRAG, (i & 31) + 2, xval(w[m].z));
-              aput(img + (i >> 5) * WR_FRAG, (i & 31) + 3, xval(w[m].w));
-              pending &= ~(1u << m);
-            }
-          if (pending && !wait_ok(wb, a.err, a.limit, a.err)) {
-            misc[0] = 1;
-            break;
-          }
-        }
-      }
+    if (s > 0) {   // h_{s-1} of every workgroup and vector into the image
+      __builtin_amdgcn_s_sleep(WR_SCORE_DELAY);
+      if (!gather_y<LV, H, 256, true>(X + __builtin_amdgcn_readfirstlane((int)((s - 1) & 1)) * (LV * H),
+                                      (uint32_t)((s - 1) >> 1) + 1u, img, r, -1, a))
+        misc[0] = 1;
       __syncthreads();
       if (misc[0]) return;
     }
-    const int64_t n = a.t0 + s;
-    if (wave < 3) {   // gate `wave`: rows wave H + 16 k .. + 15 of R h, as the sampling kernel forms them
-      f32x4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0}, accA = {0, 0, 0, 0}, accB = {0, 0, 0, 0};
-      score_products<KT2>(img, W, fine, acc0, acc1, accA, accB);
-      if (lane < 16) {
-        float v = mfma_row(acc0) + mfma_row(acc1);
-        if (wave < 2) v += score_cb(a, n)[wave * H + 16 * k + lane];   // bias + conditioning of u and r
-        pre[wave * 16 + lane] = fine ? xround(v) : xround(v) + xround(mfma_row(accA) + mfma_row(accB));
-      }
-    }
-    __syncthreads();
+    if ((s & 63) == 0) targets(s + 64);
+    if ((s & 63) == 1) put_targets((int)(((s >> 6) + 1) & 1));
+    __syncthreads();                                 // the products are in
+    xw* Y = X + (size_t)((s & 1) * LV + ub) * H + u;
+    const uint32_t tag = (uint32_t)(s >> 1) + 1u;
+    if (!gt && ub < LV) xpub_l(Y, tag, 0.0f, lx);      // a vector not in use: its words are waited for too
     if (gt) {
-      const float v0 = pre[tid], v1 = pre[16 + tid], v2 = pre[32 + tid];
-      const float cbe = score_cb(a, n)[2 * H + u];
-      const int tg = a.target[s], c = tg >> 8;
+      const int ut = (r >> 4) & 1, row = r & 15;
+      auto P = [&](int chain, int q) { return part[((chain * 6 + ut * 3 + q) * LV + ub) * 16 + row]; };
+      float v[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        float x = P(0, q) + P(1, q);
+        if (q < 2) x += cb[q];                       // bias + conditioning of u and r
+        v[q] = fine ? xround(x) : xround(x) + xround(P(2, q) + P(3, q));
+      }
+      const float v0 = v[0], v1 = v[1], v2 = v[2], cbe = cb[2];
+      const int tg = tgt[(s >> 6) & 1][(int)(s & 63) * LV + ub], c = tg >> 8;
       const float x0 = fscale(cp), x1 = fscale(fp);
+      float uu, rr, e;
       if (!fine) {   // the sampling head's coarse terms, then its gates with f_{t-1}
         const float cu = v0 + cf[0][0] * x0, cr = v1 + cf[1][0] * x0, cie = cf[2][0] * x0;
-        const float uu = fsig(__builtin_fmaf(cf[0][1], x1, cu)), rr = fsig(__builtin_fmaf(cf[1][1], x1, cr));
-        const float e = ftanh(__builtin_fmaf(rr, v2, __builtin_fmaf(cf[2][1], x1, cie) + cbe));
-        h = __builtin_fmaf(uu, h, (1.0f - uu) * e);
-        a.traj_c[s * Hh + u] = h;
+        uu = fsig(__builtin_fmaf(cf[0][1], x1, cu)), rr = fsig(__builtin_fmaf(cf[1][1], x1, cr));
+        e = ftanh(__builtin_fmaf(rr, v2, __builtin_fmaf(cf[2][1], x1, cie) + cbe));
       } else {       // its fine terms, then its gates with c_t
         const float fu = v0 + __builtin_fmaf(cf[0][1], x1, cf[0][0] * x0);
         const float fr = v1 + __builtin_fmaf(cf[1][1], x1, cf[1][0] * x0);
         const float fie = __builtin_fmaf(cf[2][1], x1, cf[2][0] * x0);
         const float x2 = fscale(c);
-        const float uu = fsig(__builtin_fmaf(cf[0][2], x2, fu)), rr = fsig(__builtin_fmaf(cf[1][2], x2, fr));
-        const float e = ftanh(__builtin_fmaf(rr, v2, __builtin_fmaf(cf[2][2], x2, fie) + cbe));
-        h = __builtin_fmaf(uu, h, (1.0f - uu) * e);
-        a.traj_f[s * Hh + (u - Hh)] = h;
+        uu = fsig(__builtin_fmaf(cf[0][2], x2, fu)), rr = fsig(__builtin_fmaf(cf[1][2], x2, fr));
+        e = ftanh(__builtin_fmaf(rr, v2, __builtin_fmaf(cf[2][2], x2, fie) + cbe));
       }
-      xpub(a.xc + (size_t)(s & 1) * H + u, (uint32_t)(s >> 1) + 1u, h);
+      h = __builtin_fmaf(uu, h, (1.0f - uu) * e);
+      xpub_l(Y, tag, h, lx);
+      if (fine) a.traj_f[((size_t)vb * a.T + s) * Hh + (u - Hh)] = h;
+      else a.traj_c[((size_t)vb * a.T + s) * Hh + u] = h;
       cp = c;
       fp = tg & 255;
+      if (s + 1 == edge) frame();
     }
   }
-  if (gt && a.h_out) a.h_out[u] = h;
-  if (k == 0 && tid == 0) {
-    if (a.c_out) a.c_out[0] = (uint8_t)cp;
-    if (a.f_out) a.f_out[0] = (uint8_t)fp;
-  }
-}
-
-// Up to 8 utterances at once (a.nv of them).  Vector b sits in rows 2b and
-// 2b + 1 of the operand image, so the products cost what one utterance's do,
-// and lane l of a gate wave's result holds output row l % 16 of vectors
-// 2 (l / 16) and 2 (l / 16) + 1.  Thread 16 b + i (< 16 nv) finishes unit
-// 16 k + i of vector b with wr_score_kernel's arithmetic (vector 0's
-// products come from the same lanes and elements of the same products), so
-// every utterance's state and logits are those of scoring it alone, bit for
-// bit.  Exchange: h_s of vector b at xc[(s mod 2) 8H + b H + u], the tags as
-// above; the gathering lanes read nv H words per step.
-template <int KT2>
-__global__ __launch_bounds__(WR_THREADS, 1) void wr_score_multi(ScoreArgs a) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  constexpr int H = 32 * KT2, LV = 8;
-  unsigned char* img = lds;                          // [KT2] operand image of h (vector b: rows 2b, 2b + 1)
-  float* pre = (float*)(lds + KT2 * WR_FRAG);        // [3][LV][16] this step's R h (+ bias, conditioning)
-  int* misc = (int*)(pre + 3 * LV * 16);             // [0] abort
-  constexpr int NG = WR_THREADS - 192;               // gathering lanes (waves 3-7)
-  constexpr int MW4 = (LV * H / 4 + NG - 1) / NG;    // 16-byte groups per gathering lane at most
-  static_assert(MW4 <= 32, "pending mask");
-  const int k = blockIdx.x, Hh = a.Hh, nv = a.nv;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  for (int i = tid; i < KT2 * WR_FRAG / 16; i += WR_THREADS) ((uint4*)img)[i] = uint4{0, 0, 0, 0};
-  if (tid == 0) misc[0] = 0;
-  bf16x8 W[KT2];
-  if (wave < 3) {
-    const uint4* src = a.w + ((size_t)(k * 3 + wave) * KT2) * 64 + lane;
-#pragma unroll
-    for (int i = 0; i < KT2; ++i) W[i] = __builtin_bit_cast(bf16x8, src[(size_t)i * 64]);
-  }
-  __syncthreads();
-  for (int i = tid; i < nv * H; i += WR_THREADS) {
-    const int b = i / H, col = i % H;
-    aput(img + (col >> 5) * WR_FRAG, col & 31, a.h_in ? xround(a.h_in[i]) : 0.0f, b);
-  }
-  // gate thread tid < 16 nv: unit u of vector ub, its I* row, its state and last bytes
-  const int ub = tid >> 4;
-  const bool gt = ub < nv;
-  const int u = 16 * k + (tid & 15);
-  const bool fine = u >= Hh;
-  float cf[3][3];
-#pragma unroll
-  for (int g = 0; g < 3; ++g)
-#pragma unroll
-    for (int q = 0; q < 3; ++q) cf[g][q] = gt ? a.Iw[3 * (g * H + u) + q] : 0.0f;
-  float h = gt && a.h_in ? a.h_in[(size_t)ub * H + u] : 0.0f;
-  int cp = gt && a.c_in ? a.c_in[ub] : 128, fp = gt && a.f_in ? a.f_in[ub] : 0;
-  const float* cbv = a.cb + (size_t)(gt ? ub : 0) * a.n_cb * 3 * H;   // this vector's table
-  const uint16_t* tgv = a.target + (size_t)(gt ? ub : 0) * a.T;
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  for (int64_t s = 0; s < a.T; ++s) {
-    if (s > 0) {   // h_{s-1} of every workgroup and vector into the image
-      if (wave >= 3) {   // 4 words of one vector per 16-byte load, each word checked
-        const xw* Y = a.xc + (size_t)((s - 1) & 1) * LV * H;
-        const uint32_t tag = (uint32_t)((s - 1) >> 1) + 1u;
-        const int r = tid - 192;
-        uint32_t pending = 0;
-#pragma unroll
-        for (int m = 0; m < MW4; ++m)
-          if (r + NG * m < nv * H / 4) pending |= 1u << m;
-        WaitBudget wb{wr_clock(), 0};
-        while (pending) {
-          const __amdgpu_buffer_rsrc_t rs = xrsrc(xopaque(Y), (uint32_t)(LV * H) * 4u);
-          xw4 w[MW4];
-#pragma unroll
-          for (int m = 0; m < MW4; ++m) w[m] = (pending >> m & 1u) ? xpeek4(rs, 16u * (r + NG * m)) : xw4{0, 0, 0, 0};
-#pragma unroll
-          for (int m = 0; m < MW4; ++m)
-            if ((pending >> m & 1u) && xok4(w[m], tag)) {
-              const int i = 4 * (r + NG * m), b = i / H, col = i % H;
-              unsigned char* f = img + (col >> 5) * WR_FRAG;
-              aput(f, col & 31, xval(w[m].x), b);
-              aput(f, (col & 31) + 1, xval(w[m].y), b);
-              aput(f, (col & 31) + 2, xval(w[m].z), b);
-              aput(f, (col & 31) + 3, xval(w[m].w), b);
-              pending &= ~(1u << m);
-            }
-          if (pending && !wait_ok(wb, a.err, a.limit, a.err)) {
-            misc[0] = 1;
-            break;
-          }
-        }
-      }
-      __syncthreads();
-      if (misc[0]) return;
-    }
-    const int64_t n = a.t0 + s;
-    int64_t fr = n / a.frame_len;
-    if (fr >= a.n_cb) fr = a.n_cb - 1;
-    if (wave < 3) {   // gate `wave`: rows wave H + 16 k .. + 15 of R h for every vector
-      f32x4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0}, accA = {0, 0, 0, 0}, accB = {0, 0, 0, 0};
-      score_products<KT2>(img, W, fine, acc0, acc1, accA, accB);
-      const int b0 = 2 * (lane >> 4), row = lane & 15;
-      if (b0 < nv) {
-        float v0 = mfma_row(acc0) + mfma_row(acc1), v1 = mfma_row_hi(acc0) + mfma_row_hi(acc1);
-        if (wave < 2) {   // bias + conditioning of u and r
-          v0 += a.cb[((size_t)b0 * a.n_cb + fr) * 3 * H + wave * H + 16 * k + row];
-          if (b0 + 1 < nv) v1 += a.cb[((size_t)(b0 + 1) * a.n_cb + fr) * 3 * H + wave * H + 16 * k + row];
-        }
-        const float f0 = fine ? 0.0f : xround(mfma_row(accA) + mfma_row(accB));
-        const float f1 = fine ? 0.0f : xround(mfma_row_hi(accA) + mfma_row_hi(accB));
-        pre[(wave * LV + b0) * 16 + row] = fine ? xround(v0) : xround(v0) + f0;
-        if (b0 + 1 < nv) pre[(wave * LV + b0 + 1) * 16 + row] = fine ? xround(v1) : xround(v1) + f1;
-      }
-    }
-    __syncthreads();
-    if (gt) {
-      const int ui = tid & 15;
-      const float v0 = pre[ub * 16 + ui], v1 = pre[(LV + ub) * 16 + ui], v2 = pre[(2 * LV + ub) * 16 + ui];
-      const float cbe = cbv[fr * 3 * H + 2 * H + u];
-      const int tg = tgv[s], c = tg >> 8;
-      const float x0 = fscale(cp), x1 = fscale(fp);
-      if (!fine) {
-        const float cu = v0 + cf[0][0] * x0, cr = v1 + cf[1][0] * x0, cie = cf[2][0] * x0;
-        const float uu = fsig(__builtin_fmaf(cf[0][1], x1, cu)), rr = fsig(__builtin_fmaf(cf[1][1], x1, cr));
-        const float e = ftanh(__builtin_fmaf(rr, v2, __builtin_fmaf(cf[2][1], x1, cie) + cbe));
-        h = __builtin_fmaf(uu, h, (1.0f - uu) * e);
-        a.traj_c[((size_t)ub * a.T + s) * Hh + u] = h;
-      } else {
-        const float fu = v0 + __builtin_fmaf(cf[0][1], x1, cf[0][0] * x0);
-        const float fr2 = v1 + __builtin_fmaf(cf[1][1], x1, cf[1][0] * x0);
-        const float fie = __builtin_fmaf(cf[2][1], x1, cf[2][0] * x0);
-        const float x2 = fscale(c);
-        const float uu = fsig(__builtin_fmaf(cf[0][2], x2, fu)), rr = fsig(__builtin_fmaf(cf[1][2], x2, fr2));
-        const float e = ftanh(__builtin_fmaf(rr, v2, __builtin_fmaf(cf[2][2], x2, fie) + cbe));
-        h = __builtin_fmaf(uu, h, (1.0f - uu) * e);
-        a.traj_f[((size_t)ub * a.T + s) * Hh + (u - Hh)] = h;
-      }
-      xpub(a.xc + (size_t)(s & 1) * LV * H + (size_t)ub * H + u, (uint32_t)(s >> 1) + 1u, h);
-      cp = c;
-      fp = tg & 255;
-    }
-  }
-  if (gt && a.h_out) a.h_out[(size_t)ub * H + u] = h;
-  if (k == 0 && gt && (tid & 15) == 0) {
-    if (a.c_out) a.c_out[ub] = (uint8_t)cp;
-    if (a.f_out) a.f_out[ub] = (uint8_t)fp;
+  if (gt && a.h_out) a.h_out[(size_t)vb * H + u] = h;
+  if (k == 0 && gt && (r & 31) == 0) {
+    if (a.c_out) a.c_out[vb] = (uint8_t)cp;
+    if (a.f_out) a.f_out[vb] = (uint8_t)fp;
   }
 }
 
@@ -338,24 +233,18 @@ extern "C" __global__ void wr_score_nll(const float* zc, const float* zf, const 
   if (l == 0) nll[row] = r[0] + r[1];
 }
 
-const void* wr_score_kernel_ptr(int KT2) {
+template <int LV>
+static const void* score_ptr(int KT2) {
   switch (KT2) {
-    case 4: return (const void*)wr_score_kernel<4>;
-    case 8: return (const void*)wr_score_kernel<8>;
-    case 12: return (const void*)wr_score_kernel<12>;
-    case 16: return (const void*)wr_score_kernel<16>;
-    case 28: return (const void*)wr_score_kernel<28>;
+    case 4: return (const void*)wr_score_kernel<4, LV>;
+    case 8: return (const void*)wr_score_kernel<8, LV>;
+    case 12: return (const void*)wr_score_kernel<12, LV>;
+    case 16: return (const void*)wr_score_kernel<16, LV>;
+    case 28: return (const void*)wr_score_kernel<28, LV>;
     default: return nullptr;
   }
 }
-const void* wr_score_multi_ptr(int KT2) {
-  switch (KT2) {
-    case 4: return (const void*)wr_score_multi<4>;
-    case 8: return (const void*)wr_score_multi<8>;
-    case 12: return (const void*)wr_score_multi<12>;
-    case 16: return (const void*)wr_score_multi<16>;
-    case 28: return (const void*)wr_score_multi<28>;
-    default: return nullptr;
-  }
+const void* wr_score_kernel_ptr(int KT2, int LV) {
+  return LV == 1 ? score_ptr<1>(KT2) : LV == 2 ? score_ptr<2>(KT2) : LV == 4 ? score_ptr<4>(KT2) : score_ptr<8>(KT2);
 }
 const void* wr_score_nll_ptr() { return (const void*)wr_score_nll; }
