@@ -206,6 +206,21 @@ const void* wr_persist_kernel_ptr(int KH);   // null if no instantiation for KH
 const void* wr_score_kernel_ptr(int KT2, int LV);   // teacher-forced recurrence for H = 32 KT2, LV utterances a group; null if none
 const void* wr_score_nll_ptr();
 const void* wr_sparse_kernel_ptr(int KH, int GU);   // null if no instantiation
+// Prologue of a call: table cb of each stream (n_streams of them, cb_stride
+// floats apart), frames f0 .. f0 + nf - 1, and its exchange words zeroed
+// (n_words 64-bit words, x_stride 32-bit words apart; null: none).
+struct CondArgs {
+  const float* Wct;         // [Dc][rows] conditioning projection, or null (Dc = 0: the bias alone)
+  const float* bias;        // [rows]
+  const float* feat;        // [n_streams][n_frames][Dc]
+  int Dc, rows;
+  int64_t n_frames, f0, nf;
+  float* cb;
+  int64_t cb_stride;
+  xw* words;
+  int64_t n_words, x_stride;
+};
+#define WR_COND_FRAMES 8    // frames per workgroup of wr_cond_kernel
 const void* wr_cond_kernel_ptr();
 const void* wr_batch_kernel_ptr(int KH, bool ctx, int L, bool lag);   // null if no instantiation (KH, L vectors
                                                                       // per group, lag: a future-horizon schedule)

@@ -16,7 +16,7 @@
 // What bounds a step is the chain of exchanges between workgroups (gate words,
 // y slices at L = 8, partial logits twice, and for subscale the drawn samples),
 // so a group sits whole on one XCD, and when it finds itself there
-// (leads_share_xcd) every word but the drawn samples, which other groups read,
+// (group_shares_xcd) every word but the drawn samples, which other groups read,
 // is published into that XCD's L2.  H = 896, us a step, with the units spread
 // over the XCDs and one owner drawing each vector, and now: 64 utterances
 // 10.3 -> 7.2, 14 utterances 7.0 -> 5.8, subscale 16 with F = 4 10.0 -> 7.7.
@@ -502,7 +502,7 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
     cfr = n / a.frame_len;
     cin = (int)(n - cfr * a.frame_len);
   }
-  if (WR_LOCAL_XCHG) lx = leads_share_xcd(X + P.x_xcc, P.NH + P.NU, j, misc + 1, a);
+  if (WR_LOCAL_XCHG) lx = group_shares_xcd(X + P.x_xcc, P.NH + P.NU, j, misc + 1, a);
   if (SLICE) slice_probe();
   else if (gate) all_probe();
 
@@ -879,7 +879,7 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
     if (!gather_y<L, 64 * KH, WR_THREADS, !FL>(Y, tag, img + kt0 * WR_FRAGP, tid, -1, a)) misc[0] = 1;
     __syncthreads();
   };
-  if (WR_LOCAL_XCHG) lx = leads_share_xcd(X + P.x_xcc, P.NH + P.NU, P.NH + k, misc + 1, a);
+  if (WR_LOCAL_XCHG) lx = group_shares_xcd(X + P.x_xcc, P.NH + P.NU, P.NH + k, misc + 1, a);
   phase_c();
   phase_f();
   // the first step's context: row 0 of the table; for a resumed window

@@ -163,6 +163,13 @@ __device__ __forceinline__ T* xopaque(T* p) {
   asm volatile("" : "+s"(p));
   return p;
 }
+// The same for a base that every lane holds but the compiler keeps per lane.
+template <class T>
+__device__ __forceinline__ T* xopaque_u(T* p) {
+  const uint64_t v = (uint64_t)p;
+  return xopaque((T*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
+                      (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32));
+}
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t xrsrc(const xw* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);   // raw 32-bit data (gfx9)
 }

@@ -51,8 +51,53 @@ float bf2f(uint16_t b) {
 
 enum Path { PATH_SMALL = 0, PATH_PERSIST = 1, PATH_BATCHED = 2 };
 constexpr int PATH_SPARSE_ID = 3, PATH_CONCURRENT_ID = 4, PATH_FUSED_ID = 5;   // wavernn_model_path's ids of the variants
-#define WR_FAN 4   // concurrent batch-1 launches: the caller's stream and 3 internal ones (HIP's default
-                   // of 4 hardware queues gives each its own)
+
+#define WR_FAN 4   // batch-1 grids side by side: the caller's stream and 3 internal ones (HIP's default of 4
+                   // hardware queues gives each its own)
+#define WR_MAX_DEVICES 64
+
+// The internal streams of a device, shared by its models: with 3 for each
+// model, the streams of a program's later models fell on the caller's hardware
+// queue, and one of the 4 grids ran after another (4 utterances x 9,613 among
+// three models: 49.2 ms a call, 37.3 with shared streams; one model: 37.2).
+// Created with the first model that uses them (default priority), destroyed
+// with the last one.
+struct FanStreams {
+  hipStream_t st[WR_FAN - 1] = {};
+  int refs = 0;
+  static std::mutex& mu() {
+    static std::mutex m;
+    return m;
+  }
+  static FanStreams& of(int dev) {
+    static FanStreams all[WR_MAX_DEVICES];
+    return all[dev];
+  }
+  static const hipStream_t* acquire(int dev) {   // null: no stream could be created
+    if (dev < 0 || dev >= WR_MAX_DEVICES) return nullptr;
+    std::lock_guard<std::mutex> lock(mu());
+    FanStreams& f = of(dev);
+    if (!f.refs)
+      for (hipStream_t& s : f.st)
+        if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) {
+          f.clear();
+          return nullptr;
+        }
+    ++f.refs;
+    return f.st;
+  }
+  static void release(int dev) {
+    std::lock_guard<std::mutex> lock(mu());
+    FanStreams& f = of(dev);
+    if (--f.refs == 0) f.clear();
+  }
+  void clear() {
+    for (hipStream_t& s : st) {
+      if (s) (void)hipStreamDestroy(s);
+      s = nullptr;
+    }
+  }
+};
 
 const u64 kWaitTicks = 200000000ull;  // 2 s of the 100 MHz clock per wait
 
@@ -66,7 +111,7 @@ struct wavernn_model {
   unsigned* d_err = nullptr;
   // small path
   float* d_image = nullptr;
-  float* d_Wc = nullptr;
+  float* d_Wc = nullptr;             // [3H][Dc] (small path), [Dc][3H] (the others)
   // persistent path
   PersistPlan plan;
   const void* pk = nullptr;          // kernel instantiation for the plan
@@ -97,14 +142,13 @@ struct wavernn_model {
   int64_t so_cap = 0;                       // rows of d_so and d_sz (at most one chunk of the output layers)
   u64* trace = nullptr;
   int64_t trace_steps = 0;
-  // concurrent batch-1 launches: a few utterances, each on its own persistent
-  // grid and its own internal stream, all grids co-resident at once
+  // a few utterances side by side, each on its own batch-1 grid and stream, all grids co-resident at once
   int nfan = 0;                      // most utterances served this way (0: none)
-  hipStream_t fan_st[WR_FAN - 1] = {};  // launches 1 .. (launch 0 runs on the caller's stream)
+  const hipStream_t* fan_st = nullptr;   // streams of grids 1 .. (FanStreams); grid 0 runs on the caller's stream
   hipEvent_t fan_fork = nullptr, fan_join[WR_FAN - 1] = {};
-  xw* d_fxc[WR_FAN] = {};            // exchange words of launch i
-  float* d_fcb[WR_FAN] = {};         // [fcb_cap][3H] bias + conditioning of launch i
-  int64_t fcb_cap = 0;
+  xw* d_fxc = nullptr;               // exchange words [nfan][x_words]
+  float* d_fcb = nullptr;            // [nfan][frames][3H] bias + conditioning
+  int64_t fcb_cap = 0;               // frames
   // conditioning CNN of a subscale model (Sec. 4.1): weight fragments of the
   // input layer, then per layer the convolution and the projection, then the
   // output layer, in one buffer; biases likewise; activations grown on demand
@@ -152,12 +196,10 @@ struct wavernn_model {
     return WAVERNN_OK;
   }
   ~wavernn_model() {
-    for (int i = 0; i < WR_FAN - 1; ++i) {
-      if (fan_st[i]) (void)hipStreamSynchronize(fan_st[i]);
-      if (fan_st[i]) (void)hipStreamDestroy(fan_st[i]);
-      if (fan_join[i]) (void)hipEventDestroy(fan_join[i]);
-    }
+    for (hipEvent_t e : fan_join)
+      if (e) (void)hipEventDestroy(e);
     if (fan_fork) (void)hipEventDestroy(fan_fork);
+    if (fan_st) FanStreams::release(device);
     for (void* q : allocs) (void)hipFree(q);
   }
 };
@@ -368,7 +410,8 @@ wavernn_status upload_common(wavernn_model* m, const wavernn_weights* w) {
   if ((s = m->upload(&m->d_b4, b4.data(), 256 * 4)) != WAVERNN_OK) return s;
   if (c.cond_dim > 0) {
     std::vector<float> wc((size_t)3 * H * c.cond_dim);
-    for (size_t i = 0; i < wc.size(); ++i) wc[i] = rd(w->W_cond[i]);
+    for (int row = 0; row < 3 * H; ++row)            // transposed (wr_cond_kernel)
+      for (int q = 0; q < c.cond_dim; ++q) wc[(size_t)q * 3 * H + row] = rd(w->W_cond[(size_t)row * c.cond_dim + q]);
     if ((s = m->upload(&m->d_Wc, wc.data(), wc.size() * 4)) != WAVERNN_OK) return s;
   }
   m->cb_cap = c.cond_dim > 0 ? 1024 : 1;
@@ -391,17 +434,16 @@ wavernn_status check_coresident(wavernn_model* m, const void* k, int grid, int l
 }
 
 
-// Launch s of n persistent grids side by side: heads and mirrors on XCD
-// 8 s / n, units spread over the XCDs.
+// Grid s of n batch-1 grids side by side: heads and mirrors on XCD 8 s / n,
+// units spread over the XCDs.
 PersistPlan fan_plan(const wavernn_model* m, int s, int n) {
   PersistPlan P = m->plan;
   wr_place(&P, 8 * s / n, 255);
   return P;
 }
 
-// Concurrent batch-1 launches for up to WR_FAN utterances, when that many
-// persistent grids fit the device together: internal streams (default
-// priority), fork / join events, and per-launch exchange words.
+// Up to WR_FAN utterances side by side, when that many batch-1 grids fit the
+// device together.
 wavernn_status build_fanout(wavernn_model* m) {
   const PersistPlan& P = m->plan;
   int per_cu = 0;
@@ -424,15 +466,11 @@ wavernn_status build_fanout(wavernn_model* m) {
     if (fits) break;
   }
   if (n < 2) return WAVERNN_OK;
+  wavernn_status s = m->alloc(&m->d_fxc, (size_t)n * P.x_words * 4);
+  if (s != WAVERNN_OK) return s;
   HIPOK(hipEventCreateWithFlags(&m->fan_fork, hipEventDisableTiming));
-  for (int i = 0; i < n; ++i) {
-    if (i + 1 < n) {   // launch 0 runs on the caller's stream
-      HIPOK(hipStreamCreateWithFlags(&m->fan_st[i], hipStreamNonBlocking));
-      HIPOK(hipEventCreateWithFlags(&m->fan_join[i], hipEventDisableTiming));
-    }
-    wavernn_status s = m->alloc(&m->d_fxc[i], (size_t)(P.x_words + 1) / 2 * 8);
-    if (s != WAVERNN_OK) return s;
-  }
+  for (int i = 0; i + 1 < n; ++i) HIPOK(hipEventCreateWithFlags(&m->fan_join[i], hipEventDisableTiming));
+  if (!(m->fan_st = FanStreams::acquire(m->device))) return fail(WAVERNN_E_HIP, "no internal streams");
   m->nfan = n;
   return WAVERNN_OK;
 }
@@ -559,7 +597,8 @@ wavernn_status build_fused(wavernn_model* m, const wavernn_weights* w) {
   m->d_b4 = m->d_b2 + 64;
   if (c.cond_dim > 0) {
     std::vector<float> wc((size_t)3 * H * c.cond_dim);
-    for (size_t i = 0; i < wc.size(); ++i) wc[i] = rd(w->W_cond[i]);
+    for (int row = 0; row < 3 * H; ++row)            // transposed (wr_cond_kernel)
+      for (int q = 0; q < c.cond_dim; ++q) wc[(size_t)q * 3 * H + row] = rd(w->W_cond[(size_t)row * c.cond_dim + q]);
     if ((s = m->upload(&m->d_Wc, wc.data(), wc.size() * 4)) != WAVERNN_OK) return s;
   }
   m->cb_cap = c.cond_dim > 0 ? 1024 : 1;
@@ -1105,18 +1144,31 @@ wavernn_status run_cnn_stream(wavernn_model* m, int U, const uint16_t* seq, int6
   return WAVERNN_OK;
 }
 
-// Bias + conditioning table cb[s][f][3H] for n_streams streams of n_frames frames.
-wavernn_status launch_cond(const wavernn_model* m, const float* feat, int64_t n_frames, int n_streams, float* cb,
+// The bias + conditioning tables of n_streams streams (cb_stride floats apart,
+// 0: n_frames rows) for frames f0 .. f1 of n_frames, and their exchange words
+// (n_words each, x_stride apart) zeroed; words null: none.
+wavernn_status launch_cond(const wavernn_model* m, const float* feat, int64_t n_frames, int64_t f0, int64_t f1,
+                           int n_streams, float* cb, int64_t cb_stride, xw* words, int64_t n_words, int64_t x_stride,
                            hipStream_t st) {
-  const float* Wc = m->d_Wc;
-  const float* bias = m->d_bias;
-  int dc = m->cfg.cond_dim;
-  int rows = 3 * m->cfg.hidden;
-  int64_t nf = n_frames;
-  int ns = n_streams;
-  void* args[] = {&Wc, &bias, &feat, &dc, &rows, &nf, &ns, &cb};
-  const int64_t n = (int64_t)n_streams * n_frames * rows;
-  HIPOK(hipLaunchKernel(wr_cond_kernel_ptr(), dim3((unsigned)((n + 255) / 256)), dim3(256), args, 0, st));
+  CondArgs a;
+  memset(&a, 0, sizeof a);
+  a.Wct = m->d_Wc;
+  a.bias = m->d_bias;
+  a.feat = feat;
+  a.Dc = m->cfg.cond_dim;
+  a.rows = 3 * m->cfg.hidden;
+  a.n_frames = n_frames;
+  a.f0 = std::max<int64_t>(0, std::min(f0, n_frames - 1));
+  a.nf = std::min(f1, n_frames - 1) - a.f0 + 1;
+  a.cb = cb;
+  a.cb_stride = cb_stride ? cb_stride : n_frames * a.rows;
+  a.words = words;
+  a.n_words = (n_words + 1) / 2;
+  a.x_stride = x_stride;
+  void* args[] = {&a};
+  const dim3 grid((unsigned)((a.rows + 255) / 256), (unsigned)((a.nf + WR_COND_FRAMES - 1) / WR_COND_FRAMES),
+                  (unsigned)n_streams);
+  HIPOK(hipLaunchKernel(wr_cond_kernel_ptr(), grid, dim3(256), args, (size_t)a.Dc * WR_COND_FRAMES * 4, st));
   return WAVERNN_OK;
 }
 
@@ -1150,6 +1202,14 @@ struct RunIO {
   int64_t step0 = 0;             // subscale: the schedule steps [step0, step0 + n_steps) of the call run
   int64_t n_steps = -1;          // (-1: the whole schedule, a wavernn_sample call)
 };
+
+// First and last conditioning frame a call reads.
+inline int64_t first_frame(const wavernn_model* m, const RunIO& io) {
+  return m->cfg.cond_dim > 0 && io.init ? io.init->t0 / m->cfg.frame_len : 0;
+}
+inline int64_t last_frame(const wavernn_model* m, const RunIO& io) {
+  return m->cfg.cond_dim > 0 ? ((io.init ? io.init->t0 : 0) + io.T - 1) / m->cfg.frame_len : 0;
+}
 
 inline size_t rup256(size_t n) { return (n + 255) / 256 * 256; }
 
@@ -1216,28 +1276,18 @@ wavernn_status run_small(wavernn_model* m, const RunIO& io) {
   return WAVERNN_OK;
 }
 
-// One persistent launch for utterance s of the call, with exchange words xc
-// and bias + conditioning table cb, on stream st.  A launch that runs alone
-// (fan = 0) takes the tuned placement, one of fan side by side the placement
-// of fan_plan.
+// The placement of a launch that runs alone (wavernn_tune).
 PersistPlan solo_plan(const wavernn_model* m) {
   PersistPlan P = m->plan;
   wr_place(&P, m->solo_hx, m->solo_uxm);
   return P;
 }
 
-wavernn_status launch_persist_one(wavernn_model* m, const RunIO& io, int s, xw* xc, float* cb, int64_t n_cb,
-                                  hipStream_t st, int fan) {
-  const PersistPlan P = fan ? fan_plan(m, s, fan) : solo_plan(m);
+// The arguments of utterance s on placement P with exchange words xc and table cb.
+PersistArgs persist_args(const wavernn_model* m, const RunIO& io, int s, const PersistPlan& P, xw* xc, const float* cb,
+                         int64_t n_cb) {
   const int H = P.H, Dc = m->cfg.cond_dim;
   const int frame_len = m->cfg.frame_len > 0 ? m->cfg.frame_len : 1;
-  {
-    const float* feat = io.cond ? io.cond + (size_t)s * io.n_frames * Dc : nullptr;
-    wavernn_status c = launch_cond(m, feat, n_cb, 1, cb, st);
-    if (c != WAVERNN_OK) return c;
-  }
-  wavernn_status stt = launch_fill(xc, P.x_words, st);
-  if (stt != WAVERNN_OK) return stt;
   PersistArgs a;
   memset(&a, 0, sizeof a);
   a.P = P;
@@ -1284,11 +1334,34 @@ wavernn_status launch_persist_one(wavernn_model* m, const RunIO& io, int s, xw* 
     a.trace = m->trace;
     a.trace_steps = m->trace ? m->trace_steps : 0;
   }
-  void* args[] = {&a};
-  // An ordinary launch: create() checked that the whole grid fits on the
-  // device at once, and every cross-workgroup wait is bounded, so a grid
-  // that did not become co-resident ends with an error, never a hang.
-  HIPOK(hipLaunchKernel(m->pk, dim3(P.grid), dim3(WR_THREADS), args, P.lds, st));
+  return a;
+}
+
+// Utterances s .. s + n - 1 of the call, a persistent launch each, with
+// exchange words xc and bias + conditioning tables cb at the given strides.
+// One alone uses the tuned placement; several run side by side on the caller's
+// stream and the internal ones, forked from and joined back into it, at the
+// placements of fan_plan.
+wavernn_status launch_persist(wavernn_model* m, const RunIO& io, int s, int n, xw* xc, int64_t x_stride, float* cb,
+                              int64_t cb_stride, int64_t n_cb) {
+  const float* feat = io.cond ? io.cond + (size_t)s * io.n_frames * m->cfg.cond_dim : nullptr;
+  wavernn_status c = launch_cond(m, feat, n_cb, first_frame(m, io), last_frame(m, io), n, cb, cb_stride, xc,
+                                 m->plan.x_words, x_stride, io.st);
+  if (c != WAVERNN_OK) return c;
+  if (n > 1) HIPOK(hipEventRecord(m->fan_fork, io.st));
+  for (int i = n - 1; i >= 0; --i) {   // the caller's stream last
+    const PersistPlan P = n > 1 ? fan_plan(m, i, n) : solo_plan(m);
+    PersistArgs a = persist_args(m, io, s + i, P, xc + i * x_stride, cb + i * cb_stride, n_cb);
+    void* args[] = {&a};
+    const hipStream_t st = i ? m->fan_st[i - 1] : io.st;
+    if (i) HIPOK(hipStreamWaitEvent(st, m->fan_fork, 0));
+    // An ordinary launch: create() checked that the whole grid fits on the
+    // device at once, and every cross-workgroup wait is bounded, so a grid
+    // that did not become co-resident ends with an error, never a hang.
+    HIPOK(hipLaunchKernel(m->pk, dim3(P.grid), dim3(WR_THREADS), args, P.lds, st));
+    if (i) HIPOK(hipEventRecord(m->fan_join[i - 1], st));
+  }
+  for (int i = 1; i < n; ++i) HIPOK(hipStreamWaitEvent(io.st, m->fan_join[i - 1], 0));
   return WAVERNN_OK;
 }
 
@@ -1305,21 +1378,40 @@ wavernn_status grow_cb(wavernn_model* m, float** cb, int64_t* cap, int64_t n_cb)
   return WAVERNN_OK;
 }
 
-// Several utterances one after another on the caller's stream.
+// Utterances on batch-1 grids: up to nfan side by side (a dense or fused model
+// made for several; co-residency checked at create), then the next.  At batch 4
+// about four times the batch-1 rate, where the batched kernel, which shares one
+// grid among the utterances, gives under three.
 wavernn_status run_persist(wavernn_model* m, const RunIO& io) {
   const int64_t n_cb = m->cfg.cond_dim > 0 ? io.n_frames : 1;
-  if (io.ws) {   // every launch of the call reuses one region of the workspace, in stream order
-    xw* xc;
-    float* cb;
-    wavernn_status st = carve_ws(io, 1, m->plan.x_words, (size_t)n_cb * 3 * m->plan.H, &xc, &cb);
-    for (int s = 0; s < io.S && st == WAVERNN_OK; ++s) st = launch_persist_one(m, io, s, xc, cb, n_cb, io.st, 0);
-    return st;
+  int per = std::min(std::max(m->nfan, 1), io.S);
+  xw* xc[WR_FAN] = {m->d_xc};
+  float* cb[WR_FAN] = {};
+  int64_t xs = m->plan.x_words, cs = n_cb * 3 * m->plan.H;
+  wavernn_status st;
+  if (io.ws) {   // every launch of the call reuses the same region of the workspace, in stream order
+    // a call of at most nfan utterances of a dense model needs a region each; any other takes what fits
+    if (m->fused || io.S > m->nfan)
+      while (per > 1 && (size_t)per * (rup256((size_t)m->plan.x_words * 4) + rup256((size_t)cs * 4)) > io.ws_cap) --per;
+    if ((st = carve_ws(io, per, m->plan.x_words, (size_t)cs, xc, cb)) != WAVERNN_OK) return st;
+    if (per > 1) xs = xc[1] - xc[0], cs = cb[1] - cb[0];
+  } else if (per > 1) {
+    if (n_cb > m->fcb_cap) {
+      HIPOK(hipStreamSynchronize(io.st));
+      float* p = nullptr;
+      if ((st = m->alloc(&p, (size_t)m->nfan * cs * 4)) != WAVERNN_OK) return st;
+      m->d_fcb = p;
+      m->fcb_cap = n_cb;
+    }
+    xc[0] = m->d_fxc;
+    cb[0] = m->d_fcb;
+  } else {
+    if (n_cb > m->cb_cap) HIPOK(hipStreamSynchronize(io.st));
+    if ((st = grow_cb(m, &m->d_cb, &m->cb_cap, n_cb)) != WAVERNN_OK) return st;
+    cb[0] = m->d_cb;
   }
-  if (n_cb > m->cb_cap) HIPOK(hipStreamSynchronize(io.st));
-  wavernn_status st = grow_cb(m, &m->d_cb, &m->cb_cap, n_cb);
-  if (st != WAVERNN_OK) return st;
-  for (int s = 0; s < io.S; ++s)
-    if ((st = launch_persist_one(m, io, s, m->d_xc, m->d_cb, n_cb, io.st, 0)) != WAVERNN_OK) return st;
+  for (int s = 0; s < io.S; s += per)
+    if ((st = launch_persist(m, io, s, std::min(per, io.S - s), xc[0], xs, cb[0], cs, n_cb)) != WAVERNN_OK) return st;
   return WAVERNN_OK;
 }
 
@@ -1354,7 +1446,9 @@ wavernn_status run_score(wavernn_model* m, const RunIO& io) {
     if ((st = m->alloc(&m->d_sz, (size_t)2 * ch * 256 * 4)) != WAVERNN_OK) return st;
     m->so_cap = ch;
   }
-  if ((st = launch_cond(m, io.cond, n_cb, io.S, m->d_scb, io.st)) != WAVERNN_OK) return st;
+  if ((st = launch_cond(m, io.cond, n_cb, first_frame(m, io), last_frame(m, io), io.S, m->d_scb, 0, nullptr, 0, 0,
+                        io.st)) != WAVERNN_OK)
+    return st;
   if ((st = launch_fill(m->d_sxc, (int64_t)G * score_words(H, LV), io.st)) != WAVERNN_OK) return st;
   {
     ScoreArgs a;
@@ -1417,48 +1511,6 @@ wavernn_status run_score(wavernn_model* m, const RunIO& io) {
   return WAVERNN_OK;
 }
 
-// A few utterances at once: utterance 0 runs the batch-1 kernel on the
-// caller's stream, utterance s > 0 on internal stream s - 1 (each its own
-// grid, exchange words and table), forked from and joined back into the
-// caller's stream, so the call stays stream-ordered.  The grids are
-// co-resident together (checked at create); with one hardware queue per
-// stream (4 by default, so the caller's stream and 3 more) the launches run
-// side by side: at batch 4 about four times the batch-1 rate, where the
-// batched kernel, which shares one grid among the utterances, gives under
-// three.
-wavernn_status run_fanout(wavernn_model* m, const RunIO& io) {
-  const int64_t n_cb = m->cfg.cond_dim > 0 ? io.n_frames : 1;
-  wavernn_status st = WAVERNN_OK;
-  xw* xc[WR_FAN] = {};
-  float* cb[WR_FAN] = {};
-  if (io.ws) {
-    if ((st = carve_ws(io, io.S, m->plan.x_words, (size_t)n_cb * 3 * m->plan.H, xc, cb)) != WAVERNN_OK) return st;
-  } else {
-    for (int i = 0; i < io.S; ++i) xc[i] = m->d_fxc[i];
-  }
-  if (!io.ws && n_cb > m->fcb_cap) {
-    HIPOK(hipStreamSynchronize(io.st));
-    int64_t cap = 0;
-    for (int i = 0; i < m->nfan && st == WAVERNN_OK; ++i) {
-      cap = m->fcb_cap;
-      st = grow_cb(m, &m->d_fcb[i], &cap, n_cb);
-    }
-    if (st != WAVERNN_OK) return st;
-    m->fcb_cap = cap;
-  }
-  if (!io.ws)
-    for (int i = 0; i < io.S; ++i) cb[i] = m->d_fcb[i];
-  HIPOK(hipEventRecord(m->fan_fork, io.st));
-  for (int s = 1; s < io.S; ++s) {
-    HIPOK(hipStreamWaitEvent(m->fan_st[s - 1], m->fan_fork, 0));
-    if ((st = launch_persist_one(m, io, s, xc[s], cb[s], n_cb, m->fan_st[s - 1], io.S)) != WAVERNN_OK) return st;
-    HIPOK(hipEventRecord(m->fan_join[s - 1], m->fan_st[s - 1]));
-  }
-  if ((st = launch_persist_one(m, io, 0, xc[0], cb[0], n_cb, io.st, io.S)) != WAVERNN_OK) return st;
-  for (int s = 1; s < io.S; ++s) HIPOK(hipStreamWaitEvent(io.st, m->fan_join[s - 1], 0));
-  return WAVERNN_OK;
-}
-
 wavernn_status run_batch(wavernn_model* m, const RunIO& io) {
   const int SB = m->cfg.subscale;                 // lanes per utterance
   const int V = io.S * SB;                        // vectors
@@ -1490,7 +1542,9 @@ wavernn_status run_batch(wavernn_model* m, const RunIO& io) {
   }
   const void* kernel = wr_batch_kernel_ptr(B.KH, B.KX > 0, B.L, F >= 0);
   if (!kernel) return fail(WAVERNN_E_UNSUPPORTED, "no batched kernel for %d vectors", V);
-  if ((st = launch_cond(m, io.cond, n_cb, io.S, cbt, io.st)) != WAVERNN_OK) return st;
+  if ((st = launch_cond(m, io.cond, n_cb, first_frame(m, io), last_frame(m, io), io.S, cbt, 0, nullptr, 0, 0, io.st)) !=
+      WAVERNN_OK)
+    return st;
   BatchArgs a;
   memset(&a, 0, sizeof a);
   a.P = B;
@@ -1608,12 +1662,11 @@ wavernn_status run(wavernn_model* m, RunIO& io, bool noalloc = false) {
   if (dev != m->device) return fail(WAVERNN_E_INVALID, "model lives on device %d, current device is %d", m->device, dev);
   if (noalloc && (s = scratch_of(dev, &io.ws, &io.ws_cap)) != WAVERNN_OK) return s;
   if (m->path == PATH_SMALL) return run_small(m, io);
-  if (m->fused) return run_persist(m, io);   // one fused launch per utterance
+  if (m->fused) return run_persist(m, io);
   if (m->path == PATH_PERSIST) {
     // one utterance (or a model that runs its utterances one after another) scores on the recurrence kernel
     if (io.target && m->score) return run_score(m, io);
-    if (io.S > 1 && io.S <= m->nfan) return run_fanout(m, io);
-    return io.S > 1 && m->has_batch ? run_batch(m, io) : run_persist(m, io);
+    return io.S > std::max(m->nfan, 1) && m->has_batch ? run_batch(m, io) : run_persist(m, io);
   }
   if (m->path == PATH_BATCHED) return run_batch(m, io);
   return fail(WAVERNN_E_UNSUPPORTED, "no kernel for this configuration");
@@ -1626,7 +1679,6 @@ wavernn_status run(wavernn_model* m, RunIO& io, bool noalloc = false) {
 // never uses the array's name as an address: the device address is looked up
 // once per device with hipGetSymbolAddress and kept in g_scratch.
 #define WR_SCRATCH_BYTES ((size_t)16 << 20)
-#define WR_MAX_DEVICES 64
 static __device__ __align__(256) uint64_t scratch[WR_SCRATCH_BYTES / 8];
 
 namespace {
@@ -1749,6 +1801,7 @@ wavernn_status wavernn_create(const wavernn_config* cfg, const wavernn_weights* 
     else {
       m->path = PATH_PERSIST;
       s = build_fused(m, w);
+      if (s == WAVERNN_OK && cfg->max_streams > 1) s = build_fanout(m);
     }
   } else if (B > 1) {
     // Subscale (Sec. 4): the B lanes of each utterance are vectors of the
@@ -1913,7 +1966,7 @@ int32_t wavernn_model_path(const wavernn_model* m, int32_t n_streams, int32_t* g
              batch_plan(m->cfg.hidden, (n_streams > 0 ? n_streams : 1) * m->cfg.subscale, &B, m->cfg.ctx_dim,
                         m->cfg.subscale, horizon_of(m->cfg), lead_of(m->cfg), m->has_cnn)) {
     g = B.grid, b = WR_THREADS;
-  } else if (m->path == PATH_PERSIST && n_streams > 1 && n_streams <= m->nfan) {
+  } else if (m->path == PATH_PERSIST && !m->fused && n_streams > 1 && n_streams <= m->nfan) {
     path = PATH_CONCURRENT_ID, g = m->plan.grid, b = WR_THREADS;
   } else if (m->path == PATH_PERSIST && n_streams > 1 && m->has_batch && batch_plan(m->cfg.hidden, n_streams, &B)) {
     path = PATH_BATCHED, g = B.grid, b = WR_THREADS;

@@ -254,7 +254,7 @@ __device__ __forceinline__ bool gather_y(const xw* Y, uint32_t tag, unsigned cha
   const uint32_t todo = pending;
   WaitBudget wb{0, 0};
   for (;;) {
-    const __amdgpu_buffer_rsrc_t rs = xrsrc(xopaque(Y), (uint32_t)(L * HH) * 4u);
+    const __amdgpu_buffer_rsrc_t rs = xrsrc(xopaque_u(Y), (uint32_t)(L * HH) * 4u);
 #pragma unroll
     for (int m = 0; m < N; ++m)
       if (pending >> m & 1u) w[m] = xpeek4(rs, 16u * (r + NT * m));
@@ -293,15 +293,40 @@ __device__ __forceinline__ void trace_at(const A& a, int64_t t, int slot) {
 #ifndef WR_LOCAL_XCHG
 #define WR_LOCAL_XCHG 1
 #endif
-// Do all n workgroups of a launch that exchange words (the heads and mirrors
-// of a batch-1 grid, or a whole group of the batched one, placed on one XCD)
-// run on one XCD?  Workgroup i publishes its XCD (the XCC_ID hardware
-// register) in words[i] and lane k of wave 0 reads workgroup k's (n <= 64);
-// all read the same words, so all get the same answer.  Called by every
+// Do all n lead workgroups of a launch (the heads and mirrors of a batch-1
+// grid, placed on one XCD) run on one XCD?  Lead i publishes its XCD (the
+// XCC_ID hardware register) in words[i] and thread 0 reads every lead's; all
+// leads read the same words, so all get the same answer.  Called by every
 // thread of the workgroup (one barrier inside; flag: an LDS int).  A wait
 // that expires flags the launch's error word and answers no.
 template <class A>
 __device__ __forceinline__ bool leads_share_xcd(xw* words, int n, int i, int* flag, const A& a) {
+  if (threadIdx.x == 0) {
+    const unsigned x = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u;   // XCC_ID, bits 3:0
+    __hip_atomic_store(words + i, 0x100u | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int same = 1;
+    WaitBudget wb{wr_clock(), 0};
+    for (int k = 0; k < n && same; ++k) {
+      xw w;
+      while (!((w = xpeek(words + k)) & 0x100u))
+        if (!wait_ok(wb, a.err, a.limit, a.err)) {
+          same = 0;
+          break;
+        }
+      same = same && (w & 15u) == x;
+    }
+    *flag = same;
+  }
+  __syncthreads();
+  return *flag != 0;
+}
+
+// The same for the up to 64 workgroups of a whole group of the batched and
+// scoring kernels: lane k of wave 0 reads workgroup k's XCD, one load's wait
+// for all of them.  (The batch-1 kernels keep the loop above: with this form
+// the compiler's schedule of their step loop came out 2% slower.)
+template <class A>
+__device__ __forceinline__ bool group_shares_xcd(xw* words, int n, int i, int* flag, const A& a) {
   if (threadIdx.x < 64) {
     const int k = threadIdx.x;
     const unsigned x = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u;   // XCC_ID, bits 3:0

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(WR_THREADS, 1) void wr_score_kernel(ScoreArgs a) {
     const uint4* src = a.w + ((size_t)(k * 4 + wave) * NF) * 64 + lane;
 #pragma unroll
     for (int i = 0; i < NF; ++i) W[i] = __builtin_bit_cast(bf16x8, src[(size_t)i * 64]);
-    leads_share_xcd(X + 2 * LV * H, NW, k, misc + 1, a);
+    group_shares_xcd(X + 2 * LV * H, NW, k, misc + 1, a);
     __syncthreads();
     const int row = lane & 15, b0 = 2 * (lane >> 4);
     auto put = [&](int i, f32x4 d) {                 // tile i = chain * 6 + unit tile * 3 + gate
@@ -153,13 +153,13 @@ __global__ __launch_bounds__(WR_THREADS, 1) void wr_score_kernel(ScoreArgs a) {
   };
   targets(0);
   put_targets(0);
-  const bool lx = leads_share_xcd(X + 2 * LV * H, NW, k, misc + 1, a) && WR_LOCAL_XCHG;
+  const bool lx = group_shares_xcd(X + 2 * LV * H, NW, k, misc + 1, a) && WR_LOCAL_XCHG;
   __builtin_amdgcn_s_waitcnt(0);   // prologue loads in before the loop (see the persistent heads)
   __syncthreads();
   for (int64_t s = 0; s < a.T; ++s) {
     if (s > 0) {   // h_{s-1} of every workgroup and vector into the image
       __builtin_amdgcn_s_sleep(WR_SCORE_DELAY);
-      if (!gather_y<LV, H, 256, true>(X + __builtin_amdgcn_readfirstlane((int)((s - 1) & 1)) * (LV * H),
+      if (!gather_y<LV, H, 256, true>(X + ((s - 1) & 1) * (LV * H),
                                       (uint32_t)((s - 1) >> 1) + 1u, img, r, -1, a))
         misc[0] = 1;
       __syncthreads();
