@@ -68,7 +68,7 @@ struct PersistArgs {
 // Teacher-forced recurrence of the dense batch-1 model (wr_score.hip).
 // S utterances in G groups of LV (the last one partly used); every
 // per-utterance array holds them one after another: cb [S][n_cb][3H], target
-// [S][T], h [S][H], c / f [S], traj [S][T][Hh].  Exchange words of a group:
+// [S][T], h [S][H], c / f [S], traj [S][T].  Exchange words of a group:
 // h [2][LV][H], then the XCDs of its workgroups.
 inline __host__ __device__ int score_words(int H, int LV) { return 2 * LV * H + 64; }
 struct ScoreArgs {
@@ -89,8 +89,8 @@ struct ScoreArgs {
   float* h_out;             // [H] or null
   uint8_t* c_out;
   uint8_t* f_out;
-  float* traj_c;            // [T][Hh] coarse half of h after each step
-  float* traj_f;            // [T][Hh] fine half
+  uint16_t* traj_c;         // [S][T] split rows (CnnGemmArgs) of the coarse half of h after each step
+  uint16_t* traj_f;         // of the fine half
   xw* xc;                   // [G][score_words] exchange words, zeroed before the launch
   unsigned* err;
   u64 limit;
@@ -147,8 +147,13 @@ struct BatchArgs {
 // One GEMM of the conditioning CNN: dst[m][n] (epilogue) over
 // acc = sum_k A[m][k] W[n][k], n < N, on 128 x 128 tiles.
 #define WR_CNN_MAXB 64   // sub-tensors of a streamed CNN run at most
+// Activations that a GEMM reads are split rows: a row of width K is K / 32
+// groups of 32 bf16 high parts and then the 32 bf16 remainders of the same
+// columns (2 K elements, one 128-byte line a group), written so by whoever
+// makes them, so the GEMM's loads are copies.
 struct CnnGemmArgs {
-  const float* src;       // activations [M][kin]
+  const uint16_t* src;    // activations [M] split rows of width kin
+  const uint16_t* zero;   // 128 bytes of zeros: rows read as zero
   int kin;                // source row width (a multiple of 32)
   int taps, dil;          // A row m = [src row m + tap dil (same block, tap < taps)], zero past the block
                           // and past the utterance's last row
@@ -161,14 +166,16 @@ struct CnnGemmArgs {
   const uint4* w;         // weight fragments [N / 16][K / 32] x 64 lanes
   const float* bias;      // [N]
   int N;                  // a multiple of 128
-  float* dst;             // [M][N] rows, or with out_B > B block (u, s) of the run at block u out_B + out_s0 + s
+  float* dst;             // [M][N] rows, or with out_B > B block (u, s) of the run at block u out_B + out_s0 + s,
+                          // or null
+  uint16_t* dsts;         // the same rows split, or null
   int out_B, out_s0;      // (out_B = B, out_s0 = 0: row m at row m)
   int epi;                // 0: acc + bias; 1: relu(acc + bias); 2: dst + (acc + bias)
   int group;              // K-steps per accumulation group (the sum is ((g0 + g1) + g2) + ..., each g_q from 0)
   int split;              // 1: a workgroup runs every group of its tile; > 1 (= the number of groups):
                           // workgroup (tile, q) writes g_q to part[q] and wr_cnn_reduce adds them in order
   float* part;            // [groups][M][N] (split > 1)
-  int tiles_m, tiles, per_xcd;   // 128-row tiles, all tiles, tiles x split per XCD slot
+  int tiles, per_xcd;     // tiles, tiles x split per XCD slot
   // Streamed runs (rng = 1): block b of the run is (utterance b / B, sub-tensor out_s0 + b % B); its
   // row k is utterance row lo[s] + k, and only rows below hi[s] are computed (the others are read as
   // zero and not stored).  With src_abs (dst_abs) the source (destination) is a whole-utterance array
@@ -177,10 +184,8 @@ struct CnnGemmArgs {
   int rng, src_abs, dst_abs;
   int lo[WR_CNN_MAXB], hi[WR_CNN_MAXB];
 };
-#define CNN_TM 128
-#define CNN_TN 128
-#define CNN_THREADS 512
-#define CNN_LDS_BUF (3 * 8 * 1024)   // A high, A low (8 row tiles each), W (8 column tiles), fragments of 1 KiB
+#define CNN_TN 128            // columns of a tile; its rows are 32 MI
+#define CNN_THREADS 256
 
 // Input rows of the conditioning CNN (see wr_cnn_input).
 struct CnnInputArgs {
@@ -194,7 +199,7 @@ struct CnnInputArgs {
   int s0, nsb;            // the run covers sub-tensors s0 .. s0 + nsb - 1 of each utterance: block m / win =
                           // (u, s - s0)
   int M, kin;
-  float* x;               // [M][kin]
+  uint16_t* x;            // [M] split rows of width kin
   int rng;                // streamed run: block (u, s - s0)'s row k is utterance row lo[s] + k
   int lo[WR_CNN_MAXB];
 };
@@ -228,6 +233,6 @@ const void* wr_batch_floor_kernel_ptr(int KH, bool ctx, int L, bool lag);   // n
 const void* wr_fill_kernel_ptr();
 const void* wr_fused_kernel_ptr(int KH);     // null if no instantiation
 const void* wr_floor_kernel_ptr();
-const void* wr_cnn_gemm_ptr();
+const void* wr_cnn_gemm_ptr(int MI);         // tiles of 32 MI rows, MI 2 .. 4
 const void* wr_cnn_input_ptr();
 const void* wr_cnn_reduce_ptr();

@@ -136,9 +136,11 @@ struct wavernn_model {
   float* d_sb = nullptr;
   size_t sw_off[4] = {}, sb_off[4] = {};
   int sc_np = 0;
-  float* d_traj = nullptr;            // [2][rows][Hh] h after each step (coarse half, then fine half)
+  uint16_t* d_traj = nullptr;         // [2][rows] split rows of h after each step (coarse half, then fine half)
   int64_t traj_cap = 0;               // rows
-  float *d_so = nullptr, *d_sz = nullptr;   // [rows][NP] first-layer output, [2][rows][256] logits
+  uint16_t* d_so = nullptr;           // [rows] split rows of the first-layer output (NP wide)
+  float* d_sz = nullptr;              // [2][rows][256] logits
+  uint16_t* d_zero = nullptr;         // 128 bytes of zeros (GEMM rows read as zero)
   int64_t so_cap = 0;                       // rows of d_so and d_sz (at most one chunk of the output layers)
   u64* trace = nullptr;
   int64_t trace_steps = 0;
@@ -157,11 +159,13 @@ struct wavernn_model {
     uint4* w = nullptr;
     float* bias = nullptr;
     std::vector<size_t> woff, boff;   // [input, conv 0, proj 0, conv 1, ..., output] in uint4 / floats
-    float *x = nullptr, *r = nullptr, *act = nullptr;
+    uint16_t *x = nullptr, *rs = nullptr, *act = nullptr;   // split rows: input, residual, convolution
+    float* r = nullptr;                // the residual in fp32
     int64_t cap = 0;                   // activation rows the buffers hold
     float* part = nullptr;             // per-group partial products of split GEMMs
     int64_t part_cap = 0;              // floats
     float* rfull = nullptr;            // streamed sampling: residual activations [U][B][rows][Rc]
+    uint16_t* rfulls = nullptr;        // and their split rows
     int64_t rfull_cap = 0;             // floats
   } cnn;
   bool has_cnn = false;
@@ -750,6 +754,12 @@ wavernn_status build_batch(wavernn_model* m, const wavernn_weights* w) {
   return WAVERNN_OK;
 }
 
+// The GEMMs' row of zeros.
+wavernn_status upload_zero(wavernn_model* m) {
+  const unsigned char z[128] = {};
+  return m->d_zero ? WAVERNN_OK : m->upload(&m->d_zero, z, sizeof z);
+}
+
 // Fragments [N / 16][K / 32] (operand B of v_mfma_f32_16x16x32_bf16) of a
 // matrix W(n, k), n < N, k < K (K a multiple of 32), bf16 round to nearest even.
 template <class M>
@@ -822,7 +832,7 @@ wavernn_status build_cnn(wavernn_model* m, const wavernn_ctx_cnn* n) {
   wavernn_status s;
   if ((s = m->upload(&C.w, w.data(), w.size() * 2)) != WAVERNN_OK) return s;
   if ((s = m->upload(&C.bias, b.data(), b.size() * 4)) != WAVERNN_OK) return s;
-  HIPOK(hipFuncSetAttribute(wr_cnn_gemm_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * CNN_LDS_BUF));
+  if ((s = upload_zero(m)) != WAVERNN_OK) return s;
   m->has_cnn = true;
   return WAVERNN_OK;
 }
@@ -875,7 +885,7 @@ wavernn_status build_score(wavernn_model* m, const wavernn_weights* w) {
   wavernn_status s;
   if ((s = m->upload(&m->d_sw, wv.data(), wv.size() * 2)) != WAVERNN_OK) return s;
   if ((s = m->upload(&m->d_sb, bv.data(), bv.size() * 4)) != WAVERNN_OK) return s;
-  HIPOK(hipFuncSetAttribute(wr_cnn_gemm_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * CNN_LDS_BUF));
+  if ((s = upload_zero(m)) != WAVERNN_OK) return s;
   for (int LV = 1; LV <= 8 && LV < 2 * m->cfg.max_streams; LV *= 2)
     if ((s = check_coresident(m, wr_score_kernel_ptr(KT2, LV), 8 * (H / 32), 0, "scoring")) != WAVERNN_OK) return s;
   if ((s = m->alloc(&m->d_sxc, (size_t)8 * score_words(H, 8) * 4)) != WAVERNN_OK) return s;
@@ -893,9 +903,24 @@ struct CnnRows {   // which utterance rows the blocks of a CNN run cover
 // never depend on the rows of a run); a GEMM with fewer tiles than CUs runs
 // each group on its own workgroup and adds them in wr_cnn_reduce.
 #define CNN_GROUP 6
-int cnn_split(int M, int N, int K) {
-  const int tiles = (M + CNN_TM - 1) / CNN_TM * (N / CNN_TN), groups = (K / 32 + CNN_GROUP - 1) / CNN_GROUP;
-  return tiles < 256 && groups > 1 ? groups : 1;
+#define CNN_SLOTS 512   // workgroups the card holds at once (two a CU)
+// Rows of a tile: 32 MI, the MI whose rounds over the slots take least (a round
+// costs its tile's rows, small tiles a little more for their W reads).
+int cnn_mi(int64_t M, int N) {
+  int best = 4;
+  double cost = 1e30;
+  for (int mi = 4; mi >= 2; --mi) {
+    const int64_t tiles = (M + 32 * mi - 1) / (32 * mi) * (N / CNN_TN);
+    const double c = (double)((tiles + CNN_SLOTS - 1) / CNN_SLOTS) * (mi + 0.5);
+    if (c < cost) cost = c, best = mi;
+  }
+  return best;
+}
+// Split where 64-row tiles fill less than half of the slots and the K loop has
+// enough groups to be worth a reduction launch.
+int cnn_split(int64_t M, int N, int K) {
+  const int64_t tiles = (M + 63) / 64 * (N / CNN_TN), groups = (K / 32 + CNN_GROUP - 1) / CNN_GROUP;
+  return tiles < CNN_SLOTS / 2 && groups >= 8 ? (int)groups : 1;
 }
 
 // A streamed run's rows (see CnnGemmArgs::rng): sub-tensor s's run rows are its utterance rows
@@ -906,9 +931,10 @@ struct CnnRng {
   int src_abs, dst_abs;
 };
 
-wavernn_status cnn_gemm(const float* src, int kin, int taps, int dil, int rows, const CnnRows& cr, int M,
-                        const uint4* w, const float* bias, int N, float* dst, int epi, hipStream_t st,
-                        float* part = nullptr, int out_B = 0, int out_s0 = 0, const CnnRng* rng = nullptr) {
+wavernn_status cnn_gemm(const wavernn_model* m, const uint16_t* src, int kin, int taps, int dil, int rows,
+                        const CnnRows& cr, int M, const uint4* w, const float* bias, int N, float* dst, uint16_t* dsts,
+                        int epi, hipStream_t st, float* part = nullptr, int out_B = 0, int out_s0 = 0,
+                        const CnnRng* rng = nullptr) {
   CnnGemmArgs g;
   memset(&g, 0, sizeof g);
   if (rng) {
@@ -932,19 +958,20 @@ wavernn_status cnn_gemm(const float* src, int kin, int taps, int dil, int rows, 
   g.bias = bias;
   g.N = N;
   g.dst = dst;
+  g.dsts = dsts;
+  g.zero = m->d_zero;
   g.out_B = out_B ? out_B : cr.B;
   g.out_s0 = out_s0;
   g.epi = epi;
   g.group = CNN_GROUP;
   g.split = part ? cnn_split(M, N, g.K) : 1;
   g.part = part;
-  g.tiles_m = (M + CNN_TM - 1) / CNN_TM;
-  g.tiles = g.tiles_m * (N / CNN_TN);
+  const int mi = g.split > 1 ? 2 : cnn_mi(M, N);
+  g.tiles = (M + 32 * mi - 1) / (32 * mi) * (N / CNN_TN);
   g.per_xcd = (g.tiles * g.split + 7) / 8;
   void* args[] = {&g};
-  HIPOK(hipLaunchKernel(wr_cnn_gemm_ptr(), dim3(8 * g.per_xcd), dim3(CNN_THREADS), args, 2 * CNN_LDS_BUF, st));
-  if (g.split > 1)
-    HIPOK(hipLaunchKernel(wr_cnn_reduce_ptr(), dim3((unsigned)(((int64_t)M * N + 255) / 256)), dim3(256), args, 0, st));
+  HIPOK(hipLaunchKernel(wr_cnn_gemm_ptr(mi), dim3(8 * g.per_xcd), dim3(CNN_THREADS), args, 0, st));
+  if (g.split > 1) HIPOK(hipLaunchKernel(wr_cnn_reduce_ptr(), dim3((M + 3) / 4), dim3(N / 4, 4), args, 0, st));
   return WAVERNN_OK;
 }
 
@@ -967,6 +994,7 @@ wavernn_status run_cnn(wavernn_model* m, int U, const uint16_t* seq, int64_t n_s
     wavernn_status s;
     if ((s = m->alloc(&C.x, (size_t)M * C.kin * 4)) != WAVERNN_OK) return s;
     if ((s = m->alloc(&C.r, (size_t)M * C.Rc * 4)) != WAVERNN_OK) return s;
+    if ((s = m->alloc(&C.rs, (size_t)M * C.Rc * 4)) != WAVERNN_OK) return s;
     if ((s = m->alloc(&C.act, (size_t)M * C.Cc * 4)) != WAVERNN_OK) return s;
     C.cap = M;
   }
@@ -1006,19 +1034,20 @@ wavernn_status run_cnn(wavernn_model* m, int U, const uint16_t* seq, int64_t n_s
   wavernn_status s;
   size_t i = 0;
   const CnnRows cr{nsb, row0 + s0 * row_step, row_step, n_samples / B};
-  if ((s = cnn_gemm(C.x, C.kin, 1, 0, win, cr, M, C.w + C.woff[i], C.bias + C.boff[i], C.Rc, C.r, 0, st, C.part)) !=
+  if ((s = cnn_gemm(m, C.x, C.kin, 1, 0, win, cr, M, C.w + C.woff[i], C.bias + C.boff[i], C.Rc, C.r, C.rs, 0, st, C.part)) !=
       WAVERNN_OK)
     return s;
   ++i;
   for (int l = 0; l < C.layers; ++l, i += 2) {
-    if ((s = cnn_gemm(C.r, C.Rc, 3, 1 << (l % 5), win, cr, M, C.w + C.woff[i], C.bias + C.boff[i], C.Cc, C.act, 1,
+    if ((s = cnn_gemm(m, C.rs, C.Rc, 3, 1 << (l % 5), win, cr, M, C.w + C.woff[i], C.bias + C.boff[i], C.Cc, nullptr, C.act, 1,
                       st, C.part)) != WAVERNN_OK)
       return s;
-    if ((s = cnn_gemm(C.act, C.Cc, 1, 0, win, cr, M, C.w + C.woff[i + 1], C.bias + C.boff[i + 1], C.Rc, C.r, 2,
+    if ((s = cnn_gemm(m, C.act, C.Cc, 1, 0, win, cr, M, C.w + C.woff[i + 1], C.bias + C.boff[i + 1], C.Rc, C.r, C.rs, 2,
                       st, C.part)) != WAVERNN_OK)
       return s;
   }
-  return cnn_gemm(C.r, C.Rc, 1, 0, win, cr, M, C.w + C.woff[i], C.bias + C.boff[i], Dx, out, 0, st, C.part, B, s0);
+  return cnn_gemm(m, C.rs, C.Rc, 1, 0, win, cr, M, C.w + C.woff[i], C.bias + C.boff[i], Dx, out, nullptr, 0, st, C.part,
+                  B, s0);
 }
 
 // The conditioning CNN streamed over a sampling call (Sec. 4.2: the
@@ -1057,6 +1086,7 @@ wavernn_status run_cnn_stream(wavernn_model* m, int U, const uint16_t* seq, int6
     HIPOK(hipStreamSynchronize(st));
     wavernn_status s;
     if ((s = m->alloc(&C.rfull, (size_t)rf * 4)) != WAVERNN_OK) return s;
+    if ((s = m->alloc(&C.rfulls, (size_t)rf * 4)) != WAVERNN_OK) return s;
     C.rfull_cap = rf;
   }
   for (int v = 0; v <= L + 1; ++v) {
@@ -1080,6 +1110,7 @@ wavernn_status run_cnn_stream(wavernn_model* m, int U, const uint16_t* seq, int6
       wavernn_status s;
       if ((s = m->alloc(&C.x, (size_t)M * C.kin * 4)) != WAVERNN_OK) return s;
       if ((s = m->alloc(&C.r, (size_t)M * C.Rc * 4)) != WAVERNN_OK) return s;
+      if ((s = m->alloc(&C.rs, (size_t)M * C.Rc * 4)) != WAVERNN_OK) return s;
       if ((s = m->alloc(&C.act, (size_t)M * C.Cc * 4)) != WAVERNN_OK) return s;
       C.cap = M;
     }
@@ -1120,22 +1151,22 @@ wavernn_status run_cnn_stream(wavernn_model* m, int U, const uint16_t* seq, int6
       const int64_t nx = (int64_t)M * C.kin;
       HIPOK(hipLaunchKernel(wr_cnn_input_ptr(), dim3((unsigned)((nx + 255) / 256)), dim3(256), args, 0, st));
       const CnnRng rg{lo[0], hi, 0, 1};
-      if ((s = cnn_gemm(C.x, C.kin, 1, 0, n, cr, M, C.w + C.woff[0], C.bias + C.boff[0], C.Rc, C.rfull, 0, st,
+      if ((s = cnn_gemm(m, C.x, C.kin, 1, 0, n, cr, M, C.w + C.woff[0], C.bias + C.boff[0], C.Rc, C.rfull, C.rfulls, 0, st,
                         C.part, B, a, &rg)) != WAVERNN_OK)
         return s;
     } else if (v <= L) {   // layer v: convolution from the residual array, projection added back into it
       const size_t i = 1 + 2 * (size_t)(v - 1);
       const CnnRng conv{lo[v], hi, 1, 0}, proj{lo[v], hi, 0, 1};
-      if ((s = cnn_gemm(C.rfull, C.Rc, 3, 1 << ((v - 1) % 5), n, cr, M, C.w + C.woff[i], C.bias + C.boff[i], C.Cc,
-                        C.act, 1, st, C.part, B, a, &conv)) != WAVERNN_OK)
+      if ((s = cnn_gemm(m, C.rfulls, C.Rc, 3, 1 << ((v - 1) % 5), n, cr, M, C.w + C.woff[i], C.bias + C.boff[i], C.Cc,
+                        nullptr, C.act, 1, st, C.part, B, a, &conv)) != WAVERNN_OK)
         return s;
-      if ((s = cnn_gemm(C.act, C.Cc, 1, 0, n, cr, M, C.w + C.woff[i + 1], C.bias + C.boff[i + 1], C.Rc, C.rfull, 2,
+      if ((s = cnn_gemm(m, C.act, C.Cc, 1, 0, n, cr, M, C.w + C.woff[i + 1], C.bias + C.boff[i + 1], C.Rc, C.rfull, C.rfulls, 2,
                         st, C.part, B, a, &proj)) != WAVERNN_OK)
         return s;
     } else {   // output rows into the whole-utterance table
       const size_t i = 1 + 2 * (size_t)L;
       const CnnRng o{lo[v], hi, 1, 1};
-      if ((s = cnn_gemm(C.rfull, C.Rc, 1, 0, n, cr, M, C.w + C.woff[i], C.bias + C.boff[i], Dx, out, 0, st, C.part,
+      if ((s = cnn_gemm(m, C.rfulls, C.Rc, 1, 0, n, cr, M, C.w + C.woff[i], C.bias + C.boff[i], Dx, out, nullptr, 0, st, C.part,
                         B, a, &o)) != WAVERNN_OK)
         return s;
     }
@@ -1474,7 +1505,7 @@ wavernn_status run_score(wavernn_model* m, const RunIO& io) {
       a.f_out = io.fin->f_prev;
     }
     a.traj_c = m->d_traj;
-    a.traj_f = m->d_traj + (size_t)rows * Hh;
+    a.traj_f = m->d_traj + (size_t)2 * rows * Hh;
     a.xc = m->d_sxc;
     a.err = m->d_err;
     a.limit = kWaitTicks;
@@ -1490,12 +1521,12 @@ wavernn_status run_score(wavernn_model* m, const RunIO& io) {
     for (int k = 0; k < 2; ++k) {
       float* user = k ? io.zf : io.zc;
       z[k] = user ? user + (size_t)r0 * 256 : m->d_sz + (size_t)k * ch * 256;
-      const float* src = m->d_traj + ((size_t)k * rows + r0) * Hh;
-      if ((st = cnn_gemm(src, Hh, 1, 0, n, cr, n, m->d_sw + m->sw_off[2 * k], m->d_sb + m->sb_off[2 * k], NP,
-                         m->d_so, 1, io.st)) != WAVERNN_OK)
+      const uint16_t* src = m->d_traj + ((size_t)k * rows + r0) * 2 * Hh;
+      if ((st = cnn_gemm(m, src, Hh, 1, 0, n, cr, n, m->d_sw + m->sw_off[2 * k], m->d_sb + m->sb_off[2 * k], NP,
+                         nullptr, m->d_so, 1, io.st)) != WAVERNN_OK)
         return st;
-      if ((st = cnn_gemm(m->d_so, NP, 1, 0, n, cr, n, m->d_sw + m->sw_off[2 * k + 1], m->d_sb + m->sb_off[2 * k + 1],
-                         256, z[k], 0, io.st)) != WAVERNN_OK)
+      if ((st = cnn_gemm(m, m->d_so, NP, 1, 0, n, cr, n, m->d_sw + m->sw_off[2 * k + 1], m->d_sb + m->sb_off[2 * k + 1],
+                         256, z[k], nullptr, 0, io.st)) != WAVERNN_OK)
         return st;
     }
     if (io.nll) {

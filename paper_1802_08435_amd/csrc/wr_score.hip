@@ -199,8 +199,10 @@ __global__ __launch_bounds__(WR_THREADS, 1) void wr_score_kernel(ScoreArgs a) {
       }
       h = __builtin_fmaf(uu, h, (1.0f - uu) * e);
       xpub_l(Y, tag, h, lx);
-      if (fine) a.traj_f[((size_t)vb * a.T + s) * Hh + (u - Hh)] = h;
-      else a.traj_c[((size_t)vb * a.T + s) * Hh + u] = h;
+      // a split row (CnnGemmArgs): units 32 k .. are one of its groups
+      uint16_t* tr = (fine ? a.traj_f : a.traj_c) + ((size_t)vb * a.T + s) * H + 64 * (fine ? k - NW / 2 : k) + (r & 31);
+      tr[0] = (uint16_t)(__float_as_uint(h) >> 16);
+      tr[32] = __builtin_bit_cast(uint16_t, (__bf16)(h - __uint_as_float(__float_as_uint(h) & 0xffff0000u)));
       cp = c;
       fp = tg & 255;
       if (s + 1 == edge) frame();
