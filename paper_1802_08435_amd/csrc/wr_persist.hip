@@ -96,8 +96,8 @@ __device__ __forceinline__ bool gather_partials(const PersistArgs& a, const xw* 
 //  GU > 1 (wide): waves 0-6 prepare the pre-activations of units tid + 448 m
 //   into LDS, then all 8 waves finish units tid + 512 m; the state stays in
 //   LDS (registers are short with the larger O-layer slices).
-// All 8 waves run the MFMA layers and gather the partial logits (two threads
-// per class); the gate threads of this head's slice of units publish it for
+// All 8 waves run the MFMA layers; the draw wave (SPLIT: waves 6 and 7) gathers
+// the partial logits; the gate threads of this head's slice of units publish it for
 // the unit workgroups.
 // MR (mirrors, dense GU = 1 only): a coarse gate's pre-activation is the
 // units' coarse-column word plus the mirrors' fine-column word, and the fine
@@ -267,27 +267,45 @@ __device__ __forceinline__ void head_role(const PersistArgs& a, int j, unsigned 
       xpub_l(dst + 32 * wave + 16 + lane, tag, mfma_row(B), lx);
     }
   };
-  // partial logits of all slices: thread (v, half) sums its half of the
-  // slices in slice order, each word checked for its tag.  The partials are
-  // being published as this head starts to wait, so the first probe waits a
-  // little (a probe at once comes back without them, and every failed probe
-  // of the whole grid loads the exchange; measured: 7 slices 5.17 us per
-  // step with a 6 x 64-clock delay, 5.59 without, 5.64 with the flag phase
-  // below).  With split heads (16 slices, 8 words per thread) lane jj of
-  // every wave first waits for the last word of slice jj, so that while the
-  // exchange is in flight only those words are polled.
+  // split heads (16 slices at H = 2048): waves 6 and 7 gather the partial
+  // logits of the first and the second half of the slices, lane l classes
+  // 4 l .. 4 l + 3 of each with one 16-byte load, and sum them in slice order.
+  // With this and the gate words' 16-byte loads (wide_words) a step at H = 2048
+  // went from 8.30 to 7.67 us; waiting first for each slice's last word costs
+  // 1%.
   auto gather_logits = [&](const xw* src, uint32_t tag) {
-    if (SPLIT) __builtin_amdgcn_s_sleep(12);
-    else __builtin_amdgcn_s_sleep(6);
-    if (SPLIT) {   // every wave waits on the flags itself: no barrier before the reads
-      float y;
-      const int jj = lane < NK ? lane : 0;
-      if (!poll_sleepy<false>(src + (size_t)jj * P.x_ps + 255, tag, &y, a)) misc[0] = 1;
+    if (wave < 6) return;
+    const int hh = wave - 6, k0 = hh ? NHP : 0, nk = hh ? NK - NHP : NHP;
+    __builtin_amdgcn_s_sleep(4);                     // (1, 4 and 10 x 64 clocks: 7.72, 7.67, 7.72 us a step)
+    const uint32_t lo = 16u * lane, ps = (uint32_t)P.x_ps * 4u;
+    xw4 w[NHP];
+    uint32_t pending = (1u << nk) - 1u;
+    WaitBudget wb{0, 0};
+    for (;;) {
+      const __amdgpu_buffer_rsrc_t r = xrsrc(xopaque(src), NK * ps);
+#pragma unroll
+      for (int k = 0; k < NHP; ++k)
+        if (pending >> k & 1u) w[k] = xpeek4(r, (k0 + k) * ps + lo);
+#pragma unroll
+      for (int k = 0; k < NHP; ++k)
+        if ((pending >> k & 1u) && xok4(w[k], tag)) pending &= ~(1u << k);
+      if (!pending) break;
+      if (!wb.spins) wb.start = wr_clock();
+      if (!wait_ok(wb, a.err, a.limit, a.err)) {
+        misc[0] = 1;
+        return;
+      }
     }
-    float s;
-    const int v = tid & 255, hh = tid >> 8;
-    if (!sum_parts<NHP>(src, P.x_ps, hh ? NHP : 0, hh ? NK : NHP, v, tag, &s, a)) misc[0] = 1;
-    else (hh ? zs2 : zs)[v] = s;
+    float4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < NHP; ++k)
+      if (k < nk) {
+        s.x += xval(w[k].x);
+        s.y += xval(w[k].y);
+        s.z += xval(w[k].z);
+        s.w += xval(w[k].w);
+      }
+    *(float4*)((hh ? zs2 : zs) + 4 * lane) = s;
   };
   auto gather_wave = [&](const xw* src, uint32_t tag, float4* z) -> bool {
     return gather_partials<NK>(a, src, tag, z);
@@ -308,50 +326,47 @@ __device__ __forceinline__ void head_role(const PersistArgs& a, int j, unsigned 
   prefetch_coarse(a.t0);
   prefetch_fine(0);
   const bool trw = j == 0 && tid == WR_THREADS - 64;       // tracing thread (draw wave)
-  // wide: the units publish a step's coarse and fine words together, so both
-  // are read at once (one round trip) with the conditioning of the e gates:
-  // coarse terms into pre, the fine words and conditioning into prf
-  // Word k of a thread: half k / (3 GU) (GA, GF), slot m = k / 3 % GU, gate
-  // k % 3; its value lands in LDS (pre rows 0-2 or prf rows 0-2) as it arrives.
+  // wide: thread t reads the words of units 4 t .. 4 t + 3 of the half this
+  // (split) head evaluates, a 16-byte load a gate, and with them the e gates'
+  // conditioning: a coarse head prepares its terms in pre, a fine head keeps
+  // the words and conditioning in prf.
   auto wide_words = [&](uint32_t tag, float x0, int64_t n) -> bool {
-    if (wave == DW) return true;
-    constexpr int NW = 6 * GU;
-    const float* cbr = cb_row(a, n) + 2 * H;
-    int un[GU];
-    float cbc[GU], cbf[GU];
-#pragma unroll
-    for (int m = 0; m < GU; ++m) {
-      un[m] = tid + 448 * m < Hh ? tid + 448 * m : tid;
-      cbc[m] = cbr[un[m]];
-      cbf[m] = cbr[Hh + un[m]];
-    }
-    // with split MLPs a head reads only the half it evaluates
-    uint32_t pending = (coarse ? (1u << 3 * GU) - 1 : 0u) | (fine ? ((1u << 3 * GU) - 1) << 3 * GU : 0u);
-    WaitBudget wb{wr_clock(), 0};
+    const int v = 4 * tid;
+    if (wave == DW || v >= Hh) return true;
+    const xw* G = coarse ? GA : GF;
+    const float4 cb = *(const float4*)(cb_row(a, n) + 2 * H + (coarse ? 0 : Hh) + v);
+    xw4 w[3];
+    uint32_t pending = 7u;
+    WaitBudget wb{0, 0};
     for (;;) {
-      xw x[NW];
+      const __amdgpu_buffer_rsrc_t r = xrsrc(xopaque(G), 3u * Hh * 4u);
 #pragma unroll
-      for (int k = 0; k < NW; ++k)
-        x[k] = (pending >> k & 1u) ? xpeek((k < 3 * GU ? GA : GF) + (k % 3) * Hh + un[k / 3 % GU]) : 0;
+      for (int k = 0; k < 3; ++k)
+        if (pending >> k & 1u) w[k] = xpeek4(r, (uint32_t)(k * Hh + v) * 4u);
 #pragma unroll
-      for (int k = 0; k < NW; ++k)
-        if ((pending >> k & 1u) && xok(x[k], tag)) {
-          (k < 3 * GU ? pre : prf)[(k % 3) * Hh + un[k / 3 % GU]] = xval(x[k]);
-          pending &= ~(1u << k);
-        }
+      for (int k = 0; k < 3; ++k)
+        if ((pending >> k & 1u) && xok4(w[k], tag)) pending &= ~(1u << k);
       if (!pending) break;
+      if (!wb.spins) wb.start = wr_clock();
       if (!wait_ok(wb, a.err, a.limit, a.err)) return false;
     }
+    const float cbv[4] = {cb.x, cb.y, cb.z, cb.w};
 #pragma unroll
-    for (int m = 0; m < GU; ++m) {
-      if (tid + 448 * m >= Hh) continue;
-      const int v = un[m];
-      const float* iv = iws + 15 * v;
-      pre[v] = pre[v] + iv[0] * x0;
-      pre[Hh + v] = pre[Hh + v] + iv[5] * x0;
-      pre[3 * Hh + v] = iv[10] * x0;
-      pre[4 * Hh + v] = cbc[m];
-      prf[3 * Hh + v] = cbf[m];
+    for (int e = 0; e < 4; ++e) {
+      const float u0 = xval(w[0][e]), r0 = xval(w[1][e]), e0 = xval(w[2][e]);
+      if (coarse) {
+        const float* iv = iws + 15 * (v + e);
+        pre[v + e] = u0 + iv[0] * x0;
+        pre[Hh + v + e] = r0 + iv[5] * x0;
+        pre[2 * Hh + v + e] = e0;
+        pre[3 * Hh + v + e] = iv[10] * x0;
+        pre[4 * Hh + v + e] = cbv[e];
+      } else {
+        prf[v + e] = u0;
+        prf[Hh + v + e] = r0;
+        prf[2 * Hh + v + e] = e0;
+        prf[3 * Hh + v + e] = cbv[e];
+      }
     }
     return true;
   };
