@@ -297,7 +297,8 @@ int32_t wavernn_model_path(const wavernn_model* m, int32_t n_streams, int32_t* g
  * an exchange depends on where producer and consumer sit, in ways that
  * differ from device to device.  Candidate i (0 <= i < 64) puts the head
  * workgroups on XCD hx = i / 8 and the unit workgroups on XCD ux = i % 8
- * (ux == hx: the units spread over every XCD, the default, candidate 0).
+ * (ux == hx: the units spread over every XCD, or on path 5 beside the heads;
+ * candidate 0 is the default).
  * A candidate fits when every workgroup of one launch can be resident at
  * once; only launches that run one at a time use the placement (the
  * concurrent launches of path 4 keep the default).  Results do not depend

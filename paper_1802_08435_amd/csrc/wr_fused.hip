@@ -154,7 +154,7 @@ __device__ __forceinline__ void fused_head_role(const PersistArgs& a, int j, uns
     __syncthreads();
   };
   // second layer: class tile `wave` (< 4) over this head's HR columns -> 16 of the 64 partials
-  bool lx = false;   // all heads on one XCD: partials published into its L2
+  bool lx = false, lxa = false;   // all heads (the whole grid) on one XCD: partials (y) published into its L2
   auto second_layer = [&](const bf16x8* W, xw* dst, uint32_t tag) {
     if (wave >= 4) return;
     f32x4 A = {0, 0, 0, 0};
@@ -165,7 +165,11 @@ __device__ __forceinline__ void fused_head_role(const PersistArgs& a, int j, uns
   // the draw wave: lane l sums partial l of every head (in head order, as
   // every head does) once all carry `tag`; the first probe waits a little
   auto gather = [&](const xw* src, uint32_t tag, float* s) -> bool {
-    __builtin_amdgcn_s_sleep(6);   // (measured: 2 x 64 clocks 7% slower)
+    // first probe, x 64 clocks: with the whole grid on one XCD the waves' polls
+    // share its L2, and a probe that comes back empty holds up the next.  H = 896,
+    // ms for 24,000 samples: 3 53.6, 6 52.3, 10 49.1, 14 48.3, 18 49.8; H = 128,
+    // whose layers are shorter, us for 342: 3 504, 6 532, 10 569
+    __builtin_amdgcn_s_sleep(KH >= 4 ? 14 : 3);
     return sum_parts<NH>(src, P.x_ps, 0, NH, lane, tag, s, a);
   };
   // Philox blocks of steps t .. t+63 (both sub-tensors: counter (position, 2 u + s),
@@ -193,7 +197,7 @@ __device__ __forceinline__ void fused_head_role(const PersistArgs& a, int j, uns
   float cu = 0.0f, cr = 0.0f, ce = 0.0f, cie = 0.0f;
   auto coarse_pre = [&](uint32_t tag, float xc0, float xc1, int64_t t) {
     if (!gate) return;
-    __builtin_amdgcn_s_sleep(8);
+    __builtin_amdgcn_s_sleep(14);   // (after the draw wave's first probe; 8 and 20: 3% and 1% slower at H = 896)
     prefetch_coarse(t);
     const xw* ps[3] = {GA + u, GA + Hh + u, GA + 2 * Hh + u};
     float v[3];
@@ -224,7 +228,10 @@ __device__ __forceinline__ void fused_head_role(const PersistArgs& a, int j, uns
     fe = v[2];
     fie = last4(2);
   };
-  if (WR_LOCAL_XCHG) lx = leads_share_xcd(a.xc + P.x_xcc, P.NH, j, misc + 8, a);
+  if (WR_LOCAL_XCHG) {
+    lxa = group_shares_xcd(a.xc + P.x_xcc, P.NH + P.NU, j, misc + 8, a);
+    lx = lxa || group_shares_xcd(a.xc + P.x_xcc, P.NH, j, misc + 9, a);
+  }
   coarse_pre(1u, fscale(misc[4]), fscale(misc[5]), 0);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
@@ -249,7 +256,7 @@ __device__ __forceinline__ void fused_head_role(const PersistArgs& a, int j, uns
       const float e = ftanh(__builtin_fmaf(rr, ce, __builtin_fmaf(ic[2][3], xf1, __builtin_fmaf(ic[2][1], xf0, cie)) + cbe_c));
       hc = __builtin_fmaf(uu, hc, (1.0f - uu) * e);
       aput(imc + (u >> 5) * WR_FRAG, u & 31, hc);
-      if (u - HR * j < (unsigned)HR) xpub(YC + u, tag, hc);
+      if (u - HR * j < (unsigned)HR) xpub_l(YC + u, tag, hc, lxa);
     }
     __syncthreads();
     if (trw) trace_at(a, t, 1);
@@ -291,7 +298,7 @@ __device__ __forceinline__ void fused_head_role(const PersistArgs& a, int j, uns
       const float e = ftanh(__builtin_fmaf(rr, fe, __builtin_fmaf(ifn[2][4], xo, fie) + cbe_f));
       hf = __builtin_fmaf(uu, hf, (1.0f - uu) * e);
       aput(imf + (u >> 5) * WR_FRAG, u & 31, hf);
-      if (u - HR * j < (unsigned)HR) xpub(YF + u, tag, hf);
+      if (u - HR * j < (unsigned)HR) xpub_l(YF + u, tag, hf, lxa);
     }
     __syncthreads();
     if (trw) trace_at(a, t, 6);

@@ -439,10 +439,10 @@ wavernn_status check_coresident(wavernn_model* m, const void* k, int grid, int l
 
 
 // Grid s of n batch-1 grids side by side: heads and mirrors on XCD 8 s / n,
-// units spread over the XCDs.
+// units spread over the XCDs (fused: each grid whole on its XCD).
 PersistPlan fan_plan(const wavernn_model* m, int s, int n) {
   PersistPlan P = m->plan;
-  wr_place(&P, 8 * s / n, 255);
+  wr_place(&P, 8 * s / n, m->fused ? 1 << (8 * s / n) : 255);
   return P;
 }
 
@@ -609,6 +609,7 @@ wavernn_status build_fused(wavernn_model* m, const wavernn_weights* w) {
   if ((s = m->alloc(&m->d_cb, (size_t)m->cb_cap * 3 * H * 4)) != WAVERNN_OK) return s;
   if ((s = m->alloc(&m->d_xc, (size_t)(P.x_words + 1) / 2 * 8)) != WAVERNN_OK) return s;
   m->fused = true;
+  m->solo_uxm = 1 << m->solo_hx;   // the whole grid on one XCD
   return check_coresident(m, m->pk, P.grid, P.lds, "fused");
 }
 
@@ -2041,7 +2042,7 @@ wavernn_status wavernn_debug_sync_floor(wavernn_model* m, int64_t n_steps, doubl
 static void candidate_plan(const wavernn_model* m, int i, PersistPlan* P) {
   *P = m->plan;
   const int hx = i / 8, ux = i % 8;
-  wr_place(P, hx, ux == hx ? 255 : 1 << ux);
+  wr_place(P, hx, ux == hx && !m->fused ? 255 : 1 << ux);
 }
 
 // Does one launch of the candidate fit the device at once (every XCD holds its

@@ -80,7 +80,7 @@ WR_HD inline SmallLayout small_layout(int H) {
 #define WR_HROWS 64       // O1 / O3 rows per head workgroup (4 row tiles)
 #define WR_XALIGN 64      // exchange regions aligned to 64 words (512 B)
 #define WR_FRAG 1024      // bytes per MFMA fragment
-#define WR_MAXUCT 3       // coarse (and fine) row tiles per unit workgroup (waves 3, 7 stay free)
+#define WR_MAXUCT 3       // coarse (and fine) row tiles per unit workgroup of the dense plan (waves 3, 7 stay free)
 #define WR_MTILES 12      // coarse row tiles per mirror workgroup (3 Hh / 16 = 12 NH of them)
 
 struct PersistPlan {
@@ -216,7 +216,15 @@ WR_HD inline bool fused_plan(int H, PersistPlan* P) {
   if (!persist_plan(H, P)) return false;
   P->NM = P->mw_frags = P->lds_m = 0;             // no mirrors: single-buffered words
   P->x_hf = P->x_gfs = P->x_pfs = P->x_xcc = 0;
-  wr_place(P, 0, 255);
+  // units of 4 row tiles a half: 7 heads and 21 units at H = 896, so the whole
+  // grid fits one XCD's 32 CUs and every word stays in its L2 (the default
+  // placement; 28 units of 3 tiles spread over the XCDs: 4.34 against 4.02 us
+  // a step)
+  P->UCT = 4;
+  P->NU = P->NCT / P->UCT;
+  P->u_lds_w = 2 * P->UCT * P->KT * WR_FRAG;
+  P->lds_u = P->u_lds_w + 2 * P->KT * WR_FRAG + 4 * 16;
+  wr_place(P, 0, 1);
   P->hw_frags = 2 * P->KH + 2 * P->KO;
   // head LDS: y_c and y_f operand images (KT fragments each), relu image (KO),
   // first-layer partials [2][64], misc [16], uniforms [2][64][8], targets [2][64][2]
@@ -230,7 +238,7 @@ WR_HD inline bool fused_plan(int H, PersistPlan* P) {
   P->x_ps = 64;
   P->x_pc = take(P->NH * P->x_ps);
   P->x_pf = take(P->NH * P->x_ps);
-  P->x_xcc = take(P->NH);
+  P->x_xcc = take(P->NH + P->NU);
   P->x_words = o;
   P->lds = P->lds_h > P->lds_u ? P->lds_h : P->lds_u;
   return P->lds <= 160 * 1024;

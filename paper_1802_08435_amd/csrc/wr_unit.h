@@ -33,7 +33,8 @@ __device__ __forceinline__ int64_t fused_sample(const PersistArgs& a, int s, int
 // MR (mirrors form the coarse rows' fine-column products): a coarse wave
 // publishes its coarse columns' part (with bias + conditioning) as soon as
 // y_c is in and holds no fine columns; the fine rows' words go to the buffer
-// of their step's parity (wr_dbuf), since mirrors read them too.
+// of their step's parity (wr_dbuf), since mirrors read them too.  (The fused
+// plan has UCT = 4: waves 3 and 7, which read h, own row tiles too.)
 template <int KH, bool FUSED, bool MR = false>
 __device__ __forceinline__ void unit_role(const PersistArgs& a, int k, unsigned char* lds) {
   constexpr int KT = 2 * KH;
@@ -70,6 +71,8 @@ __device__ __forceinline__ void unit_role(const PersistArgs& a, int k, unsigned 
     aput(img + (i >> 5) * WR_FRAG, i & 31, y);
   }
   __syncthreads();
+  // fused: the whole grid on one XCD, words into its L2
+  const bool lx = FUSED && WR_LOCAL_XCHG && group_shares_xcd(a.xc + P.x_xcc, P.NH + P.NU, P.NH + k, misc + 1, a);
   f32x4 acc0, acc1;
   // columns [0, KT) of the image: coarse inputs
   auto phase_c = [&]() {
@@ -105,7 +108,7 @@ __device__ __forceinline__ void unit_role(const PersistArgs& a, int k, unsigned 
       float v = mfma_row(acc0) + mfma_row(acc1);
       if (g < 2) v += cbv;                      // bias + conditioning of the u and r gates
       if (MR) xpub(dst + wr_dbuf(s, P.x_gfs), wr_dtag(s, P.x_gfs), v);
-      else xpub(dst, (uint32_t)s + 1u, v);
+      else xpub_l(dst, (uint32_t)s + 1u, v, lx);
     }
   };
   __builtin_amdgcn_s_waitcnt(0);   // weights and operands are in before the loop (see head_role)
