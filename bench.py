@@ -341,8 +341,7 @@ def main() -> int:
         smed = float(np.median(sm))
         score = {"call_ms_median": round(smed, 4), "samples_per_s": round(S * T / (smed / 1000.0), 1),
                  "utterances": S, "us_per_step": round(smed * 1000.0 / T, 4),
-                 "kernels": ("wr_score_kernel (one grid per utterance)" if S <= 4 else
-                             "wr_score_multi (8 utterances per grid, 4 grids side by side)") +
+                 "kernels": "wr_score_kernel (one launch, groups of up to 8 utterances)"
                             " + wr_cnn_gemm (output layers over all steps) + wr_score_nll"}
     ms = float(np.mean(call_ms))
     samples = S * T

@@ -232,8 +232,9 @@ int64_t wavernn_schedule_steps(const wavernn_model* m, int64_t n_samples);
  * static device array of 16 MiB, kept until the process
  * ends, never in buffers the model grows.  A call needs, per launch, the
  * exchange words (under 64 KiB) plus n_frames * 3 * hidden * 4 bytes of table
- * (per utterance on the batched path; 2-4 concurrent utterances take one
- * launch each), each part rounded up to 256 bytes; a call that needs more
+ * (per utterance on the batched path; 2-4 concurrent utterances of a dense
+ * model take one launch each; other utterances on batch-1 grids run as many
+ * side by side as fit the workspace), each part rounded up to 256 bytes; a call that needs more
  * than 16 MiB fails with E_INVALID before anything is launched (WaveRNN-896
  * with 64-dim frames of 120 samples: up to about 1,500 frames, 7.5 s, per
  * utterance at batch 1).  The workspace is shared by every model and call on
@@ -254,11 +255,10 @@ wavernn_status wavernn_sample_noalloc(wavernn_model* m, int32_t n_streams, int64
  * sample and byte instead of 256 (high nibble 16, then low nibble 16), and
  * the NLL is the sum over the sample's four nibbles.  Initial state as in wavernn_sample.
  * n_samples = 0 is valid (target_dev may then be NULL): nothing is launched.
- * One utterance of a dense model on the multi-workgroup persistent path
- * (or several, one after another, on a model made for one) scores on a
- * recurrence-only kernel (with the bytes given, a step only updates h: one
- * exchange per step) and then runs the output layers over all steps as
- * matrix-core GEMMs.  That path keeps h of every step (4 H bytes per sample)
+ * The utterances of a dense model on the multi-workgroup persistent path score
+ * in one launch of a recurrence-only kernel (groups of up to 8 utterances; with
+ * the bytes given, a step only updates h: one exchange per step), and then the
+ * output layers run over all steps as matrix-core GEMMs.  That path keeps h of every step (4 H bytes per sample)
  * and the output layers' intermediates (4 (Hh rounded up to 128) + 2 KiB per
  * sample, for at most 65,536 samples at a time) in model-owned buffers, grown
  * the first time a longer call needs them; its initial state, conditioning
@@ -284,9 +284,10 @@ wavernn_status wavernn_debug_uniforms(uint64_t seed, uint64_t stream_id, int64_t
  * persistent kernel serves, and every subscale model), 3 persistent with
  * block-sparse R (Sec. 3.2; one launch per stream), 4 concurrent persistent
  * (2 to 4 streams of a dense model whose grids fit the device together: one
- * batch-1 launch per stream on internal streams forked from and joined back
- * into the caller's stream; bit-identical to path 1), 5 fused 2x persistent
- * (Sec. 4.4; one launch per stream).
+ * batch-1 launch per stream on internal streams, shared by the models of a
+ * device, forked from and joined back into the caller's stream; bit-identical
+ * to path 1), 5 fused 2x persistent (Sec. 4.4; one launch per stream, up to 4
+ * side by side in the same way when max_streams > 1).
  * Fills *grid and *block with the launch shape of one launch; -1 for a null
  * model. */
 int32_t wavernn_model_path(const wavernn_model* m, int32_t n_streams, int32_t* grid, int32_t* block);

@@ -82,7 +82,8 @@ __device__ __forceinline__ void cnn_split_put(uint16_t* x, int64_t m, int K, int
 // (8 lanes a 128-byte line of a split row).  The first version converted fp32
 // rows again for every tap and column tile, had one K-step on its way and read
 // the residual's old values one by one between the epilogue's stores.  24,000
-// rows at the paper's widths (22 GEMMs): 2.73 -> 1.95 ms; a sampling chunk's
+// rows at the paper's widths (22 GEMMs): 2.73 -> 1.65-1.95 ms over the devices
+// measured (350 to 296 TFLOP/s; twice that issued, high and low part); a sampling chunk's
 // GEMM of 700 rows: 12.8 -> 11.5 us, its 10 projections without a reduction.
 //
 // Workgroup b takes work item L = (b % 8) per_xcd + b / 8 (tile L mod tiles,

@@ -208,22 +208,3 @@ __device__ __forceinline__ bool wait_ok(WaitBudget& wb, const unsigned* err, u64
   }
   return true;
 }
-
-// ---------------------------------------------------------------------------
-// Wave64 reductions (xor butterflies through ds_swizzle / DPP via shfl).
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, 64));
-  return v;
-}
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  return v;
-}
-__device__ __forceinline__ int wave_max_i(int v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = max(v, __shfl_xor(v, m, 64));
-  return v;
-}

@@ -1696,7 +1696,7 @@ wavernn_status run(wavernn_model* m, RunIO& io, bool noalloc = false) {
   if (m->path == PATH_SMALL) return run_small(m, io);
   if (m->fused) return run_persist(m, io);
   if (m->path == PATH_PERSIST) {
-    // one utterance (or a model that runs its utterances one after another) scores on the recurrence kernel
+    // dense models score on the recurrence kernel, however many utterances and whichever path samples them
     if (io.target && m->score) return run_score(m, io);
     return io.S > std::max(m->nfan, 1) && m->has_batch ? run_batch(m, io) : run_persist(m, io);
   }
@@ -1825,7 +1825,7 @@ wavernn_status wavernn_create(const wavernn_config* cfg, const wavernn_weights* 
   const int B = cfg->subscale;
   if (cfg->fused) {
     // Fused Subscale WaveRNN 2x (Sec. 4.4): the batch-1 persistent structure
-    // with fused heads, one launch per utterance
+    // with fused heads, one grid per utterance, up to nfan side by side
     if (cfg->weight_dtype != WAVERNN_BF16)
       s = fail(WAVERNN_E_UNSUPPORTED, "fused 2x sampling needs bf16 weights");
     else if (!fused_plan(H, &m->plan))

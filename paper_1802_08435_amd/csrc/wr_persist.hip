@@ -93,7 +93,8 @@ __device__ __forceinline__ bool gather_partials(const PersistArgs& a, const xw* 
 // inputs) runs on waves 0-6 while wave 7 draws; the rest follows the draw.
 //  GU = 1 (Hh <= 448): thread u < Hh owns coarse unit u and fine unit Hh + u,
 //   its state in registers.
-//  GU > 1 (wide): waves 0-6 prepare the pre-activations of units tid + 448 m
+//  GU > 1 (wide): the pre-activations of the halves it serves are read four
+//   units to a 16-byte load by the threads that are not drawing (wide_words)
 //   into LDS, then all 8 waves finish units tid + 512 m; the state stays in
 //   LDS (registers are short with the larger O-layer slices).
 // All 8 waves run the MFMA layers; the draw wave (SPLIT: waves 6 and 7) gathers
