@@ -167,11 +167,11 @@ PHASES = {
                    (8, "O4 columns: partial fine logits published"),
                    (17, "fine partials of all heads received (draw wave)"), (18, "f_t drawn (draw wave)"),
                    (10, "next step's coarse gate words received (end of step)")],
-    "batched": [(11, "coarse gate words received"), (1, "coarse gates done, y_c of the group exchanged"),
-                (3, "O1/O2: partial coarse logits published"), (4, "owned vectors' coarse partials summed"),
-                (5, "c_t drawn"), (12, "fine gate words (groups of 2 and 4: read with the coarse ones) and classes received"),
+    "batched": [(11, "gate words of both halves received"), (1, "coarse gates done, y_c of the group exchanged"),
+                (3, "O1/O2: partial coarse logits published"), (4, "coarse partials of all heads summed"),
+                (5, "c_t drawn"),
                 (6, "fine gates done, y_f of the group exchanged"), (8, "O3/O4: partial fine logits published"),
-                (9, "owned vectors' fine partials summed"), (10, "f_t drawn (end of step)")],
+                (9, "fine partials of all heads summed"), (10, "f_t drawn (end of step)")],
 }
 PHASES["block-sparse"] = [(1, "coarse gates (Eq. 2, with f_{t-1}) done, own y_c slice published"),
                           (2, "O1 rows + relu"), (3, "O2 columns: partial coarse logits published"),
