@@ -337,14 +337,24 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
       all_load(pending);
     }
   };
+  // This head's slice of y_c, for the units: behind the barrier that follows
+  // the gates, so that every unit's words of the step are in.  A unit publishes
+  // its words of step t + 1 only after reading all of h of step t, so the slice
+  // of step t may be replaced then, and not sooner: the publishing wave itself
+  // reads the words of three unit workgroups, and another unit may
+  // still have y_c of step t to read.  (y_f follows that barrier anyway.)
+  auto publish_yc = [&](uint32_t tag) {
+    if (!mine) return;
+#pragma unroll
+    for (int b = 0; b < AL; ++b) xpub_l(YC + b * Hh + u, tag, FL ? 0.0f : hcs[b * 448 + u], lx);
+  };
   // the gates of unit u of one half, every vector
   auto all_gates = [&](auto fine_, uint32_t tag, uint32_t actm) {
     constexpr bool fine = decltype(fine_)::value;
-    xw* Y = fine ? YF : YC;
 #pragma unroll
     for (int b = 0; b < AL; ++b) {
       if (FL) {
-        if (mine) xpub_l(Y + b * Hh + u, tag, 0.0f, lx);
+        if (fine && mine) xpub_l(YF + b * Hh + u, tag, 0.0f, lx);
         continue;
       }
       auto word = [&](int r) {                     // pair r of this half, vector b of it
@@ -373,23 +383,25 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
       const float hn = actm >> b & 1u ? __builtin_fmaf(uu, *hs, (1.0f - uu) * e) : *hs;   // idle: state kept
       *hs = hn;
       aput_p(fine ? imf : imc, u, hn, b);
-      if (mine) xpub_l(Y + b * Hh + u, tag, hn, lx);   // this head's slice, for the units
+      if (fine && mine) xpub_l(YF + b * Hh + u, tag, hn, lx);   // this head's slice, for the units
     }
   };
   // SLICE: one (unit, vector) pair per thread.  Its three pre-activation
   // words of each half (the units publish both halves at once), the e gates'
-  // context terms (subscale), and the first word unit k = tid publishes: a
+  // context terms (subscale), and the first word unit k = lane publishes: a
   // unit publishes its words of step t + 1 only after reading all of h of
   // step t, so once every unit's word has arrived this head may replace its
-  // slices of y of step t.  One poll at the start of a step, its first probe
+  // slices of y of step t.  Every wave waits for all of them, since each
+  // publishes its part of y_c without a barrier (y_f follows one).  One poll at
+  // the start of a step, its first probe
   // issued before the fine draw (`pw`): the fine gates then wait only for c_t.
   // Words 0-2 coarse gates, 3-5 fine gates, 6 and 7 context terms, 8 unit flag.
   constexpr int NW = 9;
-  const uint32_t wneed = 63u | (CTX ? 192u : 0u) | (SLICE && tid < P.NU ? 256u : 0u);
+  const uint32_t wneed = 63u | (CTX ? 192u : 0u) | (SLICE && lane < P.NU ? 256u : 0u);
   const uint32_t so = (uint32_t)(su * L + sb);
   uint32_t uflag = 0;
-  if (SLICE && tid < P.NU) {
-    const int tile = tid * WR_BUCT, gt = tile / (HH / 16);
+  if (SLICE && lane < P.NU) {
+    const int tile = lane * WR_BUCT, gt = tile / (HH / 16);
     uflag = (uint32_t)(P.x_ga + (gt * HH + 16 * (tile % (HH / 16))) * L);
   }
   xw pw[NW] = {};
@@ -419,10 +431,11 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
       if (!pending) break;
       if (!wait_ok(wb, a.err, a.limit, a.err)) {
         misc[0] = 1;
-        return;
+        break;
       }
       slice_load(pending);
     }
+    __builtin_amdgcn_wave_barrier();               // every lane's words before any lane publishes
   };
   auto slice_gates = [&](bool fine, uint32_t tag, int64_t t, uint32_t actm) {
     float* hs = (fine ? hfs : hcs) + sb * 448 + su;
@@ -533,6 +546,7 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
     }
     __syncthreads();
     if (misc[0]) return;
+    if (!SLICE) publish_yc(tag);
     if (trw) trace_at(a, t, 1);
     // (2) O1 rows, relu, O2 columns -> partial coarse logits of 8 vectors
     first_layer(W1, imc, b1r);
