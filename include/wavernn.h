@@ -229,13 +229,14 @@ int64_t wavernn_schedule_steps(const wavernn_model* m, int64_t n_samples);
  * forbid hipMalloc).  Same arguments, kernels and results as wavernn_sample
  * (bit for bit), but the exchange words and the per-frame bias + conditioning
  * tables of the call live in a workspace the library holds per device: a
- * static device array of 16 MiB, kept until the process
+ * static device array of 16 MiB and 64 KiB, kept until the process
  * ends, never in buffers the model grows.  A call needs, per launch, the
- * exchange words (under 64 KiB) plus n_frames * 3 * hidden * 4 bytes of table
+ * exchange words (up to about 100 KiB for a batch-1 grid, 2 MiB for the batched kernel)
+ * plus n_frames * 3 * hidden * 4 bytes of table
  * (per utterance on the batched path; 2-4 concurrent utterances of a dense
  * model take one launch each; other utterances on batch-1 grids run as many
  * side by side as fit the workspace), each part rounded up to 256 bytes; a call that needs more
- * than 16 MiB fails with E_INVALID before anything is launched (WaveRNN-896
+ * than the workspace holds fails with E_INVALID before anything is launched (WaveRNN-896
  * with 64-dim frames of 120 samples: up to about 1,500 frames, 7.5 s, per
  * utterance at batch 1).  The workspace is shared by every model and call on
  * the device and keeps the last call's contents (each call clears what must

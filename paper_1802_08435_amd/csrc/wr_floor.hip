@@ -8,8 +8,8 @@
 // the heads and publishes its gate words for the next step.  With mirrors
 // (the dense plan) each mirror waits for the coarse partials, publishes its
 // words of the coarse rows for the next step and waits for the fine partials;
-// the heads wait for those words at the start of a step, and the fine words
-// and fine partials sit in the sampling kernel's two buffers; the partials and
+// the heads wait for those words at the start of a step, and the words that
+// the sampling kernel double-buffers sit in its two buffers; the partials and
 // the mirrors' words stay in the L2 of the leads' XCD when all leads share
 // one, as in the sampling kernels.  The time per
 // step of this kernel is what the exchange pattern alone costs (Sec. 2.1 of
@@ -78,10 +78,13 @@ __device__ __forceinline__ void floor_head(const PersistArgs& a, int j, unsigned
     const uint32_t tag = (uint32_t)(t + 1);
     if (coarse) mirror_words(tag);
     if (coarse && wave == 7)
-      for (int i = lane; i < HR; i += 64) xpub(YC + HR * jk + i, tag, 0.0f);
-    if (coarse && lane < 32) xpub_l(PC + (size_t)jk * P.x_ps + 32 * wave + lane, tag, 0.0f, lx);
+      for (int i = lane; i < HR; i += 64)
+        xpub(YC + wr_dbuf(t, P.x_ycs) + HR * jk + i, wr_dtag(t, P.x_ycs), 0.0f);
+    xw* PCt = PC + wr_dbuf(t, P.x_pcs);
+    const uint32_t ctag = wr_dtag(t, P.x_pcs);
+    if (coarse && lane < 32) xpub_l(PCt + (size_t)jk * P.x_ps + 32 * wave + lane, ctag, 0.0f, lx);
     if (coarse) gate_words(GA);   // (read while the partials are exchanged, as the sampling heads prefetch)
-    gather(PC, tag);
+    gather(PCt, ctag);
     __syncthreads();
     if (misc[0]) return;
     if (fine && wave == 7)
@@ -204,7 +207,7 @@ __device__ __forceinline__ void floor_unit(const PersistArgs& a, int k, unsigned
   publish_f(0);
   for (int64_t t = 0; t + 1 < a.T; ++t) {
     const uint32_t tag = (uint32_t)(t + 1);
-    gather_half(YC, tag, true);
+    gather_half(YC + wr_dbuf(t, P.x_ycs), wr_dtag(t, P.x_ycs), true);
     if (misc[0]) return;
     if (P.NM) publish_c(t + 1);                  // with mirrors: the coarse columns' part once y_c is in
     gather_half(YF, tag, false);

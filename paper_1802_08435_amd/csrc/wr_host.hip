@@ -1710,7 +1710,7 @@ wavernn_status run(wavernn_model* m, RunIO& io, bool noalloc = false) {
 // runs the library holds its own copy until the process ends).  Host code
 // never uses the array's name as an address: the device address is looked up
 // once per device with hipGetSymbolAddress and kept in g_scratch.
-#define WR_SCRATCH_BYTES ((size_t)16 << 20)
+#define WR_SCRATCH_BYTES (((size_t)16 << 20) + ((size_t)64 << 10))   // (room for the block-sparse kernel's second buffers)
 static __device__ __align__(256) uint64_t scratch[WR_SCRATCH_BYTES / 8];
 
 namespace {

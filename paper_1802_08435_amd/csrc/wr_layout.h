@@ -104,11 +104,13 @@ struct PersistPlan {
   int x_ps;               // words between the partial-logit blocks of consecutive heads
   int x_gfs, x_pfs;       // with mirrors the fine rows' words and the fine partial logits are
                           // double-buffered by step parity: words between the two buffers (0: one)
+  int x_ycs, x_pcs;       // block-sparse: so are y_c and the coarse partial logits (and the fine ones)
   int lds_h, lds_u, lds_m, lds;  // LDS bytes
 };
 
 // Double-buffered words of step s (the fine rows' pre-activations and the fine
-// partial logits when mirrors read them too): buffer s mod 2, tagged with the
+// partial logits when mirrors read them too; y_c and both halves' partial
+// logits of the block-sparse kernel): buffer s mod 2, tagged with the
 // parity of the buffer's generation s / 2 + 1.  A writer of step s + 2 has
 // waited, through its own inputs, for every reader of step s (see the head
 // and mirror roles), and the generation bit tells step s from step s - 2.
@@ -169,6 +171,7 @@ WR_HD inline bool persist_plan(int H, PersistPlan* P) {
   P->NCT = 3 * P->Hh / 16;
   if (P->NH > 16 || P->Hh > WR_THREADS - 64) return false;   // the last wave draws, free of gate work
   P->NM = P->NCT / WR_MTILES;                                 // = NH
+  P->x_ycs = P->x_pcs = 0;
   P->mw_frags = 3 * (P->KT / 2);
   P->hw_frags = 2 * P->KH + 8;
   // head LDS: y_c and y_f operand images (KT fragments each), relu image (2),
@@ -296,8 +299,8 @@ WR_HD inline bool sparse_plan(int H, int SR, int BH, int BW, int NRC, int NRF, P
   P->UCT = 0;
   P->NCT = 3 * P->Hh / 16;
   P->NU = 3 * H / SR;
-  P->NM = P->mw_frags = P->lds_m = 0;             // no mirrors: single-buffered words
-  P->x_hf = P->x_gfs = P->x_pfs = P->x_xcc = 0;
+  P->NM = P->mw_frags = P->lds_m = 0;             // no mirrors
+  P->x_hf = P->x_gfs = P->x_xcc = 0;
   P->hw_frags = P->KH + 2 * P->KO;
   // head LDS: operand image (KT + KO fragments), first-layer partials
   // [KC][HR], logit sums [2][256], logits [256], then y [Hh] (GU = 1) or
@@ -314,13 +317,19 @@ WR_HD inline bool sparse_plan(int H, int SR, int BH, int BW, int NRC, int NRF, P
   wr_place(P, 0, 255);
   int o = 0;
   auto take = [&](int n) { int r = o; o += wr_rup(n, WR_XALIGN); return r; };
-  P->x_yc = take(P->Hh);
+  // Two buffers for y_c and the partial logits: a head runs on once the other
+  // half's heads have followed it, and another head of its own half may
+  // still read its partials, or a unit of the other half's rows its y_c (see
+  // the sparse heads).
+  P->x_ycs = wr_rup(P->Hh, WR_XALIGN);
+  P->x_yc = take(2 * P->x_ycs);
   P->x_yf = take(P->Hh);
   P->x_ga = take(3 * P->Hh);
   P->x_gf = take(3 * P->Hh);
   P->x_ps = 256;
-  P->x_pc = take(P->NK * P->x_ps);
-  P->x_pf = take(P->NK * P->x_ps);
+  P->x_pcs = P->x_pfs = P->NK * P->x_ps;
+  P->x_pc = take(2 * P->x_pcs);
+  P->x_pf = take(2 * P->x_pfs);
   P->x_xcc = take(P->NH);
   P->x_words = o;
   P->lds = P->lds_h > P->lds_u ? P->lds_h : P->lds_u;

@@ -100,6 +100,12 @@ __device__ __forceinline__ bool gather_partials(const PersistArgs& a, const xw* 
 // All 8 waves run the MFMA layers; the draw wave (SPLIT: waves 6 and 7) gathers
 // the partial logits; the gate threads of this head's slice of units publish it for
 // the unit workgroups.
+// SPLIT heads double-buffer y_c and the partial logits: a unit's gate words are
+// read by the heads of one half only, so a coarse head that starts step
+// s + 1 knows that the fine heads have read its partials of step s, but not that
+// the other coarse heads have, nor that the fine rows' units have read its y_c;
+// fine heads and their partials likewise.  By step s + 2 all of them have (a CPU
+// model of the exchange checks this).
 // MR (mirrors, dense GU = 1 only): a coarse gate's pre-activation is the
 // units' coarse-column word plus the mirrors' fine-column word, and the fine
 // rows' words and the fine partial logits are double-buffered by step parity.
@@ -214,6 +220,8 @@ __device__ __forceinline__ void head_role(const PersistArgs& a, int j, unsigned 
   const xw* HF = a.xc + P.x_hf;
   const xw* PC = a.xc + P.x_pc;
   const xw* PF = a.xc + P.x_pf;
+  constexpr int YCS = SPLIT ? (Hh + WR_XALIGN - 1) / WR_XALIGN * WR_XALIGN : 0, PCS = SPLIT ? NK * 256 : 0;   // x_ycs, x_pcs
+  const int pfs = SPLIT ? PCS : P.x_pfs;
   const int rt = wave % RT, kc = wave / RT;        // first layer: row tile, column-tile chunk
   // GU = 1: pre-activation words of this thread's units, loaded ahead (MR:
   // the units' three, then the mirrors' three of the coarse half)
@@ -463,8 +471,10 @@ __device__ __forceinline__ void head_role(const PersistArgs& a, int j, unsigned 
     const int bs = (int)((t >> 6) & 1) * 64 + (int)(t & 63);   // this step in the batch buffers
     if (wave == DW && (t & 63) == 0) fill_batch(t + 64, (int)(((t >> 6) + 1) & 1));
     // (1) coarse gates of every unit, finished with f_{t-1}
+    xw* YCt = YC + wr_dbuf(t, YCS);
+    const uint32_t ctag = wr_dtag(t, YCS);           // y_c and coarse partials of this step
     if (WIDE) {
-      if (coarse) wide_gates(fscale(misc[3]), 1, yv, imc, YC, tag);
+      if (coarse) wide_gates(fscale(misc[3]), 1, yv, imc, YCt, ctag);
     } else if (gate && coarse) {
       const float x1 = fscale(misc[3]);
       const float uu = fsig(__builtin_fmaf(ic[0][1], x1, cu)), rr = fsig(__builtin_fmaf(ic[1][1], x1, cr));
@@ -472,23 +482,24 @@ __device__ __forceinline__ void head_role(const PersistArgs& a, int j, unsigned 
       hc = __builtin_fmaf(uu, hc, (1.0f - uu) * e);
       aput(imc + (u >> 5) * WR_FRAG, u & 31, hc);
       yv[u] = hc;
-      if (u - HR * jk < (unsigned)HR) xpub(YC + u, tag, hc);   // this head's slice, for the units
+      if (u - HR * jk < (unsigned)HR) xpub(YCt + u, ctag, hc);   // this head's slice, for the units
     }
     __syncthreads();
     if (trw) trace_at(a, t, 1);
     if (trw) trace_at(a, t, 19);
     // (2) own rows of O1 -> relu -> own columns of O2 -> partial coarse logits
+    const int pcb = wr_dbuf(t, PCS);
     if (coarse) {
       first_layer(W1, imc, b1r);
       if (trw) trace_at(a, t, 2);
-      second_layer(W2, PCo, tag);
+      second_layer(W2, PCo + pcb, ctag);
       if (trw) trace_at(a, t, 3);
     }
     if (j == NH - 1 && tid == WR_THREADS - 64) trace_at(a, t, 13);
     if (j > 0 && j < 8 && tid == WR_THREADS - 64) trace_at(a, t, 24 + j);
     // (3) coarse logits of all heads; this step's fine words are loaded
     if (SPLIT) {
-      gather_logits(PC, tag);
+      gather_logits(PC + pcb, ctag);
       if (trw) trace_at(a, t, 15);
     }
     if (t > 0) prefetch_fine(t);
@@ -545,18 +556,18 @@ __device__ __forceinline__ void head_role(const PersistArgs& a, int j, unsigned 
     if (fine) {
       if (SPLIT) {
         first_layer(W1, imf, b3r);
-        second_layer(W2, PFo + wr_dbuf(t, P.x_pfs), wr_dtag(t, P.x_pfs));
+        second_layer(W2, PFo + wr_dbuf(t, pfs), wr_dtag(t, pfs));
       } else {
         first_layer(W3, imf, b3r);
         if (trw) trace_at(a, t, 7);
-        second_layer(W4, PFo + wr_dbuf(t, P.x_pfs), wr_dtag(t, P.x_pfs));
+        second_layer(W4, PFo + wr_dbuf(t, pfs), wr_dtag(t, pfs));
         if (trw) trace_at(a, t, 8);
       }
     }
     if (j == NH - 1 && tid == WR_THREADS - 64) trace_at(a, t, 14);
     // (7) fine logits of all heads
     if (SPLIT) {
-      gather_logits(PF + wr_dbuf(t, P.x_pfs), wr_dtag(t, P.x_pfs));
+      gather_logits(PF + wr_dbuf(t, pfs), wr_dtag(t, pfs));
       if (trw) trace_at(a, t, 17);
       __syncthreads();
       if (misc[0]) return;
@@ -571,7 +582,7 @@ __device__ __forceinline__ void head_role(const PersistArgs& a, int j, unsigned 
         f = draw_wave(zs, zs2, b4l, uni[bs].y, forced, zk, a.nll_out ? &lse : nullptr);
       } else {
         float4 z;
-        if (!gather_wave(PF + wr_dbuf(t, P.x_pfs), wr_dtag(t, P.x_pfs), &z)) misc[0] = 1;
+        if (!gather_wave(PF + wr_dbuf(t, pfs), wr_dtag(t, pfs), &z)) misc[0] = 1;
         if (trw) trace_at(a, t, 17);
         f = draw_z(z, b4l, uni[bs].y, forced, zk, a.nll_out ? &lse : nullptr);
       }
@@ -905,7 +916,7 @@ __device__ __forceinline__ void sparse_unit_role(const PersistArgs& a, int k, un
   for (int64_t t = 0; t + 1 < a.T; ++t) {
     const uint32_t tag = (uint32_t)(t + 1);
     const float cbv = lead && g < 2 ? cb_row(a, a.t0 + t + 1)[row] : 0.0f;
-    gather_half(YC, tag, hv, true);
+    gather_half(YC + wr_dbuf(t, P.x_ycs), wr_dtag(t, P.x_ycs), hv, true);
     if (misc[0]) return;
     phase_c();
     gather_half(YF, tag, hv + Hh, false);
