@@ -241,9 +241,10 @@ __global__ __launch_bounds__(CNN_THREADS, 2) void wr_cnn_gemm(CnnGemmArgs a) {
 
 // Split GEMMs: out = ((part[0] + part[1]) + part[2]) + ... + bias, then the
 // epilogue, as wr_cnn_gemm's own when one workgroup runs every group.  Thread
-// (x, y): columns 4 x .. +3 of row 4 blockIdx.x + y.
+// (x, y): columns 4 (32 blockIdx.y + x) .. +3 of row 8 blockIdx.x + y, so a
+// block has 256 threads whatever N.
 __global__ void wr_cnn_reduce(CnnGemmArgs a) {
-  const int m = blockIdx.x * blockDim.y + threadIdx.y, n = 4 * threadIdx.x;
+  const int m = blockIdx.x * blockDim.y + threadIdx.y, n = 4 * (blockIdx.y * blockDim.x + threadIdx.x);
   const int64_t dm = cnn_dst_row(a, m);
   if (dm < 0) return;
   const float* p = a.part + (size_t)m * a.N + n;

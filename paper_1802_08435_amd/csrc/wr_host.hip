@@ -972,7 +972,8 @@ wavernn_status cnn_gemm(const wavernn_model* m, const uint16_t* src, int kin, in
   g.per_xcd = (g.tiles * g.split + 7) / 8;
   void* args[] = {&g};
   HIPOK(hipLaunchKernel(wr_cnn_gemm_ptr(mi), dim3(8 * g.per_xcd), dim3(CNN_THREADS), args, 0, st));
-  if (g.split > 1) HIPOK(hipLaunchKernel(wr_cnn_reduce_ptr(), dim3((M + 3) / 4), dim3(N / 4, 4), args, 0, st));
+  if (g.split > 1)
+    HIPOK(hipLaunchKernel(wr_cnn_reduce_ptr(), dim3((M + 7) / 8, N / CNN_TN), dim3(CNN_TN / 4, 8), args, 0, st));
   return WAVERNN_OK;
 }
 

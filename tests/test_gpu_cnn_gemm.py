@@ -1,6 +1,7 @@
 """The conditioning CNN's GEMMs at the edges of their tiles: row counts around 64, 96 and 128 and around
 the switch between one workgroup per tile and one per group of the K loop, taps past the utterance's end,
-several utterances, residual and convolution widths that differ.  Against the oracle's network."""
+several utterances, residual and convolution widths that differ and exceed a workgroup's threads.  Against the
+oracle's network."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,7 @@ from paper_1802_08435_amd import synth, wavernn  # noqa: E402
 
 @pytest.mark.parametrize("rows,S,Rc,Cc,layers", [(1, 1, 128, 128, 10), (16, 1, 256, 128, 2), (25, 1, 128, 256, 3),
                                                  (33, 2, 640, 128, 2), (260, 1, 768, 128, 2), (1000, 1, 128, 128, 2),
-                                                 (5500, 1, 128, 128, 1)])
+                                                 (5500, 1, 128, 128, 1), (30, 1, 512, 1152, 1), (9, 1, 1152, 1408, 2)])
 def test_cnn_rows_against_the_oracle(rows, S, Rc, Cc, layers):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
