@@ -1199,7 +1199,7 @@ wavernn_status launch_cond(const wavernn_model* m, const float* feat, int64_t n_
   a.n_words = (n_words + 1) / 2;
   a.x_stride = x_stride;
   void* args[] = {&a};
-  const dim3 grid((unsigned)((a.rows + 255) / 256), (unsigned)((a.nf + WR_COND_FRAMES - 1) / WR_COND_FRAMES),
+  const dim3 grid((unsigned)((a.nf + WR_COND_FRAMES - 1) / WR_COND_FRAMES), (unsigned)((a.rows + 255) / 256),
                   (unsigned)n_streams);
   HIPOK(hipLaunchKernel(wr_cond_kernel_ptr(), grid, dim3(256), args, (size_t)a.Dc * WR_COND_FRAMES * 4, st));
   return WAVERNN_OK;

@@ -947,13 +947,14 @@ __global__ __launch_bounds__(WR_THREADS, 1) void wr_sparse_kernel(PersistArgs a)
 extern "C" __global__ __launch_bounds__(256) void wr_cond_kernel(CondArgs a) {
   extern __shared__ __align__(16) float xf[];        // [Dc][WR_COND_FRAMES] features of this workgroup's frames
   constexpr int NF = WR_COND_FRAMES;
-  const int tid = threadIdx.x, row = blockIdx.x * 256 + tid, s = blockIdx.z;
+  // grid x: groups of frames (their number has no small limit), y: rows, z: streams
+  const int tid = threadIdx.x, row = blockIdx.y * 256 + tid, s = blockIdx.z;
   if (a.words) {
     u64* w = (u64*)(a.words + s * a.x_stride);
     const int64_t n = (int64_t)gridDim.x * gridDim.y * 256;
     for (int64_t i = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + tid; i < a.n_words; i += n) w[i] = 0;
   }
-  const int64_t f0 = a.f0 + (int64_t)blockIdx.y * NF;
+  const int64_t f0 = a.f0 + (int64_t)blockIdx.x * NF;
   const int nf = (int)(a.f0 + a.nf - f0 < NF ? a.f0 + a.nf - f0 : NF);
   for (int i = tid; i < a.Dc * NF; i += 256) {
     const int f = i / a.Dc, q = i % a.Dc;

@@ -37,3 +37,22 @@ def test_groups_equal_one_at_a_time(H, S, T, frame):
     ref = O.run(O.Weights.from_dict(w, bf16=True), 1, T, feat=feat[:1], target=tgt[:1], logits=True)
     assert np.abs(many["zc"][0].cpu().numpy() - ref["zc"][0]).max() <= 1e-3
     assert np.abs(many["zf"][0].cpu().numpy() - ref["zf"][0]).max() <= 1e-3
+
+
+def test_one_frame_a_sample_over_half_a_million_frames():
+    """More than 2^16 groups of 8 frames in one call: frames of one sample with repeated features score as
+    longer frames do."""
+    T, L = 525_000, 50
+    w = synth.make_weights(128, seed=4, cond_dim=4)
+    feat = synth.features(1, T, cond_dim=4, frame_len=L)
+    tgt = cuda(synth.target_signal(1, T, seed=3, kind="uniform"))
+    nll = {}
+    for n in (L, 1):
+        w["frame_len"] = n
+        f = np.repeat(feat, L // n, axis=1)
+        assert f.shape[1] * n == T and (n > 1 or f.shape[1] > 8 * 65536)
+        m = wavernn.Model(w)
+        nll[n] = m.score(tgt, cond=cuda(f), logits=False)["nll"]
+        m.device_status()
+        m.close()
+    assert torch.equal(nll[1], nll[L])
