@@ -61,7 +61,10 @@ constexpr int PATH_SPARSE_ID = 3, PATH_CONCURRENT_ID = 4, PATH_FUSED_ID = 5;   /
 // queue, and one of the 4 grids ran after another (4 utterances x 9,613 among
 // three models: 49.2 ms a call, 37.3 with shared streams; one model: 37.2).
 // Created with the first model that uses them (default priority), destroyed
-// with the last one.
+// with the last one.  mu() is held from a call's fork to its join.  A call that is
+// being captured into a graph uses streams of its own model instead: a stream
+// that has joined a capture stays in it until the capture ends, and another
+// model's call in between would be recorded into the same graph or refused.
 struct FanStreams {
   hipStream_t st[WR_FAN - 1] = {};
   int refs = 0;
@@ -98,6 +101,16 @@ struct FanStreams {
     }
   }
 };
+
+// Is the stream being captured into a graph?
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &c) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return c != hipStreamCaptureStatusNone;
+}
 
 const u64 kWaitTicks = 200000000ull;  // 2 s of the 100 MHz clock per wait
 
@@ -147,6 +160,7 @@ struct wavernn_model {
   // a few utterances side by side, each on its own batch-1 grid and stream, all grids co-resident at once
   int nfan = 0;                      // most utterances served this way (0: none)
   const hipStream_t* fan_st = nullptr;   // streams of grids 1 .. (FanStreams); grid 0 runs on the caller's stream
+  hipStream_t cap_st[WR_FAN - 1] = {};   // the same for captured calls, created with the first one
   hipEvent_t fan_fork = nullptr, fan_join[WR_FAN - 1] = {};
   xw* d_fxc = nullptr;               // exchange words [nfan][x_words]
   float* d_fcb = nullptr;            // [nfan][frames][3H] bias + conditioning
@@ -203,6 +217,8 @@ struct wavernn_model {
     for (hipEvent_t e : fan_join)
       if (e) (void)hipEventDestroy(e);
     if (fan_fork) (void)hipEventDestroy(fan_fork);
+    for (hipStream_t q : cap_st)
+      if (q) (void)hipStreamDestroy(q);
     if (fan_st) FanStreams::release(device);
     for (void* q : allocs) (void)hipFree(q);
   }
@@ -1381,12 +1397,23 @@ wavernn_status launch_persist(wavernn_model* m, const RunIO& io, int s, int n, x
   wavernn_status c = launch_cond(m, feat, n_cb, first_frame(m, io), last_frame(m, io), n, cb, cb_stride, xc,
                                  m->plan.x_words, x_stride, io.st);
   if (c != WAVERNN_OK) return c;
-  if (n > 1) HIPOK(hipEventRecord(m->fan_fork, io.st));
+  const hipStream_t* side = m->fan_st;
+  std::unique_lock<std::mutex> lock(FanStreams::mu(), std::defer_lock);
+  if (n > 1) {
+    if (capturing(io.st)) {
+      for (int i = 0; i + 1 < n; ++i)
+        if (!m->cap_st[i]) HIPOK(hipStreamCreateWithFlags(&m->cap_st[i], hipStreamNonBlocking));
+      side = m->cap_st;
+    } else {
+      lock.lock();
+    }
+    HIPOK(hipEventRecord(m->fan_fork, io.st));
+  }
   for (int i = n - 1; i >= 0; --i) {   // the caller's stream last
     const PersistPlan P = n > 1 ? fan_plan(m, i, n) : solo_plan(m);
     PersistArgs a = persist_args(m, io, s + i, P, xc + i * x_stride, cb + i * cb_stride, n_cb);
     void* args[] = {&a};
-    const hipStream_t st = i ? m->fan_st[i - 1] : io.st;
+    const hipStream_t st = i ? side[i - 1] : io.st;
     if (i) HIPOK(hipStreamWaitEvent(st, m->fan_fork, 0));
     // An ordinary launch: create() checked that the whole grid fits on the
     // device at once, and every cross-workgroup wait is bounded, so a grid
