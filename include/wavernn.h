@@ -33,8 +33,20 @@
  *    call of a model uses the model's own exchange words, per-frame tables and
  *    error word, so two calls of one model whose GPU work overlaps (on two
  *    streams, or from two threads) race and may time out or corrupt each
- *    other; calls queued on one stream are safe.  Separate models are
- *    independent.
+ *    other; calls queued on one stream are safe.
+ *  - Separate models are independent: no call writes what another model's call
+ *    reads (the workspace of wavernn_sample_noalloc aside).  Calls of several
+ *    models on streams of their own run side by side where the workgroups they
+ *    keep on each XCD's 32 CUs fit together; a call moves to other XCDs for that
+ *    if it must (results do not depend on it), and if it fits nowhere beside the
+ *    calls in flight, it waits on its stream for the oldest of them.  At H = 896 a
+ *    fused utterance and each group of a scoring or batched call keep 28 CUs of one
+ *    XCD, a plain utterance 14 of one and 3 or 4 of the others: a plain and
+ *    a fused or scored utterance run together, two plain utterances side by side
+ *    and a fused one do not.  Calls captured into a graph are outside this: they
+ *    are placed by the order in which the models were created (the first
+ *    eight models' one-XCD grids on an XCD each), and a replay that does not fit
+ *    beside what else runs may end with an expired wait.
  *  - A failure a kernel flags (a bounded wait that expired) stays recorded in
  *    the model's error word: the launch that flagged it ends early, and every
  *    later launch of the model ends at the first wait that has to spin (the
@@ -297,13 +309,15 @@ int32_t wavernn_model_path(const wavernn_model* m, int32_t n_streams, int32_t* g
  * (paths 1, 3 and 5 of wavernn_model_path) among the 8 XCDs of the device.
  * Workgroups exchange values every step through memory, and the latency of
  * an exchange depends on where producer and consumer sit, in ways that
- * differ from device to device.  Candidate i (0 <= i < 64) puts the head
+ * differ from device to device.  (XCDs are numbered as the device does, whatever
+ * stream a call uses.)  Candidate i (0 <= i < 64) puts the head
  * workgroups on XCD hx = i / 8 and the unit workgroups on XCD ux = i % 8
  * (ux == hx: the units spread over every XCD, or on path 5 beside the heads;
  * candidate 0 is the default).
  * A candidate fits when every workgroup of one launch can be resident at
  * once; only launches that run one at a time use the placement (the
- * concurrent launches of path 4 keep the default).  Results do not depend
+ * concurrent launches of path 4 keep the default, and a launch beside another
+ * model's may be moved by some XCDs, heads and units alike).  Results do not depend
  * on the placement: only the time per step does.
  *
  * wavernn_tune: times `rounds` (1..16) rounds of one sampling launch of

@@ -81,6 +81,7 @@ struct ScoreArgs {
   int64_t n_cb;
   int frame_len;
   int S, G;
+  int rot, by_xcd;          // group g on XCD (g + rot) mod 8; as PersistPlan's
   int64_t T, t0;
   const uint16_t* target;   // [S][T]
   const float* h_in;        // [H] or null
@@ -231,6 +232,7 @@ const void* wr_batch_kernel_ptr(int KH, bool ctx, int L, bool lag);   // null if
                                                                       // per group, lag: a future-horizon schedule)
 const void* wr_batch_floor_kernel_ptr(int KH, bool ctx, int L, bool lag);   // null if no instantiation
 const void* wr_fill_kernel_ptr();
+const void* wr_xcd_kernel_ptr();             // out[b] = the XCD of block b
 const void* wr_fused_kernel_ptr(int KH);     // null if no instantiation
 const void* wr_floor_kernel_ptr();
 const void* wr_cnn_gemm_ptr(int MI);         // tiles of 32 MI rows, MI 2 .. 4

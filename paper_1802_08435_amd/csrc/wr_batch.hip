@@ -939,7 +939,7 @@ template <int KH, bool CTX, int L, bool LAG, bool FL>
 __global__ __launch_bounds__(WR_THREADS, 1) void wr_batch_kernel(BatchArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
   int g = 0;
-  const int r = wr_batch_role(a.P, blockIdx.x, &g);
+  const int r = wr_batch_role(a.P, wr_block(a.P.by_xcd), &g);
   if (r < 0) return;
   if (r < a.P.NH) bhead_role<KH, CTX, L, LAG, FL>(a, g, r, lds);
   else bunit_role<KH, CTX, L, LAG, FL>(a, g, r - a.P.NH, lds);

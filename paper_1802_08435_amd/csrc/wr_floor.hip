@@ -221,7 +221,7 @@ __device__ __forceinline__ void floor_unit(const PersistArgs& a, int k, unsigned
 
 __global__ __launch_bounds__(WR_THREADS, 1) void wr_floor_kernel(PersistArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
-  const int r = wr_role(a.P, blockIdx.x);
+  const int r = wr_role(a.P, wr_block(a.P.by_xcd));
   if (r < 0) return;
   if (r < a.P.NH) floor_head(a, r, lds);
   else if (r < a.P.NH + a.P.NM) floor_mirror(a, r - a.P.NH, lds);

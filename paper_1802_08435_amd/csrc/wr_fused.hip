@@ -363,7 +363,7 @@ __device__ __forceinline__ void fused_head_role(const PersistArgs& a, int j, uns
 template <int KH>
 __global__ __launch_bounds__(WR_THREADS, 1) void wr_fused_kernel(PersistArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
-  const int r = wr_role(a.P, blockIdx.x);
+  const int r = wr_role(a.P, wr_block(a.P.by_xcd));
   if (r < 0) return;
   if (r < a.P.NH) fused_head_role<KH>(a, r, lds);
   else unit_role<KH, true>(a, r - a.P.NH, lds);

@@ -1,6 +1,7 @@
 // Host side of libwavernn: validation, weight packing, launch plans, C ABI.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -61,10 +62,10 @@ constexpr int PATH_SPARSE_ID = 3, PATH_CONCURRENT_ID = 4, PATH_FUSED_ID = 5;   /
 // queue, and one of the 4 grids ran after another (4 utterances x 9,613 among
 // three models: 49.2 ms a call, 37.3 with shared streams; one model: 37.2).
 // Created with the first model that uses them (default priority), destroyed
-// with the last one.  mu() is held from a call's fork to its join.  A call that is
-// being captured into a graph uses streams of its own model instead: a stream
-// that has joined a capture stays in it until the capture ends, and another
-// model's call in between would be recorded into the same graph or refused.
+// with the last one.  A call that is being captured into a graph uses streams
+// of its own model instead: a stream that has joined a capture stays in it until
+// the capture ends, and another model's call in between would be recorded into
+// the same graph or refused.
 struct FanStreams {
   hipStream_t st[WR_FAN - 1] = {};
   int refs = 0;
@@ -187,6 +188,17 @@ struct wavernn_model {
   float* d_ctab = nullptr;              // context table [max_streams][B][rows or window][Dx]
   int64_t ctab_cap = 0;                 // floats
   wavernn_state cnn_state[2] = {};      // state between chunks (ping-pong)
+  // the model's calls in flight (see CallScope)
+  hipEvent_t done = nullptr;         // recorded after each call
+  bool busy = false;                 // ... and not yet seen complete
+  hipStream_t busy_st = nullptr;     // the stream of the last one
+  uint64_t busy_seq = 0;
+  XcdLoad load = {};                 // workgroups they keep on each XCD
+  int load_per_cu = 1;
+  unsigned fan_used = 0;             // internal streams they use
+  int home = 0;                      // XCDs by which a captured call's placement is moved
+  int by_xcd = 0;                    // roles go by the XCDs that blocks run on (wr_block)
+  int xcd_cus = 32, pk_per_cu = 1, score_per_cu = 1, batch_per_cu = 1;   // CUs of an XCD, workgroups of a kernel on one
   // batched path (several utterances per launch)
   bool has_batch = false;
   BatchPlan bplan;
@@ -213,7 +225,11 @@ struct wavernn_model {
     HIPOK(hipMemcpy(*p, host, bytes, hipMemcpyHostToDevice));
     return WAVERNN_OK;
   }
+  void enter_device();
+  void leave_device();
   ~wavernn_model() {
+    leave_device();
+    if (done) (void)hipEventDestroy(done);
     for (hipEvent_t e : fan_join)
       if (e) (void)hipEventDestroy(e);
     if (fan_fork) (void)hipEventDestroy(fan_fork);
@@ -223,6 +239,160 @@ struct wavernn_model {
     for (void* q : allocs) (void)hipFree(q);
   }
 };
+
+namespace {
+
+// Launches of separate models on one device.
+//
+// The workgroups of a persistent launch wait for each other, so all of them
+// must be resident at once, one to a CU.  A launch whose workgroups do not fit
+// beside those of another model's launch would hold its CUs and wait for the
+// other to end, past the limit of a bounded wait if that takes longer, and two
+// such launches can each hold a part of the CUs and both fail.  So every
+// call enters what it keeps on each XCD, and a call that starts while others
+// are in flight on other streams takes the first placement (its own, or moved
+// by 1 .. 7 XCDs) that fits beside all of them; if none does, it waits on its
+// stream for the oldest of them until it does.  A fused grid, a scoring group
+// and a batched group take 28 of an XCD's 32 CUs at H = 896, a dense grid 14
+// on one and 3 or 4 on the others.
+//
+// A call that is being captured into a graph neither waits nor is entered (its
+// launches run when the graph does); its placement is moved by the model's
+// `home`, so that the graphs of up to 8 models do not share an XCD by default.
+struct DeviceCalls {
+  std::mutex mu;                          // held while a call is enqueued
+  std::vector<wavernn_model*> models, others;   // others: scratch of a call, with room for every model
+  uint64_t seq = 0;
+  static DeviceCalls& of(int dev) {
+    static DeviceCalls* all = new DeviceCalls[WR_MAX_DEVICES + 1];   // (kept: a model may be destroyed at exit)
+    return all[dev >= 0 && dev < WR_MAX_DEVICES ? dev : WR_MAX_DEVICES];
+  }
+};
+
+// A call of model m on stream st, from its first launch to its last.
+class CallScope {
+ public:
+  CallScope(wavernn_model* m, hipStream_t st)
+      : m_(m), st_(st), D_(DeviceCalls::of(m->device)), lock_(D_.mu), captured_(capturing(st)) {}
+  ~CallScope() {
+    if (!entered_) return;
+    if (hipEventRecord(m_->done, st_) == hipSuccess) return;
+    (void)hipGetLastError();
+    m_->busy = false;
+  }
+  CallScope(const CallScope&) = delete;
+  CallScope& operator=(const CallScope&) = delete;
+  bool captured() const { return captured_; }
+  int rot() const { return rot_; }
+
+  // Choose the placement: load(rot) is what the call keeps on each XCD when it
+  // is moved by rot XCDs (movable), per_cu the workgroups of its kernels a CU holds.
+  template <class L>
+  wavernn_status place(int per_cu, bool movable, L&& load, bool wait = true) {
+    if (captured_ || !m_->by_xcd) {       // (without it where a launch runs is not known)
+      rot_ = movable && m_->by_xcd ? m_->home : 0;
+      return WAVERNN_OK;
+    }
+    XcdLoad want = load(0), held = {};
+    std::vector<wavernn_model*>& others = D_.others;
+    others.clear();
+    (void)finished(m_);                   // (its ended calls no longer count)
+    for (wavernn_model* o : D_.models)    // in flight, and not before this call on its own stream
+      if (o != m_ && o->busy && (o->busy_st != st_ || st_ == hipStreamPerThread) && !finished(o)) others.push_back(o);
+    std::sort(others.begin(), others.end(), [](auto* a, auto* b) { return a->busy_seq < b->busy_seq; });
+    size_t first = 0;                     // the others from here on are run beside
+    auto fits = [&]() {
+      int fewest = per_cu;
+      held = want;
+      for (size_t i = first; i < others.size(); ++i) {
+        wr_load_add(&held, others[i]->load);
+        fewest = std::min(fewest, others[i]->load_per_cu);
+      }
+      return first == others.size() || wr_load_fits(held, fewest * m_->xcd_cus);
+    };
+    if (wait && !fits()) {
+      int r = 1;
+      for (; movable && r < 8; ++r) {
+        want = load(r);
+        if (fits()) break;
+      }
+      if (movable && r < 8) {
+        rot_ = r;
+      } else {
+        want = load(0);
+        for (; !fits(); ++first) HIPOK(hipStreamWaitEvent(st_, others[first]->done, 0));
+      }
+    }
+    for (size_t i = first; i < others.size(); ++i) fan_used_ |= others[i]->fan_used;
+    for (int x = 0; x < 8; ++x) m_->load.n[x] = m_->busy ? std::max(m_->load.n[x], want.n[x]) : want.n[x];
+    m_->load_per_cu = m_->busy ? std::min(m_->load_per_cu, per_cu) : per_cu;
+    if (!m_->busy) m_->fan_used = 0;
+    m_->busy = entered_ = true;
+    m_->busy_st = st_;
+    m_->busy_seq = ++D_.seq;
+    return WAVERNN_OK;
+  }
+
+  // n internal streams, other ones than the calls beside this one use where there are as many.
+  void fan_streams(int n, hipStream_t* out) {
+    int at = 0;
+    auto used = [&](int s) {
+      unsigned u = 0;
+      for (int i = 0; i < n; ++i) u |= 1u << (s + i) % (WR_FAN - 1);
+      return u;
+    };
+    for (int s = 0; s < WR_FAN - 1; ++s)
+      if (!(used(s) & fan_used_)) {
+        at = s;
+        break;
+      }
+    for (int i = 0; i < n; ++i) out[i] = m_->fan_st[(at + i) % (WR_FAN - 1)];
+    m_->fan_used |= used(at);
+  }
+
+ private:
+  // Has the model's last call ended?  (Asked in a relaxed capture mode: a
+  // thread that captures elsewhere is not disturbed.)
+  static bool finished(wavernn_model* o) {
+    if (!o->busy) return true;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const hipError_t before = hipPeekAtLastError();
+    const hipError_t e = hipEventQuery(o->done);
+    if (before == hipSuccess) (void)hipGetLastError();   // "not ready" is no error of the caller's
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipErrorNotReady) o->busy = false;
+    return !o->busy;
+  }
+
+  wavernn_model* m_;
+  hipStream_t st_;
+  DeviceCalls& D_;
+  std::unique_lock<std::mutex> lock_;
+  bool captured_, entered_ = false;
+  int rot_ = 0;
+  unsigned fan_used_ = 0;                 // by the calls beside this one
+};
+
+}  // namespace
+
+void wavernn_model::enter_device() {
+  DeviceCalls& D = DeviceCalls::of(device);
+  std::lock_guard<std::mutex> lock(D.mu);
+  home = 0;
+  for (bool taken = true; taken && home < 8; home += taken) {   // the first that no model has
+    taken = false;
+    for (wavernn_model* o : D.models) taken = taken || o->home == home;
+  }
+  home %= 8;
+  D.models.push_back(this);
+  D.others.reserve(D.models.size());
+}
+void wavernn_model::leave_device() {
+  DeviceCalls& D = DeviceCalls::of(device);
+  std::lock_guard<std::mutex> lock(D.mu);
+  D.models.erase(std::remove(D.models.begin(), D.models.end(), this), D.models.end());
+}
 
 namespace {
 
@@ -440,25 +610,37 @@ wavernn_status upload_common(wavernn_model* m, const wavernn_weights* w) {
   return WAVERNN_OK;
 }
 
-// The whole persistent grid must fit on the device at once.
-wavernn_status check_coresident(wavernn_model* m, const void* k, int grid, int lds, const char* what) {
+// The whole persistent grid must fit on the device at once, and what of it an
+// XCD gets on that XCD's CUs.  *per_cu: workgroups of the kernel that one CU holds.
+wavernn_status check_coresident(wavernn_model* m, const void* k, int grid, const XcdLoad& load, int lds, const char* what,
+                                int* per_cu_out) {
+  grid = wr_rows(grid);
   HIPOK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
   int per_cu = 0;
   HIPOK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, WR_THREADS, lds));
   hipDeviceProp_t prop;
   HIPOK(hipGetDeviceProperties(&prop, m->device));
-  if (per_cu < 1 || per_cu * prop.multiProcessorCount < grid)
+  const bool xcds = prop.multiProcessorCount >= 64;   // (a partition of fewer CUs has fewer XCDs)
+  if (per_cu < 1 || per_cu * prop.multiProcessorCount < grid ||
+      (xcds && !wr_load_fits(load, per_cu * (prop.multiProcessorCount / 8))))
     return fail(WAVERNN_E_UNSUPPORTED, "%s grid of %d workgroups cannot be co-resident (%d per CU, %d CUs)", what,
                 grid, per_cu, prop.multiProcessorCount);
+  m->xcd_cus = prop.multiProcessorCount / 8;
+  if (per_cu_out) *per_cu_out = per_cu;
   return WAVERNN_OK;
 }
 
-
 // Grid s of n batch-1 grids side by side: heads and mirrors on XCD 8 s / n,
-// units spread over the XCDs (fused: each grid whole on its XCD).
-PersistPlan fan_plan(const wavernn_model* m, int s, int n) {
+// units spread over the XCDs (fused: each grid whole on its XCD); all `rot` XCDs on.
+PersistPlan fan_plan(const wavernn_model* m, int s, int n, int rot = 0) {
   PersistPlan P = m->plan;
-  wr_place(&P, 8 * s / n, m->fused ? 1 << (8 * s / n) : 255);
+  wr_place_rot(&P, 8 * s / n, m->fused ? 1 << (8 * s / n) : 255, rot);
+  return P;
+}
+// The placement of a launch that runs alone (wavernn_tune), `rot` XCDs on.
+PersistPlan solo_plan(const wavernn_model* m, int rot = 0) {
+  PersistPlan P = m->plan;
+  wr_place_rot(&P, m->solo_hx, m->solo_uxm, rot);
   return P;
 }
 
@@ -475,15 +657,9 @@ wavernn_status build_fanout(wavernn_model* m) {
   // of all n grids at once (idle blocks return at once)
   int n = std::min(WR_FAN, (int)m->cfg.max_streams);
   for (; n >= 2; --n) {
-    int busy[8] = {};
-    for (int i = 0; i < n; ++i) {
-      const PersistPlan Q = fan_plan(m, i, n);
-      for (int b = 0; b < Q.grid; ++b)
-        if (wr_role(Q, b) >= 0) ++busy[b % 8];
-    }
-    bool fits = per_cu >= 1;
-    for (int x = 0; x < 8; ++x) fits = fits && busy[x] <= per_cu * (prop.multiProcessorCount / 8);
-    if (fits) break;
+    XcdLoad l = {};
+    for (int i = 0; i < n; ++i) wr_load_add(&l, wr_load(fan_plan(m, i, n)));
+    if (per_cu >= 1 && wr_load_fits(l, per_cu * (prop.multiProcessorCount / 8))) break;
   }
   if (n < 2) return WAVERNN_OK;
   wavernn_status s = m->alloc(&m->d_fxc, (size_t)n * P.x_words * 4);
@@ -550,7 +726,7 @@ wavernn_status build_persist(wavernn_model* m, const wavernn_weights* w) {
   wavernn_status s;
   if ((s = upload_dense_units(m, w)) != WAVERNN_OK) return s;
   if ((s = upload_common(m, w)) != WAVERNN_OK) return s;
-  return check_coresident(m, m->pk, P.grid, P.lds, "persistent");
+  return check_coresident(m, m->pk, P.grid, wr_load(P), P.lds, "persistent", &m->pk_per_cu);
 }
 
 // Fused Subscale WaveRNN 2x (Sec. 4.4): the dense units of the batch-1 plan,
@@ -626,7 +802,7 @@ wavernn_status build_fused(wavernn_model* m, const wavernn_weights* w) {
   if ((s = m->alloc(&m->d_xc, (size_t)(P.x_words + 1) / 2 * 8)) != WAVERNN_OK) return s;
   m->fused = true;
   m->solo_uxm = 1 << m->solo_hx;   // the whole grid on one XCD
-  return check_coresident(m, m->pk, P.grid, P.lds, "fused");
+  return check_coresident(m, m->pk, P.grid, wr_load(P), P.lds, "fused", &m->pk_per_cu);
 }
 
 // Block-sparse R (Sec. 3.2) as the block-sparse units store it (layout in
@@ -701,7 +877,7 @@ wavernn_status build_sparse(wavernn_model* m, const wavernn_weights* w) {
   if ((s = upload_common(m, w)) != WAVERNN_OK) return s;
   m->sparse = true;
   (void)NR;
-  return check_coresident(m, m->pk, P.grid, P.lds, "block-sparse");
+  return check_coresident(m, m->pk, P.grid, wr_load(P), P.lds, "block-sparse", &m->pk_per_cu);
 }
 
 // Batched path: unit blocks for WR_BUCT = 4 row tiles per half (the head
@@ -763,7 +939,9 @@ wavernn_status build_batch(wavernn_model* m, const wavernn_weights* w) {
                   "units too large for LDS?)", v, horizon_of(m->cfg));
     const void* k = wr_batch_kernel_ptr(Q.KH, Q.KX > 0, Q.L, horizon_of(m->cfg) >= 0);
     if (!k) return fail(WAVERNN_E_UNSUPPORTED, "hidden %d: no batched kernel instantiation", H);
-    if ((s = check_coresident(m, k, Q.grid, Q.lds, "batched")) != WAVERNN_OK) return s;
+    int per_cu = 0;
+    if ((s = check_coresident(m, k, Q.grid, wr_load(Q.G, Q.NH + Q.NU, 0), Q.lds, "batched", &per_cu)) != WAVERNN_OK) return s;
+    m->batch_per_cu = xwords ? std::min(m->batch_per_cu, per_cu) : per_cu;
     xwords = std::max(xwords, (size_t)Q.G * Q.x_words);
   }
   if ((s = m->alloc(&m->d_bxc, (xwords + 1) / 2 * 8)) != WAVERNN_OK) return s;
@@ -904,7 +1082,13 @@ wavernn_status build_score(wavernn_model* m, const wavernn_weights* w) {
   if ((s = m->upload(&m->d_sb, bv.data(), bv.size() * 4)) != WAVERNN_OK) return s;
   if ((s = upload_zero(m)) != WAVERNN_OK) return s;
   for (int LV = 1; LV <= 8 && LV < 2 * m->cfg.max_streams; LV *= 2)
-    if ((s = check_coresident(m, wr_score_kernel_ptr(KT2, LV), 8 * (H / 32), 0, "scoring")) != WAVERNN_OK) return s;
+  {
+    int per_cu = 0;
+    if ((s = check_coresident(m, wr_score_kernel_ptr(KT2, LV), 8 * (H / 32), wr_load(8, H / 32, 0), 0, "scoring",
+                              &per_cu)) != WAVERNN_OK)
+      return s;
+    m->score_per_cu = LV > 1 ? std::min(m->score_per_cu, per_cu) : per_cu;
+  }
   if ((s = m->alloc(&m->d_sxc, (size_t)8 * score_words(H, 8) * 4)) != WAVERNN_OK) return s;
   m->score = true;
   return WAVERNN_OK;
@@ -1250,6 +1434,8 @@ struct RunIO {
   size_t ws_cap = 0;             // its bytes
   int64_t step0 = 0;             // subscale: the schedule steps [step0, step0 + n_steps) of the call run
   int64_t n_steps = -1;          // (-1: the whole schedule, a wavernn_sample call)
+  CallScope* call = nullptr;
+  bool pinned = false;           // batch-1 grids at their own placement, whatever else runs (wavernn_tune)
 };
 
 // First and last conditioning frame a call reads.
@@ -1321,15 +1507,15 @@ wavernn_status run_small(wavernn_model* m, const RunIO& io) {
   if (io.init) { a.h_in = io.init->h; a.c_in = io.init->c_prev; a.f_in = io.init->f_prev; }
   if (io.fin) { a.h_out = io.fin->h; a.c_out = io.fin->c_prev; a.f_out = io.fin->f_prev; }
   void* args[] = {&a};
+  // its workgroups wait for no other, so the launch need not either
+  wavernn_status s = io.call->place(1, false, [&](int) {
+    XcdLoad l = {};
+    for (int x = 0; x < 8; ++x) l.n[x] = (io.S + 7 - x) / 8;
+    return l;
+  }, false);
+  if (s != WAVERNN_OK) return s;
   HIPOK(hipLaunchKernel(wr_small_kernel_ptr(m->cfg.hidden), dim3(io.S), dim3(WR_SMALL_THREADS), args, 0, io.st));
   return WAVERNN_OK;
-}
-
-// The placement of a launch that runs alone (wavernn_tune).
-PersistPlan solo_plan(const wavernn_model* m) {
-  PersistPlan P = m->plan;
-  wr_place(&P, m->solo_hx, m->solo_uxm);
-  return P;
 }
 
 // The arguments of utterance s on placement P with exchange words xc and table cb.
@@ -1397,28 +1583,28 @@ wavernn_status launch_persist(wavernn_model* m, const RunIO& io, int s, int n, x
   wavernn_status c = launch_cond(m, feat, n_cb, first_frame(m, io), last_frame(m, io), n, cb, cb_stride, xc,
                                  m->plan.x_words, x_stride, io.st);
   if (c != WAVERNN_OK) return c;
-  const hipStream_t* side = m->fan_st;
-  std::unique_lock<std::mutex> lock(FanStreams::mu(), std::defer_lock);
+  hipStream_t side[WR_FAN - 1] = {};
   if (n > 1) {
-    if (capturing(io.st)) {
+    if (io.call->captured()) {
       for (int i = 0; i + 1 < n; ++i)
         if (!m->cap_st[i]) HIPOK(hipStreamCreateWithFlags(&m->cap_st[i], hipStreamNonBlocking));
-      side = m->cap_st;
+      std::copy(m->cap_st, m->cap_st + n - 1, side);
     } else {
-      lock.lock();
+      io.call->fan_streams(n - 1, side);
     }
     HIPOK(hipEventRecord(m->fan_fork, io.st));
   }
   for (int i = n - 1; i >= 0; --i) {   // the caller's stream last
-    const PersistPlan P = n > 1 ? fan_plan(m, i, n) : solo_plan(m);
+    const PersistPlan P = n > 1 ? fan_plan(m, i, n, io.call->rot()) : solo_plan(m, io.call->rot());
     PersistArgs a = persist_args(m, io, s + i, P, xc + i * x_stride, cb + i * cb_stride, n_cb);
     void* args[] = {&a};
     const hipStream_t st = i ? side[i - 1] : io.st;
     if (i) HIPOK(hipStreamWaitEvent(st, m->fan_fork, 0));
     // An ordinary launch: create() checked that the whole grid fits on the
-    // device at once, and every cross-workgroup wait is bounded, so a grid
-    // that did not become co-resident ends with an error, never a hang.
-    HIPOK(hipLaunchKernel(m->pk, dim3(P.grid), dim3(WR_THREADS), args, P.lds, st));
+    // device at once, CallScope keeps launches that do not fit beside it away,
+    // and every cross-workgroup wait is bounded, so a grid that did not become
+    // co-resident all the same ends with an error, never a hang.
+    HIPOK(hipLaunchKernel(m->pk, dim3(wr_rows(P.grid)), dim3(WR_THREADS), args, P.lds, st));
     if (i) HIPOK(hipEventRecord(m->fan_join[i - 1], st));
   }
   for (int i = 1; i < n; ++i) HIPOK(hipStreamWaitEvent(io.st, m->fan_join[i - 1], 0));
@@ -1470,6 +1656,17 @@ wavernn_status run_persist(wavernn_model* m, const RunIO& io) {
     if ((st = grow_cb(m, &m->d_cb, &m->cb_cap, n_cb)) != WAVERNN_OK) return st;
     cb[0] = m->d_cb;
   }
+  const int rest = io.S % per;
+  st = io.call->place(m->pk_per_cu, !io.pinned, [&](int rot) {
+    XcdLoad most = {};
+    for (int n : {per, rest}) {     // launches of `per` utterances at once, then the rest
+      XcdLoad l = {};
+      for (int i = 0; i < n; ++i) wr_load_add(&l, wr_load(n > 1 ? fan_plan(m, i, n, rot) : solo_plan(m, rot)));
+      for (int x = 0; x < 8; ++x) most.n[x] = std::max(most.n[x], l.n[x]);
+    }
+    return most;
+  });
+  if (st != WAVERNN_OK) return st;
   for (int s = 0; s < io.S; s += per)
     if ((st = launch_persist(m, io, s, std::min(per, io.S - s), xc[0], xs, cb[0], cs, n_cb)) != WAVERNN_OK) return st;
   return WAVERNN_OK;
@@ -1510,9 +1707,12 @@ wavernn_status run_score(wavernn_model* m, const RunIO& io) {
                         io.st)) != WAVERNN_OK)
     return st;
   if ((st = launch_fill(m->d_sxc, (int64_t)G * score_words(H, LV), io.st)) != WAVERNN_OK) return st;
+  if ((st = io.call->place(m->score_per_cu, true, [&](int rot) { return wr_load(G, NW, rot); })) != WAVERNN_OK) return st;
   {
     ScoreArgs a;
     memset(&a, 0, sizeof a);
+    a.rot = io.call->rot();
+    a.by_xcd = m->by_xcd;
     a.w = m->d_srw;
     a.Iw = m->d_I;
     a.cb = m->d_scb;
@@ -1539,8 +1739,8 @@ wavernn_status run_score(wavernn_model* m, const RunIO& io) {
     a.err = m->d_err;
     a.limit = kWaitTicks;
     void* args[] = {&a};
-    // an ordinary launch (co-residency checked at create; waits bounded): workgroup k of group g is block 8 k + g
-    HIPOK(hipLaunchKernel(wr_score_kernel_ptr(H / 32, LV), dim3(8 * (NW - 1) + G), dim3(WR_THREADS), args, 0, io.st));
+    // an ordinary launch (co-residency checked at create; waits bounded): workgroup k of group g is in row k
+    HIPOK(hipLaunchKernel(wr_score_kernel_ptr(H / 32, LV), dim3(8 * NW), dim3(WR_THREADS), args, 0, io.st));
   }
   if (!post) return WAVERNN_OK;
   for (int64_t r0 = 0; r0 < rows; r0 += CH) {
@@ -1605,6 +1805,10 @@ wavernn_status run_batch(wavernn_model* m, const RunIO& io) {
   if ((st = launch_cond(m, io.cond, n_cb, first_frame(m, io), last_frame(m, io), io.S, cbt, 0, nullptr, 0, 0, io.st)) !=
       WAVERNN_OK)
     return st;
+  if ((st = io.call->place(m->batch_per_cu, true, [&](int rot) { return wr_load(B.G, B.NH + B.NU, rot); })) != WAVERNN_OK)
+    return st;
+  B.rot = io.call->rot();
+  B.by_xcd = m->by_xcd;
   BatchArgs a;
   memset(&a, 0, sizeof a);
   a.P = B;
@@ -1711,6 +1915,24 @@ wavernn_status run_batch(wavernn_model* m, const RunIO& io) {
   return WAVERNN_OK;
 }
 
+// Do the blocks of a launch go to XCDs 0 .. 7 in turn, from any of them?  (Asked
+// of the device once a model; roles go by blockIdx if not.)
+wavernn_status find_xcds(wavernn_model* m) {
+  constexpr int N = 512;
+  unsigned* d = nullptr;
+  wavernn_status s = m->alloc(&d, N * sizeof(unsigned));
+  if (s != WAVERNN_OK) return s;
+  unsigned h[N];
+  void* args[] = {&d};
+  HIPOK(hipLaunchKernel(wr_xcd_kernel_ptr(), dim3(N), dim3(64), args, 0, nullptr));
+  HIPOK(hipMemcpy(h, d, sizeof h, hipMemcpyDeviceToHost));
+  m->by_xcd = 1;
+  for (int b = 0; b < N; ++b)
+    if (h[b] > 7 || ((h[b] - h[0] - b) & 7)) m->by_xcd = 0;
+  m->plan.by_xcd = m->by_xcd;
+  return WAVERNN_OK;
+}
+
 wavernn_status scratch_of(int dev, unsigned char** out, size_t* cap);
 
 wavernn_status run(wavernn_model* m, RunIO& io, bool noalloc = false) {
@@ -1721,6 +1943,8 @@ wavernn_status run(wavernn_model* m, RunIO& io, bool noalloc = false) {
   HIPOK(hipGetDevice(&dev));
   if (dev != m->device) return fail(WAVERNN_E_INVALID, "model lives on device %d, current device is %d", m->device, dev);
   if (noalloc && (s = scratch_of(dev, &io.ws, &io.ws_cap)) != WAVERNN_OK) return s;
+  CallScope call(m, io.st);
+  io.call = &call;
   if (m->path == PATH_SMALL) return run_small(m, io);
   if (m->fused) return run_persist(m, io);
   if (m->path == PATH_PERSIST) {
@@ -1770,7 +1994,7 @@ wavernn_status time_launch(wavernn_model* m, const void* k, int grid, int lds, v
   HIPOK(hipEventCreate(&e0));
   HIPOK(hipEventCreate(&e1));
   hipError_t he = hipEventRecord(e0, st);
-  if (he == hipSuccess) he = hipLaunchKernel(k, dim3(grid), dim3(WR_THREADS), args, lds, st);
+  if (he == hipSuccess) he = hipLaunchKernel(k, dim3(wr_rows(grid)), dim3(WR_THREADS), args, lds, st);
   if (he == hipSuccess) he = hipEventRecord(e1, st);
   if (he == hipSuccess) he = hipEventSynchronize(e1);
   float ms = 0.0f;
@@ -1794,8 +2018,12 @@ wavernn_status batch_floor(wavernn_model* m, int64_t n_steps, double* us, hipStr
     return fail(WAVERNN_E_UNSUPPORTED, "no batched plan for %d vectors", V);
   const void* k = wr_batch_floor_kernel_ptr(B.KH, B.KX > 0, B.L, F >= 0);
   if (!k) return fail(WAVERNN_E_UNSUPPORTED, "hidden %d: no batched floor instantiation", B.H);
-  wavernn_status s = check_coresident(m, k, B.grid, B.lds, "batched sync-floor");
+  const XcdLoad load = wr_load(B.G, B.NH + B.NU, 0);
+  int per_cu = 0;
+  wavernn_status s = check_coresident(m, k, B.grid, load, B.lds, "batched sync-floor", &per_cu);
   if (s != WAVERNN_OK) return s;
+  CallScope call(m, st);
+  if ((s = call.place(per_cu, false, [&](int) { return load; })) != WAVERNN_OK) return s;
   const size_t cbn = (size_t)m->cfg.max_streams * 3 * B.H;   // one frame of bias + conditioning (zeros)
   if (cbn > m->bcb_cap) {
     float* p = nullptr;
@@ -1808,6 +2036,7 @@ wavernn_status batch_floor(wavernn_model* m, int64_t n_steps, double* us, hipStr
   BatchArgs a;
   memset(&a, 0, sizeof a);
   a.P = B;
+  a.P.by_xcd = m->by_xcd;
   a.hw = m->d_hw;
   a.uw = m->d_buw;
   a.ur = m->d_bur;
@@ -1927,10 +2156,15 @@ wavernn_status wavernn_create(const wavernn_config* cfg, const wavernn_weights* 
     s = m->alloc(&m->d_err, 64);
     if (s == WAVERNN_OK && hipMemset(m->d_err, 0, 64) != hipSuccess) s = fail(WAVERNN_E_HIP, "hipMemset failed");
   }
+  if (m->path == PATH_SMALL) m->by_xcd = 1;   // (its blocks have no roles)
+  else if (s == WAVERNN_OK) s = find_xcds(m);
+  if (s == WAVERNN_OK && hipEventCreateWithFlags(&m->done, hipEventDisableTiming) != hipSuccess)
+    s = fail(WAVERNN_E_HIP, "hipEventCreateWithFlags failed");
   if (s != WAVERNN_OK) {
     delete m;
     return s;
   }
+  m->enter_device();
   *out = m;
   return WAVERNN_OK;
 }
@@ -2027,11 +2261,11 @@ int32_t wavernn_model_path(const wavernn_model* m, int32_t n_streams, int32_t* g
                         m->cfg.subscale, horizon_of(m->cfg), lead_of(m->cfg), m->has_cnn)) {
     g = B.grid, b = WR_THREADS;
   } else if (m->path == PATH_PERSIST && !m->fused && n_streams > 1 && n_streams <= m->nfan) {
-    path = PATH_CONCURRENT_ID, g = m->plan.grid, b = WR_THREADS;
+    path = PATH_CONCURRENT_ID, g = wr_rows(m->plan.grid), b = WR_THREADS;
   } else if (m->path == PATH_PERSIST && n_streams > 1 && m->has_batch && batch_plan(m->cfg.hidden, n_streams, &B)) {
     path = PATH_BATCHED, g = B.grid, b = WR_THREADS;
   } else if (m->path == PATH_PERSIST) {
-    g = solo_plan(m).grid, b = WR_THREADS;
+    g = wr_rows(solo_plan(m).grid), b = WR_THREADS;
     if (m->sparse) path = PATH_SPARSE_ID;
     if (m->fused) path = PATH_FUSED_ID;
   }
@@ -2053,8 +2287,11 @@ wavernn_status wavernn_debug_sync_floor(wavernn_model* m, int64_t n_steps, doubl
   const PersistPlan P = solo_plan(m);
   if ((3 * P.Hh) % P.NU) return fail(WAVERNN_E_UNSUPPORTED, "gate words do not split evenly over the units");
   const void* k = wr_floor_kernel_ptr();
-  wavernn_status s = check_coresident(m, k, P.grid, P.lds, "sync-floor");
+  int per_cu = 0;
+  wavernn_status s = check_coresident(m, k, P.grid, wr_load(P), P.lds, "sync-floor", &per_cu);
   if (s != WAVERNN_OK) return s;
+  CallScope call(m, st);
+  if ((s = call.place(per_cu, false, [&](int) { return wr_load(P); })) != WAVERNN_OK) return s;
   if ((s = launch_fill(m->d_xc, P.x_words, st)) != WAVERNN_OK) return s;
   PersistArgs a;
   memset(&a, 0, sizeof a);
@@ -2083,11 +2320,7 @@ static wavernn_status candidate_fits(const wavernn_model* m, int i, bool* fits) 
   hipDeviceProp_t prop;
   HIPOK(hipGetDeviceProperties(&prop, m->device));
   const int per_xcd = per_cu * (prop.multiProcessorCount / 8);
-  int busy[8] = {};
-  for (int b = 0; b < P.grid; ++b)
-    if (wr_role(P, b) >= 0) ++busy[b % 8];
-  *fits = per_cu >= 1 && P.grid <= per_cu * prop.multiProcessorCount;
-  for (int x = 0; x < 8; ++x) *fits = *fits && busy[x] <= per_xcd;
+  *fits = per_cu >= 1 && wr_rows(P.grid) <= per_cu * prop.multiProcessorCount && wr_load_fits(wr_load(P), per_xcd);
   return WAVERNN_OK;
 }
 
@@ -2142,6 +2375,7 @@ wavernn_status wavernn_tune(wavernn_model* m, int64_t n_steps, int32_t rounds, f
       (Dc == 0 || step(hipMemsetAsync(cond, 0, (size_t)n_frames * Dc * 4, st))) &&
       step(hipEventCreate(&e0)) && step(hipEventCreate(&e1))) {
     RunIO io{1, T, cond, n_frames, 1, nullptr, nullptr, nullptr, out, nullptr, nullptr, nullptr, st};
+    io.pinned = true;
     // round -1 warms up (code objects, tables) on the default placement
     for (int r = -1; r < rounds && s == WAVERNN_OK; ++r)
       for (int i = 0; i < 64 && s == WAVERNN_OK; ++i) {
@@ -2151,7 +2385,11 @@ wavernn_status wavernn_tune(wavernn_model* m, int64_t n_steps, int32_t rounds, f
         m->solo_hx = P.hx;
         m->solo_uxm = P.uxm;
         if (!step(hipEventRecord(e0, st))) break;
-        if ((s = run_persist(m, io)) != WAVERNN_OK) break;
+        {
+          CallScope call(m, st);
+          io.call = &call;
+          if ((s = run_persist(m, io)) != WAVERNN_OK) break;
+        }
         float ms = 0.0f;
         if (!step(hipEventRecord(e1, st)) || !step(hipEventSynchronize(e1)) || !step(hipEventElapsedTime(&ms, e0, e1))) break;
         unsigned err = 0;

@@ -287,6 +287,13 @@ __device__ __forceinline__ void trace_at(const A& a, int64_t t, int slot) {
   if (a.trace && t < a.trace_steps) a.trace[t * WR_TRACE_SLOTS + slot] = wr_clock();
 }
 
+// The XCD this workgroup runs on (XCC_ID, bits 3:0).
+__device__ __forceinline__ unsigned wr_xcd() { return __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u; }
+// The number of this block that roles go by (see wr_role): its row of 8 and its XCD.
+__device__ __forceinline__ int wr_block(int by_xcd) {
+  return by_xcd ? (int)((blockIdx.x & ~7u) | (wr_xcd() & 7u)) : (int)blockIdx.x;
+}
+
 // Words that only the lead workgroups read (partial logits, the mirrors'
 // words) are published into the L2 of their XCD when all leads share one
 // (build with WR_LOCAL_XCHG=0 to keep every word coherent across XCDs).
@@ -294,15 +301,15 @@ __device__ __forceinline__ void trace_at(const A& a, int64_t t, int slot) {
 #define WR_LOCAL_XCHG 1
 #endif
 // Do all n lead workgroups of a launch (the heads and mirrors of a batch-1
-// grid, placed on one XCD) run on one XCD?  Lead i publishes its XCD (the
-// XCC_ID hardware register) in words[i] and thread 0 reads every lead's; all
+// grid, placed on one XCD) run on one XCD?  Lead i publishes its XCD
+// in words[i] and thread 0 reads every lead's; all
 // leads read the same words, so all get the same answer.  Called by every
 // thread of the workgroup (one barrier inside; flag: an LDS int).  A wait
 // that expires flags the launch's error word and answers no.
 template <class A>
 __device__ __forceinline__ bool leads_share_xcd(xw* words, int n, int i, int* flag, const A& a) {
   if (threadIdx.x == 0) {
-    const unsigned x = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u;   // XCC_ID, bits 3:0
+    const unsigned x = wr_xcd();
     __hip_atomic_store(words + i, 0x100u | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int same = 1;
     WaitBudget wb{wr_clock(), 0};
@@ -329,7 +336,7 @@ template <class A>
 __device__ __forceinline__ bool group_shares_xcd(xw* words, int n, int i, int* flag, const A& a) {
   if (threadIdx.x < 64) {
     const int k = threadIdx.x;
-    const unsigned x = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u;   // XCC_ID, bits 3:0
+    const unsigned x = wr_xcd();
     if (k == 0) __hip_atomic_store(words + i, 0x100u | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     bool same = true;
     if (k < n) {

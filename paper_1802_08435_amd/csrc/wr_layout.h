@@ -94,7 +94,8 @@ struct PersistPlan {
                           // (coarse columns, fine columns); 0 for the dense kernel
   int BH, BW, BR, u_wb;   // block-sparse units: block shape (4 x 4 or 16 x 1), block-rows per unit,
                           // bytes of the weights before the block-column indices
-  int grid;               // workgroups launched: head j at block 8j + hx, units on the others
+  int grid;               // blocks: head j at block 8j + hx, units on the others (launched: whole rows of 8)
+  int by_xcd;             // 1: blocks are numbered by the XCD they run on, 0: by blockIdx (wr_block)
   int hx, uxm;            // placement: heads on XCD hx, units on the XCDs of the bits of uxm
   int hw_frags;           // head fragments per wave: O1[KH], O3[KH], O2[2 KO], O4[2 KO]
   int u_lds_w;            // unit LDS block: dense R tiles, or the block-sparse records
@@ -120,11 +121,16 @@ WR_HD inline uint32_t wr_dtag(int64_t s, int stride) {
 }
 
 WR_HD inline int wr_rup(int x, int m) { return (x + m - 1) / m * m; }
+WR_HD inline int wr_rows(int grid) { return wr_rup(grid, 8); }
 
 // Block index of head j and the role of block b (head index, mirror index +
 // NH, unit index + NH + NM, or -1 idle).
-// Placement.  Blocks are dealt round-robin over the 8 XCDs (block b runs on
-// XCD b % 8), so lead block i (head i < NH, then mirror i - NH) sits at block
+// Placement.  A launch's blocks are dealt round-robin over the 8 XCDs, from an XCD
+// that the hardware queue of its stream sets (measured: block b on XCD
+// (b + 5) mod 8, 6, 7 and 0 for the four queues, every launch of a queue alike).
+// So roles go by blocks numbered anew within each row of 8: b is the row times
+// 8 plus the XCD the block finds itself on (wr_block), and a grid is whole rows
+// (wr_rows).  Lead block i (head i < NH, then mirror i - NH) sits at
 // 8 i + hx, and bit x of uxm admits units on the other blocks of XCD x.  Unit
 // blocks below b:
 WR_HD inline int wr_units_below(const PersistPlan& P, int b) {
@@ -154,8 +160,43 @@ WR_HD inline void wr_place(PersistPlan* P, int hx, int uxm) {
   P->grid = g;
 }
 
+// The same placement `rot` XCDs on.
+WR_HD inline void wr_place_rot(PersistPlan* P, int hx, int uxm, int rot) {
+  wr_place(P, (hx + rot) & 7, (uxm << rot | uxm >> (8 - rot)) & 255);
+}
+
+// Workgroups that launches keep on each XCD until they end.
+struct XcdLoad {
+  int n[8];
+};
+WR_HD inline XcdLoad wr_load(const PersistPlan& P) {
+  XcdLoad l = {};
+  l.n[P.hx] = P.NH + P.NM;
+  for (int b = 0, k = 0; k < P.NU; ++b)
+    if ((P.uxm >> (b & 7) & 1) && !((b & 7) == P.hx && b / 8 < P.NH + P.NM)) ++l.n[b & 7], ++k;
+  return l;
+}
+// G groups of n workgroups, group g on XCD (g + rot) mod 8 (batched and scoring kernels).
+WR_HD inline XcdLoad wr_load(int G, int n, int rot) {
+  XcdLoad l = {};
+  for (int g = 0; g < G; ++g) l.n[(g + rot) & 7] += n;
+  return l;
+}
+WR_HD inline void wr_load_add(XcdLoad* a, const XcdLoad& b) {
+  for (int x = 0; x < 8; ++x) a->n[x] += b.n[x];
+}
+// Do all of them fit at once?  `room` workgroups an XCD: its CUs times the
+// fewest workgroups of any of the kernels that one CU holds (so many always
+// find a place, wherever the others went).
+WR_HD inline bool wr_load_fits(const XcdLoad& a, int room) {
+  for (int x = 0; x < 8; ++x)
+    if (a.n[x] > room) return false;
+  return true;
+}
+
 WR_HD inline bool persist_plan(int H, PersistPlan* P) {
   if (H <= 0 || H % 128) return false;
+  P->by_xcd = 0;
   P->H = H;
   P->Hh = H / 2;
   P->KT = P->Hh / 32;
@@ -271,6 +312,7 @@ WR_HD inline bool fused_plan(int H, PersistPlan* P) {
 // ---------------------------------------------------------------------------
 WR_HD inline bool sparse_plan(int H, int SR, int BH, int BW, int NRC, int NRF, PersistPlan* P) {
   if (H <= 0 || H % 128) return false;
+  P->by_xcd = 0;
   P->H = H;
   P->Hh = H / 2;
   P->KT = P->Hh / 32;
@@ -357,6 +399,8 @@ WR_HD inline bool sparse_plan(int H, int SR, int BH, int BW, int NRC, int NRF, P
 struct BatchPlan {
   int H, Hh, KT, KH, NH, NCT, NU, G, grid;
   int L;                  // vectors per group (2, 4 or 8)
+  int rot;                // group g on XCD (g + rot) mod 8
+  int by_xcd;             // as PersistPlan's
   int hw_frags;           // head fragments per wave (as the batch-1 plan)
   int u_lds_w;            // unit LDS weights: [UCT][KT] coarse tiles, then [UCT][KT] fine tiles
   int x_xcc;              // per group: the XCD of each head and unit, published at the start
@@ -371,10 +415,10 @@ struct BatchPlan {
 };
 
 // Role of block b: head index j (group *g), NH + unit index, or -1 (idle).
-// Blocks are dealt round-robin over the 8 XCDs, so group g (its heads, then
-// its units) sits on XCD g: at most 7 + 21 workgroups on its 32 CUs.
+// Group g (its heads, then its units) sits on XCD (g + rot) mod 8: at most
+// 7 + 21 workgroups on its 32 CUs.
 WR_HD inline int wr_batch_role(const BatchPlan& P, int b, int* g) {
-  *g = b % 8;
+  *g = (b - P.rot) & 7;
   return *g < P.G && b / 8 < P.NH + P.NU ? b / 8 : -1;
 }
 
@@ -396,7 +440,8 @@ WR_HD inline bool batch_plan(int H, int n_vectors, BatchPlan* P, int ctx_dim = 0
   P->NU = P->NCT / WR_BUCT;
   P->L = n_vectors <= 2 * WR_BL ? WR_BL / 4 : n_vectors <= 4 * WR_BL ? WR_BL / 2 : WR_BL;
   P->G = (n_vectors + P->L - 1) / P->L;
-  P->grid = 8 * (P->NH + P->NU - 1) + P->G;  // the last group's last unit block + 1
+  P->rot = P->by_xcd = 0;
+  P->grid = 8 * (P->NH + P->NU);
   P->hw_frags = 2 * P->KH + 8;
   P->u_lds_w = 2 * WR_BUCT * P->KT * WR_FRAG;
   int o = 0;

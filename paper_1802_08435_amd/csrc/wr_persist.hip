@@ -783,7 +783,7 @@ __device__ __forceinline__ void mirror_role(const PersistArgs& a, int j, unsigne
 template <int KH>
 __global__ __launch_bounds__(WR_THREADS, 1) void wr_persist_kernel(PersistArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
-  const int r = wr_role(a.P, blockIdx.x);
+  const int r = wr_role(a.P, wr_block(a.P.by_xcd));
   if (r < 0) return;
   if (r < a.P.NH) head_role<KH, 4, 1, false, true>(a, r, lds);
   else if (r < a.P.NH + a.P.NM) mirror_role<KH>(a, r - a.P.NH, lds);
@@ -930,7 +930,7 @@ __device__ __forceinline__ void sparse_unit_role(const PersistArgs& a, int k, un
 template <int KH, int GU>
 __global__ __launch_bounds__(WR_THREADS, 1) void wr_sparse_kernel(PersistArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
-  const int r = wr_role(a.P, blockIdx.x);
+  const int r = wr_role(a.P, wr_block(a.P.by_xcd));
   if (r < 0) return;
   if (r < a.P.NH) head_role<KH, 4, GU, true>(a, r, lds);
   else sparse_unit_role(a, r - a.P.NH, lds);
@@ -979,6 +979,12 @@ extern "C" __global__ __launch_bounds__(256) void wr_cond_kernel(CondArgs a) {
   for (int f = 0; f < NF; ++f)
     if (f < nf) cb[(size_t)f * a.rows] = a.Dc > 0 ? acc[f] + b : b;
 }
+
+// The XCD of every block.
+extern "C" __global__ void wr_xcd_kernel(unsigned* out) {
+  if (threadIdx.x == 0) out[blockIdx.x] = wr_xcd();
+}
+const void* wr_xcd_kernel_ptr() { return (const void*)wr_xcd_kernel; }
 
 extern "C" __global__ void wr_fill_u64(u64* p, int64_t n, u64 v) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

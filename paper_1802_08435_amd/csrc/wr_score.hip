@@ -4,8 +4,8 @@
 // so one kind of workgroup does it all, with one exchange per step.
 //
 // The utterances of a call are dealt to up to 8 groups of LV of them (LV = 1,
-// 2, 4 or 8: as few a group as 8 groups allow), group g on XCD g, all in one
-// launch.  Workgroup k of a group owns hidden units 32 k .. 32 k + 31 (all in
+// 2, 4 or 8: as few a group as 8 groups allow), group g on XCD g (or `rot`
+// XCDs on, beside another model's launch), all in one launch.  Workgroup k of a group owns hidden units 32 k .. 32 k + 31 (all in
 // one half) of its vectors.  Waves 0-3 hold the six tiles of their gate rows of
 // R (u, r, e) in VGPRs and form R h on the matrix cores; of waves 4-7, 32 LV
 // threads finish the gates with the given bytes and publish the new slice of
@@ -48,7 +48,7 @@ template <int KT2, int LV>
 __global__ __launch_bounds__(WR_THREADS, 1) void wr_score_kernel(ScoreArgs a) {
   constexpr int H = 32 * KT2, Hh = H / 2, KT = KT2 / 2, NW = H / 32;
   constexpr int FH = KT2 / 2, CH = KT / 2, NF = 3 * FH;   // column tiles of a fine and a coarse chain, fragments
-  const int g = blockIdx.x % 8, k = blockIdx.x / 8;
+  const int b = wr_block(a.by_xcd), g = (b - a.rot) & 7, k = b / 8;
   if (g >= a.G || k >= NW) return;
   __shared__ __align__(16) unsigned char img[KT2 * WR_FRAGP];   // operand image of h
   __shared__ float part[24 * LV * 16];               // [chain][unit tile][gate][LV][16] products

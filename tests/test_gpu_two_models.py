@@ -80,3 +80,66 @@ def test_a_captured_call_leaves_other_models_alone(kind):
         b.check()
         a.run()
         a.check()
+
+
+def at_once(calls):
+    """Every call on a stream of its own, enqueued one after another."""
+    streams = [torch.cuda.Stream() for _ in calls]
+    for c in calls:
+        c.clear()
+    for c, s in zip(calls, streams):
+        c.run(s)
+    torch.cuda.synchronize()
+    for c in calls:
+        c.check()
+
+
+def fused896(seed):
+    return synth.make_fused_weights(896, F=2, seed=seed, cond_dim=0)
+
+
+def test_more_fused_models_than_xcds():
+    """A fused grid takes 28 of an XCD's 32 CUs: eight of them run on an XCD each, the ninth waits."""
+    at_once([Call(fused896(s), 1, 600).alone() for s in range(9)])
+
+
+def test_kinds_of_models_beside_each_other():
+    """Dense, fused, scoring, subscale, a small model and side-by-side utterances of another dense model."""
+    ws = synth.make_weights(256, seed=4, cond_dim=8, B=4, ctx_dim=64)
+    ws["F"] = 1
+    calls = [Call(synth.make_weights(896, seed=1, cond_dim=8), 1, 700), Call(fused896(2), 2, 600),
+             Call(ws, 2, 4 * 300), Call(synth.make_weights(256, seed=3, cond_dim=8), 3, 500),
+             Call(synth.make_weights(896, seed=6, cond_dim=8), 1, 650)]
+    for c in calls:
+        c.alone()
+    sc = wavernn.Model(synth.make_weights(896, seed=5, cond_dim=0), max_streams=9)
+    tgt = cuda(synth.target_signal(9, 400, seed=2, kind="uniform"))
+    one = {S: sc.score(tgt[:S].contiguous(), logits=False)["nll"] for S in (1, 9)}
+    sc.device_status()
+    s = torch.cuda.Stream()
+    for _ in range(3):
+        r = {S: sc.score(tgt[:S].contiguous(), logits=False, stream=s)["nll"] for S in (1, 9)}
+        at_once(calls)
+        sc.device_status(s)
+        for S in r:
+            assert torch.equal(r[S], one[S])
+
+
+def test_a_call_that_does_not_fit_waits_for_a_long_one():
+    """A batched call that fills every XCD for over two seconds (a bounded wait's limit), and a fused
+    call on another stream meanwhile: the second starts when the first has ended."""
+    long = Call(synth.make_weights(896, seed=1, cond_dim=0), 64, 320_000)
+    short = Call(fused896(2), 1, 1200).alone()
+    short.clear()
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    e0, e1, e2 = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+    e0.record(s1)
+    long.run(s1)
+    e1.record(s1)
+    short.run(s2)
+    e2.record(s2)
+    torch.cuda.synchronize()
+    assert e0.elapsed_time(e1) > 2000, "the long call must outlast a bounded wait"
+    assert e1.elapsed_time(e2) > 0
+    long.m.device_status()
+    short.check()
