@@ -1084,9 +1084,9 @@ wavernn_status build_score(wavernn_model* m, const wavernn_weights* w) {
   for (int LV = 1; LV <= 8 && LV < 2 * m->cfg.max_streams; LV *= 2)
   {
     int per_cu = 0;
-    if ((s = check_coresident(m, wr_score_kernel_ptr(KT2, LV), 8 * (H / 32), wr_load(8, H / 32, 0), 0, "scoring",
-                              &per_cu)) != WAVERNN_OK)
-      return s;
+    const void* k = wr_score_kernel_ptr(KT2, LV);
+    if (!k) break;   // (a hidden size without batched kernels: create refuses several utterances)
+    if ((s = check_coresident(m, k, 8 * (H / 32), wr_load(8, H / 32, 0), 0, "scoring", &per_cu)) != WAVERNN_OK) return s;
     m->score_per_cu = LV > 1 ? std::min(m->score_per_cu, per_cu) : per_cu;
   }
   if ((s = m->alloc(&m->d_sxc, (size_t)8 * score_words(H, 8) * 4)) != WAVERNN_OK) return s;

@@ -241,7 +241,9 @@ static const void* score_ptr(int KT2) {
     case 4: return (const void*)wr_score_kernel<4, LV>;
     case 8: return (const void*)wr_score_kernel<8, LV>;
     case 12: return (const void*)wr_score_kernel<12, LV>;
-    case 16: return (const void*)wr_score_kernel<16, LV>;
+    case 16:   // H = 512 has no batched kernel, so its models serve one utterance
+      if constexpr (LV == 1) return (const void*)wr_score_kernel<16, 1>;
+      else return nullptr;
     case 28: return (const void*)wr_score_kernel<28, LV>;
     default: return nullptr;
   }
