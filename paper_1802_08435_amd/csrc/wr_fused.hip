@@ -166,10 +166,12 @@ __device__ __forceinline__ void fused_head_role(const PersistArgs& a, int j, uns
   // every head does) once all carry `tag`; the first probe waits a little
   auto gather = [&](const xw* src, uint32_t tag, float* s) -> bool {
     // first probe, x 64 clocks: with the whole grid on one XCD the waves' polls
-    // share its L2, and a probe that comes back empty holds up the next.  H = 896,
-    // ms for 24,000 samples: 3 53.6, 6 52.3, 10 49.1, 14 48.3, 18 49.8; H = 128,
-    // whose layers are shorter, us for 342: 3 504, 6 532, 10 569
-    __builtin_amdgcn_s_sleep(KH >= 4 ? 14 : 3);
+    // share its L2, and a probe that comes back empty holds up the next; longer
+    // layers bring the partials later.  us a step at 3, 6, 10 and 14:
+    //   H = 128 2.65 2.78 3.00 3.21   256 3.13 3.09 3.24 3.46   384 3.34 3.23 3.36 3.59
+    //   H = 512 3.57 3.46 3.42 3.60   896 4.44 4.29 3.75-4.09 3.97-4.02 (three devices: 14 varies less)
+    // (units on another XCD: 6 best or within 1% at every size, 14 2 to 3% slower)
+    __builtin_amdgcn_s_sleep(KH >= 5 ? 14 : KH >= 4 ? 10 : KH >= 2 ? 6 : 3);
     return sum_parts<NH>(src, P.x_ps, 0, NH, lane, tag, s, a);
   };
   // Philox blocks of steps t .. t+63 (both sub-tensors: counter (position, 2 u + s),
@@ -197,7 +199,8 @@ __device__ __forceinline__ void fused_head_role(const PersistArgs& a, int j, uns
   float cu = 0.0f, cr = 0.0f, ce = 0.0f, cie = 0.0f;
   auto coarse_pre = [&](uint32_t tag, float xc0, float xc1, int64_t t) {
     if (!gate) return;
-    __builtin_amdgcn_s_sleep(14);   // (after the draw wave's first probe; 8 and 20: 3% and 1% slower at H = 896)
+    __builtin_amdgcn_s_sleep(14);   // (after the draw wave's first probe; 8 and 20: 3% and 1% slower at H = 896,
+                                    // 128 to 512: 8 within 2% either way)
     prefetch_coarse(t);
     const xw* ps[3] = {GA + u, GA + Hh + u, GA + 2 * Hh + u};
     float v[3];
