@@ -285,7 +285,8 @@ def main() -> int:
             m.set_placement(args.placement)
             k = max(args.placement, 0)
             placement = {"candidate": k, "tuned": False}
-        placement.update(heads_xcd=k // 8, units_xcd="all" if k % 8 == k // 8 else k % 8)
+        spread = k % 8 == k // 8 and path != "fused"      # (a fused grid's units sit beside its heads then)
+        placement.update(heads_xcd=k // 8, units_xcd="all" if spread else k % 8)
         path, grid, block = m.path(S)
     feat_np = synth.features(S, T, per_stream_seed=S > 1)
     feat = torch.from_numpy(feat_np).cuda()

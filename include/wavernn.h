@@ -368,9 +368,11 @@ wavernn_status wavernn_debug_sync_floor(wavernn_model* m, int64_t n_steps, doubl
  * [n_streams][n_samples] (n_samples a multiple of B).  Every layer runs as one
  * matrix-core GEMM over all rows of all sub-tensors, activations at fp32
  * accuracy (bf16 high and low parts) against the bf16 weights.  Scratch
- * activations are the model's (grown on demand: 4 (Rc + Cc + 32) bytes per
- * row of every sub-tensor).  Errors: E_INVALID (no CNN, bad sizes), E_OOM,
- * E_HIP. */
+ * activations are the model's (grown on demand: 4 (2 Rc + Cc + 2B rounded up to
+ * a multiple of 32) bytes per row of every sub-tensor, the residual kept in fp32 and as its two bf16
+ * parts; sampling keeps 8 Rc bytes more for every row of the call, and GEMMs of
+ * few rows a workspace of their K groups' sums).  Errors: E_INVALID (no CNN, bad
+ * sizes), E_OOM, E_HIP. */
 wavernn_status wavernn_ctx_cnn_run(wavernn_model* m, int32_t n_streams, int64_t n_samples, const uint16_t* seq_dev,
                                    float* out_dev, void* stream);
 

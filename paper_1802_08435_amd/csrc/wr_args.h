@@ -146,7 +146,7 @@ struct BatchArgs {
 };
 
 // One GEMM of the conditioning CNN: dst[m][n] (epilogue) over
-// acc = sum_k A[m][k] W[n][k], n < N, on 128 x 128 tiles.
+// acc = sum_k A[m][k] W[n][k], n < N, on tiles of 64, 96 or 128 rows x 128 columns.
 #define WR_CNN_MAXB 64   // sub-tensors of a streamed CNN run at most
 // Activations that a GEMM reads are split rows: a row of width K is K / 32
 // groups of 32 bf16 high parts and then the 32 bf16 remainders of the same

@@ -219,7 +219,7 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
     __syncthreads();
   };
   // class tiles 2*wave, 2*wave+1 over this head's 64 columns, for all vectors
-  bool lx = false;   // the group's heads share one XCD: partials and classes into its L2
+  bool lx = false;   // the whole group (heads and units) on one XCD: its words into that L2
   auto second_layer = [&](const bf16x8* W, xw* dst, uint32_t tag) {
     f32x4 A = {0, 0, 0, 0}, B = {0, 0, 0, 0};
     if (!FL) {
@@ -492,7 +492,7 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
   const int bw = wave;                              // vector (in the group) drawn by this wave, if below L
   const int vw = min(v0 + bw, a.S - 1);
   const size_t ob = obase(a, vw);
-  auto fill_batch = [&](int64_t t, int buf) {       // wave w: uniforms / targets of its owned vector
+  auto fill_batch = [&](int64_t t, int buf) {       // wave w: uniforms / targets of vector w
     const int64_t s = t + lane, p = vpos<LAG>(a, vw, s);
     if (s < a.T && p >= 0 && p < a.rows) {
       float uc, uf;

@@ -1033,8 +1033,7 @@ wavernn_status build_cnn(wavernn_model* m, const wavernn_ctx_cnn* n) {
 }
 
 // Teacher-forced scoring on the dense batch-1 plan: the recurrence kernel
-// (the plan's units, heads that evaluate their own slices from the given
-// bytes) and the output layers as GEMM fragments for the matrix cores: O1 and
+// (one kind of workgroup: 32 units' rows of R and their gates) and the output layers as GEMM fragments for the matrix cores: O1 and
 // O3 with their rows padded to NP = Hh rounded up to 128, O2 and O4 with their
 // columns padded to NP, biases rounded like the sampling heads' and padded
 // with zeros (a padded first-layer row is relu(0) = 0 and meets a zero column).
@@ -1101,8 +1100,8 @@ struct CnnRows {   // which utterance rows the blocks of a CNN run cover
 };
 
 // A CNN GEMM's K loop sums in groups of CNN_GROUP K-steps (always, so that results
-// never depend on the rows of a run); a GEMM with fewer tiles than CUs runs
-// each group on its own workgroup and adds them in wr_cnn_reduce.
+// never depend on the rows of a run); a GEMM with few tiles and many groups
+// (cnn_split) runs each group on its own workgroup and adds them in wr_cnn_reduce.
 #define CNN_GROUP 6
 #define CNN_SLOTS 512   // workgroups the card holds at once (two a CU)
 // Rows of a tile: 32 MI, the MI whose rounds over the slots take least (a round
@@ -1117,8 +1116,8 @@ int cnn_mi(int64_t M, int N) {
   }
   return best;
 }
-// Split where 64-row tiles fill less than half of the slots and the K loop has
-// enough groups to be worth a reduction launch.
+// Split where 64-row tiles fill less than half of the slots (fewer than 256) and
+// the K loop has at least 8 groups, enough to be worth a reduction launch.
 int cnn_split(int64_t M, int N, int K) {
   const int64_t tiles = (M + 63) / 64 * (N / CNN_TN), groups = (K / 32 + CNN_GROUP - 1) / CNN_GROUP;
   return tiles < CNN_SLOTS / 2 && groups >= 8 ? (int)groups : 1;
@@ -1673,8 +1672,8 @@ wavernn_status run_persist(wavernn_model* m, const RunIO& io) {
 }
 
 // Teacher-forced scoring of one or more utterances on the dense batch-1 plan
-// (Sec. 5's NLL; Eq. 2 with the bytes given).  Per utterance the scoring
-// kernel runs the recurrence and writes h after every step; then the output
+// (Sec. 5's NLL; Eq. 2 with the bytes given).  One launch of the scoring
+// kernel runs the recurrence of every utterance and writes h after every step; then the output
 // layers of all steps run as GEMMs on the matrix cores (O2 relu(O1 y_c + b1)
 // + b2, the same for the fine half; up to 65,536 steps at a time) and the
 // NLL as one reduction per step.

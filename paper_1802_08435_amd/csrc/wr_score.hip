@@ -16,7 +16,8 @@
 // fits one XCD (28 of its 32 CUs at H = 896) and publishes into its L2 when it
 // finds itself there.  H = 896, us a step, with 56 workgroups of 16 units over
 // all XCDs (grids of several utterances on streams of their own) and now: one
-// utterance 2.27 -> 1.42, 21 utterances 4.2 -> 2.4 with their output layers.
+// utterance 2.27 -> 1.42, 21 utterances 5.3 -> 2.2 with their output layers (4.1
+// before where the four grids' streams had a hardware queue each).
 //
 // The products and the gate arithmetic are the sampling kernel's operation for
 // operation, so a scored trajectory reproduces the sampler's state bit for
