@@ -379,8 +379,9 @@ def main() -> int:
         "sync_floor": None if floor_us is None else {
             "us_per_step": round(floor_us, 4), "frac_of_step": round(floor_us / us_per_sample_step, 4)},
         "limiter": ("cross-CU exchange latency: the weights stay in VGPRs and LDS, so the HBM roofline below is "
-                    "the weights' algorithmic bytes per step; the synchronization floor of the same launch "
-                    f"(its exchanges and waits, no arithmetic) takes {floor_us / us_per_sample_step:.0%} of the step")
+                    "the weights' algorithmic bytes per step; the synchronization floor kernel (the launch's exchanged "
+                    "words with the floor kernel's own polls, no arithmetic) takes "
+                    f"{floor_us / us_per_sample_step:.0%} of the step's time")
                    if floor_us is not None else None,
         "roofline": {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": traffic,

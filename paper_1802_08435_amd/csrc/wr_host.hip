@@ -296,7 +296,7 @@ class CallScope {
     XcdLoad want = load(0), held = {};
     std::vector<wavernn_model*>& others = D_.others;
     others.clear();
-    (void)finished(m_);                   // (its ended calls no longer count)
+    if (D_.models.size() > 1) (void)finished(m_);   // (its ended calls no longer count)
     for (wavernn_model* o : D_.models)    // in flight, and not before this call on its own stream
       if (o != m_ && o->busy && (o->busy_st != st_ || st_ == hipStreamPerThread) && !finished(o)) others.push_back(o);
     std::sort(others.begin(), others.end(), [](auto* a, auto* b) { return a->busy_seq < b->busy_seq; });
@@ -2157,7 +2157,7 @@ wavernn_status wavernn_create(const wavernn_config* cfg, const wavernn_weights* 
   }
   if (m->path == PATH_SMALL) m->by_xcd = 1;   // (its blocks have no roles)
   else if (s == WAVERNN_OK) s = find_xcds(m);
-  if (s == WAVERNN_OK && hipEventCreateWithFlags(&m->done, hipEventDisableTiming) != hipSuccess)
+  if (s == WAVERNN_OK && hipEventCreateWithFlags(&m->done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess)
     s = fail(WAVERNN_E_HIP, "hipEventCreateWithFlags failed");
   if (s != WAVERNN_OK) {
     delete m;
