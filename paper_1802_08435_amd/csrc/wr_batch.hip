@@ -338,7 +338,7 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
     }
   };
   // This head's slice of y_c, for the units: behind the barrier that follows
-  // the gates, so that every unit's words of the step are in.  A unit publishes
+  // the gates (and after the partial logits, which are waited for sooner), so that every unit's words of the step are in.  A unit publishes
   // its words of step t + 1 only after reading all of h of step t, so the slice
   // of step t may be replaced then, and not sooner: the publishing wave itself
   // reads the words of three unit workgroups, and another unit may
@@ -546,11 +546,11 @@ __device__ __forceinline__ void bhead_role(const BatchArgs& a, int g, int j, uns
     }
     __syncthreads();
     if (misc[0]) return;
-    if (!SLICE) publish_yc(tag);
     if (trw) trace_at(a, t, 1);
     // (2) O1 rows, relu, O2 columns -> partial coarse logits of 8 vectors
     first_layer(W1, imc, b1r);
     second_layer(W2, PCo, tag);
+    if (!SLICE) publish_yc(tag);                      // (the units need it no sooner: y_f is two hops away)
     if (trw) trace_at(a, t, 3);
     if (tid < L && t + 1 < a.T) cb_next(t);           // (this step's offsets have been used)
     // (3) every vector's sums over the heads and coarse draw (wave w: vector w)
@@ -938,8 +938,8 @@ __device__ __forceinline__ void bunit_role(const BatchArgs& a, int g, int k, uns
 template <int KH, bool CTX, int L, bool LAG, bool FL>
 __global__ __launch_bounds__(WR_THREADS, 1) void wr_batch_kernel(BatchArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
-  int g = 0;
-  const int r = wr_batch_role(a.P, wr_block(a.P.by_xcd), &g);
+  int g = 0, r = wr_batch_role(a.P, wr_block(a.P.by_xcd), &g);
+  asm volatile("" : "+s"(r), "+s"(g));   // (worked out once: re-derived where they are used, 2% slower at subscale 16)
   if (r < 0) return;
   if (r < a.P.NH) bhead_role<KH, CTX, L, LAG, FL>(a, g, r, lds);
   else bunit_role<KH, CTX, L, LAG, FL>(a, g, r - a.P.NH, lds);

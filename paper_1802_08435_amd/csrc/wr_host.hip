@@ -197,7 +197,7 @@ struct wavernn_model {
   int load_per_cu = 1;
   unsigned fan_used = 0;             // internal streams they use
   int home = 0;                      // XCDs by which a captured call's placement is moved
-  int by_xcd = 0;                    // roles go by the XCDs that blocks run on (wr_block)
+  int by_xcd = 0;                    // 7: roles go by the XCDs that blocks run on (wr_block)
   int xcd_cus = 32, pk_per_cu = 1, score_per_cu = 1, batch_per_cu = 1;   // CUs of an XCD, workgroups of a kernel on one
   // batched path (several utterances per launch)
   bool has_batch = false;
@@ -1925,7 +1925,7 @@ wavernn_status find_xcds(wavernn_model* m) {
   void* args[] = {&d};
   HIPOK(hipLaunchKernel(wr_xcd_kernel_ptr(), dim3(N), dim3(64), args, 0, nullptr));
   HIPOK(hipMemcpy(h, d, sizeof h, hipMemcpyDeviceToHost));
-  m->by_xcd = 1;
+  m->by_xcd = 7;
   for (int b = 0; b < N; ++b)
     if (h[b] > 7 || ((h[b] - h[0] - b) & 7)) m->by_xcd = 0;
   m->plan.by_xcd = m->by_xcd;
@@ -2155,7 +2155,7 @@ wavernn_status wavernn_create(const wavernn_config* cfg, const wavernn_weights* 
     s = m->alloc(&m->d_err, 64);
     if (s == WAVERNN_OK && hipMemset(m->d_err, 0, 64) != hipSuccess) s = fail(WAVERNN_E_HIP, "hipMemset failed");
   }
-  if (m->path == PATH_SMALL) m->by_xcd = 1;   // (its blocks have no roles)
+  if (m->path == PATH_SMALL) m->by_xcd = 7;   // (its blocks have no roles)
   else if (s == WAVERNN_OK) s = find_xcds(m);
   if (s == WAVERNN_OK && hipEventCreateWithFlags(&m->done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess)
     s = fail(WAVERNN_E_HIP, "hipEventCreateWithFlags failed");

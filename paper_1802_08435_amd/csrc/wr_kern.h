@@ -291,7 +291,7 @@ __device__ __forceinline__ void trace_at(const A& a, int64_t t, int slot) {
 __device__ __forceinline__ unsigned wr_xcd() { return __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u; }
 // The number of this block that roles go by (see wr_role): its row of 8 and its XCD.
 __device__ __forceinline__ int wr_block(int by_xcd) {
-  return by_xcd ? (int)((blockIdx.x & ~7u) | (wr_xcd() & 7u)) : (int)blockIdx.x;
+  return (int)((blockIdx.x & ~(unsigned)by_xcd) | (wr_xcd() & (unsigned)by_xcd));
 }
 
 // Words that only the lead workgroups read (partial logits, the mirrors'

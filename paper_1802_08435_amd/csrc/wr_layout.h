@@ -95,7 +95,7 @@ struct PersistPlan {
   int BH, BW, BR, u_wb;   // block-sparse units: block shape (4 x 4 or 16 x 1), block-rows per unit,
                           // bytes of the weights before the block-column indices
   int grid;               // blocks: head j at block 8j + hx, units on the others (launched: whole rows of 8)
-  int by_xcd;             // 1: blocks are numbered by the XCD they run on, 0: by blockIdx (wr_block)
+  int by_xcd;             // 7: blocks are numbered by the XCD they run on, 0: by blockIdx (wr_block)
   int hx, uxm;            // placement: heads on XCD hx, units on the XCDs of the bits of uxm
   int hw_frags;           // head fragments per wave: O1[KH], O3[KH], O2[2 KO], O4[2 KO]
   int u_lds_w;            // unit LDS block: dense R tiles, or the block-sparse records

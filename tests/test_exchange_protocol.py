@@ -25,8 +25,8 @@ polls and publishes its part of the head's own slice, and the heads exchange
 slices.  In both modes every head sums and draws every vector; one writer head
 per vector's sample word.  `guard`: y_c is published only after a word of the step has come
 from every unit of the group, so that none still has to read the y_c it
-replaces: ALL behind the barrier that follows the gates, SLICE once the
-publishing wave itself has seen a word of every unit.
+replaces: ALL behind the barrier that follows the gates (and after the partial
+logits), SLICE once the publishing wave itself has seen a word of every unit.
 
 The units wait for the drawn samples of step t - A of every lane of their
 utterance: at the start of the step with a context lead A > 0 (before the
@@ -105,10 +105,10 @@ def run(mode="ALL", G=8, NH=2, L=2, B=16, F=4, A=1, rows=8, SS=None, seed=0, idl
                                 yield wait1((half, g, jj, pp), tag)
                 n += 1
                 yield from barrier(g, j, n)
-                if publishes and late:
-                    yield pub((half, g, j, p), tag)
                 if p == 0:
                     yield pub((out, g, j), tag)
+                    if late:
+                        yield pub((half, g, j, p), tag)
                     for jj in range(NH):
                         yield wait1((out, g, jj), tag)
                     if out == "PF":
