@@ -41,7 +41,7 @@
  *    if it must (results do not depend on it), and if it fits nowhere beside the
  *    calls in flight, it waits on its stream for the oldest of them.  At H = 896 a
  *    fused utterance and each group of a scoring or batched call keep 28 CUs of one
- *    XCD, a plain utterance 14 of one and 3 or 4 of the others: a plain and
+ *    XCD, a plain utterance 14 of one and 4 of each other: a plain and
  *    a fused or scored utterance run together, two plain utterances side by side
  *    and a fused one do not.  Calls captured into a graph are outside this: they
  *    are placed by the order in which the models were created (the first

@@ -254,7 +254,7 @@ namespace {
 // by 1 .. 7 XCDs) that fits beside all of them; if none does, it waits on its
 // stream for the oldest of them until it does.  A fused grid, a scoring group
 // and a batched group take 28 of an XCD's 32 CUs at H = 896, a dense grid 14
-// on one and 3 or 4 on the others.
+// on one and 4 on each other.
 //
 // A call that is being captured into a graph neither waits nor is entered (its
 // launches run when the graph does); its placement is moved by the model's
